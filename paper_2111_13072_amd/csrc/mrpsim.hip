@@ -170,6 +170,10 @@ struct Tables {
     const float4 *lw4_32;
 };
 
+// The moments kernel splits the orders m over the waves of its blocks, in up to
+// this many slices (kWavesPerBlock per block of a group).
+constexpr int kMaxMSlices = 16;
+
 // Channels are kept in "stream order": m = 0..m_top outer, l = max(m,1)..L
 // inner, cos then sin for m > 0.  l = 0 has no channel: its field is Gauss's
 // law over the radial order (computed in the field kernel).
@@ -188,6 +192,8 @@ struct KParams {
     int fp32;       // SIM_FP32_COMP
     int field_only; // evaluation without a step: every used member runs
     int fuse_keys;  // the push prepares the next step's sort records
+    // moments kernel: slice s of m is [m_slice[s], m_slice[s + 1])
+    uint8_t m_slice[kMaxMSlices + 1];
 };
 
 // The push's tail takes over the key pass from this many tiles on: the
@@ -559,19 +565,20 @@ __global__ __launch_bounds__(kBlock) void k_sort_rank_move(Map mp, const OrdRec 
 // kernel sums the rescaled Qh_l^m = Q_l^m / N_lm (a three-operation
 // recurrence); the carries restore N_lm.
 
-// A slot holds two channels, one LDS row each: the wave's 64 lanes after the
-// fold across 16-lane rows, four quarter rows of 16 partial sums: interior of
-// half 0 (lanes 0-15), exterior of half 0 (16-31), interior of half 1 (32-47)
-// and exterior of half 1 (48-63), quarter q at row offset q * kQuarterOff.  A
-// batch of kSlots slots is read back by pairs of lanes, each pair summing one
-// quarter row (kPartials entries each, then one lane exchange).  With
-// kQuarterOff = 17 and kRowLen = 68 the 16 lanes of each quarter of the wave
-// start their reads on distinct banks.
-constexpr int kSlots = 4;                          // slots per batch
-constexpr int kQuarterOff = 17;
-constexpr int kRowLen = 4 * kQuarterOff;
-constexpr int kPartials = 8;                       // entries per lane: 16 / 2
-static_assert(kWave == 2 * (2 * kSlots) * 4, "one lane pair per quarter row of a batch");
+// A lane holds four consecutive particles of the group (lane i: slots 4 i ..
+// 4 i + 3, so eight lanes hold a half tile) and adds its particles' terms in
+// registers; the eight lanes of a half then meet in LDS.  kMomSlots channels
+// make a batch: per channel and side (interior, exterior) one LDS row of the
+// wave's 64 partial sums, the eight of a half at kMomHalfOff doubles.  A batch
+// is read back with one (channel, side, half) per lane: its eight entries as
+// four 16-byte reads, whose lanes fall on distinct banks by the 80-byte stride.
+constexpr int kMomParts = kGroupSlots / kWave;     // particles per lane
+constexpr int kMomSlots = 4;
+constexpr int kMomLanes = kHalf / kMomParts;       // lanes of a half tile
+constexpr int kMomHalves = kGroupSlots / kHalf;    // halves of a group
+constexpr int kMomHalfOff = kMomLanes + 2;
+constexpr int kMomRow = kMomHalves * kMomHalfOff;
+static_assert(2 * kMomSlots * kMomHalves == kWave, "one lane per sum of a batch");
 
 // Orders this wave's LDS accesses at this point: LDS instructions of one wave
 // complete in issue order, so rows a wave wrote are visible to its later
@@ -582,18 +589,6 @@ __device__ inline void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Exchange the odd 16-lane rows of a with the even rows of b: afterwards a
-// holds the rows {a0, b0, a2, b2} and b the rows {a1, b1, a3, b3}.
-__device__ inline void swap_rows16(double &a, double &b)
-{
-    const uint64_t ua = (uint64_t)__double_as_longlong(a), ub = (uint64_t)__double_as_longlong(b);
-    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)ua, (uint32_t)ub, false, false);
-    const auto hi =
-        __builtin_amdgcn_permlane16_swap((uint32_t)(ua >> 32), (uint32_t)(ub >> 32), false, false);
-    a = __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | (uint64_t)lo[0]));
-    b = __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | (uint64_t)lo[1]));
 }
 
 // The value of another lane of this lane's quad, through DPP: kPerm is a
@@ -609,251 +604,267 @@ __device__ inline double dpp_quad(double v)
     return __longlong_as_double((long long)(((uint64_t)phi << 32) | plo));
 }
 
-// A tile's row of H: [interior | interior, half 0 | exterior | exterior,
-// half 1 | charge, unused]: the interior sums of the group's tiles before
-// this one, the halves' own sums (a half's coefficients take the other half's
-// part from them), the exterior sums of the group's tiles after this one, and
-// the charge of the group's tiles before this one.
-
-// The value of lane + 4 within its row of 16 lanes (DPP row_shl:4; the last
-// four lanes of a row read zero).
-__device__ inline double dpp_row_shl4(double v)
+// The value of the lane four below within the upper half of every 8 lanes, zero
+// in the lower (DPP row_shr:4 into banks 1 and 3 of a row of 16 lanes).
+__device__ inline double dpp_shr4_odd_banks(double v)
 {
     const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const uint32_t plo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x104, 0xF, 0xF, true);
+    const uint32_t plo =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, 0x114, 0xF, 0xA, false);
     const uint32_t phi =
-        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x104, 0xF, 0xF, true);
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), 0x114, 0xF, 0xA, false);
     return __longlong_as_double((long long)(((uint64_t)phi << 32) | plo));
 }
 
+// A tile's row of H: per channel {interior sums of the group's tiles before
+// this one, interior sum of half 0, exterior sums of the group's tiles after
+// this one, exterior sum of half 1}, then the charge of the group's tiles
+// before this one.
+//
+// One block per group and kWavesPerBlock slices of m: every wave goes through
+// all 256 particles of the group for its slice's channels.  FP64 VALU is what
+// bounds the kernel (9 operations per (l, m), particle and side pair); a
+// layout with one particle per lane spent twice that on the cross-lane folds
+// (v_permlane16_swap costs 1.5 FP64 FMAs, and v_mfma_f64_4x4x4 3.6, on the
+// same unit).  Slicing m over the waves, not the particles, keeps the group's
+// scan over its tiles inside a wave, without barriers, and lets a small launch
+// spread one group over several blocks (21,347 particles at l_max 32: the
+// evaluation 344 -> 222 us).  1.6e7 particles, l_max 16: 1.94 -> 1.29 ms.
 template <bool FULL>
-__global__ __launch_bounds__(kBlock, 8) void k_moments(Map mp, State B, Tables tb, KParams kp,
-                                                    double *H, double *GS)
+__global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, State B, Tables tb, KParams kp,
+                                                       double *H, double *GS)
 {
-    // Per wave (one tile of 64 particles), the sums of q R (interior) and
-    // q I (exterior) of every channel over each half of the tile, in a tree:
-    //  1. R and I of one channel are folded across 16-lane rows (lanes 0-15
-    //     then hold R over particle pairs of half 0, lanes 16-31 I of half 0,
-    //     lanes 32-63 the same for half 1), and the result is one LDS row of a
-    //     slot; a slot holds two channels (cos and sin of one (l, m), or two
-    //     degrees of m = 0);
-    //  2. every kSlots slots each pair of lanes sums one quarter row
-    //     (kPartials entries each, then a lane exchange); the pairs of half 0
-    //     add half 1's sum from four lanes on (the whole-tile sums), and the
-    //     halves' own sums (interior of half 0, exterior of half 1) go to the
-    //     tile's row of H;
-    //  3. every kXBatches batches the four waves of the block (the group's
-    //     tiles) trade their whole-tile sums through LDS, one channel and
-    //     side per lane: each stores in its tile's row of H the interior
-    //     sums of the tiles before it and the exterior sums of those after
-    //     it; the last and first wave store the group's interior and
-    //     exterior totals in its row of the carry scan (GS: interior,
-    //     exterior, charge).
-    // The m = 0 block is padded to an even count with a zero channel, so a
-    // slot always holds two positions of the padded channel order.
-    __shared__ double buf[kWavesPerBlock][kSlots * 2 * kRowLen];
-    // whole-tile sums of kXBatches batches, per wave (interior, exterior):
-    // one channel and side per lane of an exchange (one set, with a barrier
-    // before and after its reads, keeps eight waves per SIMD)
-    constexpr int kXBatches = 4;
-    constexpr int kXLen = kXBatches * 2 * kSlots;
-    static_assert(2 * kXLen <= kWave, "one channel and side per lane in an exchange");
-    __shared__ double xch[kWavesPerBlock][2][kXLen];
-    __shared__ double qx[kWavesPerBlock];
+    __shared__ double buf[kWavesPerBlock][2 * kMomSlots * kMomRow];
     const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
+    const int w = (int)uniform_u32(threadIdx.x >> 6);
     const uint32_t group = blockIdx.x;
-    const uint32_t tile = uniform_u32(group * kTilesPerGroup + w);
-    // the member (the same for the group's four tiles: a member's slots are
-    // whole groups); n = its alive count, lt = the tile's index in it
-    bool tile_ok = false, halves = false;
-    uint32_t n = 0, lt = 0;
-    if ((int)tile < kp.n_tiles) {
-        const uint32_t mb = uniform_u32(mp.tile_member[tile]);
-        if (mb != kNone && member_runs(mp.seg[mb], mp.ctl[mb], kp)) {
-            tile_ok = true;
-            n = mp.ctl[mb].n_live;
-            lt = tile - mp.seg[mb].t0;
-            // the halves' own sums only where the field kernel uses them
-            halves = uniform_u32((uint32_t)mp.seg[mb].near_w) == (uint32_t)kHalf;
-        }
+    const uint32_t mb = uniform_u32(mp.tile_member[group * kTilesPerGroup]);
+    if (mb == kNone || !member_runs(mp.seg[mb], mp.ctl[mb], kp)) return;
+    // the group's particles: slots first .. first + count of the member's n_live
+    const uint32_t first = (group - mp.seg[mb].g0) * kGroupSlots;
+    const uint32_t n = mp.ctl[mb].n_live;
+    const int count = n > first ? (int)min(n - first, (uint32_t)kGroupSlots) : 0;
+
+    double x[kMomParts], y[kMomParts], z[kMomParts], q[kMomParts];
+    const size_t p = (size_t)group * kGroupSlots + kMomParts * lane;
+    uint64_t ions[kMomParts];
+#pragma unroll
+    for (int j = 0; j < kMomParts; ++j) {
+        const bool valid = kMomParts * lane + j < count;
+        x[j] = valid ? B.x[p + j] : 0.0;
+        y[j] = valid ? B.y[p + j] : 0.0;
+        z[j] = valid ? B.z[p + j] : 2.0;
+        const bool ion = valid && (B.uid[p + j] & kIonBit) != 0;
+        q[j] = valid ? (ion ? 1.0 : kQ) : 0.0;
+        ions[j] = __ballot(ion);
     }
-    const uint32_t p = tile * kWave + lane;
-    const bool valid = tile_ok && lt * kWave + lane < n;
-    double x = 0.0, y = 0.0, z = 2.0;
-    bool ion = false;
-    if (valid) {
-        x = B.x[p];
-        y = B.y[p];
-        z = B.z[p];
-        ion = (B.uid[p] & kIonBit) != 0;
-    }
-    const double q = valid ? (ion ? 1.0 : kQ) : 0.0;
-    const double r2 = x * x + y * y + z * z;
-    const double inv_r2 = 1.0 / r2;
-    const double inv_r = 1.0 / sqrt(r2);
-    const int L = kp.L;
-    const int C = kp.C;
-    double *Ht = H + (size_t)tile * kp.HW;
+    const int L = kp.L, C = kp.C;
+    double *Hg = H + (size_t)group * kTilesPerGroup * kp.HW;
     double *Gs = GS + (size_t)group * kp.SW;
-    {
-        // the tile's charge (exact: counts of ions and electrons), then the
-        // group's tiles before this one (in tile order) and the group's total
-        const uint64_t vb = __ballot(valid), ib = __ballot(valid && ion);
-        const int n_val = __popcll(vb), n_ion = __popcll(ib);
-        if (lane == 0) qx[w] = (double)n_ion + kQ * (double)(n_val - n_ion);
-        __syncthreads();
-        if (tile_ok && lane == 0) {
-            double sq = 0.0;
-            for (int k = 0; k < w; ++k) sq += qx[k];
-            Ht[4 * C] = sq;
-            if (w == kWavesPerBlock - 1) Gs[kp.C2] = sq + qx[w];
+    const int turn = (int)(group & (kWavesPerBlock - 1));
+    const int slice = (int)blockIdx.y * kWavesPerBlock + ((w + turn) & (kWavesPerBlock - 1));
+    if (slice == 0) {
+        // charge of the group's tiles before each one, and of the group
+        // (exact: counts of ions and electrons)
+        double sq = 0.0;
+        for (int t = 0; t < kTilesPerGroup; ++t) {
+            const int n_val = min(max(count - t * kWave, 0), kWave);
+            int n_ion = 0;
+#pragma unroll
+            for (int j = 0; j < kMomParts; ++j)
+                n_ion += __popcll((ions[j] >> (t * (kWave / kMomParts))) & 0xffffull);
+            if (lane == t) Hg[(size_t)t * kp.HW + 4 * C] = sq;
+            sq += (double)n_ion + kQ * (double)(n_val - n_ion);
         }
+        if (lane == 0) Gs[kp.C2] = sq;
+    }
+    const int m_begin = kp.m_slice[slice], m_end = kp.m_slice[slice + 1];
+    if (m_begin >= m_end) return;
+
+    double r2[kMomParts], inv_r2[kMomParts];
+    double cq[kMomParts], sq[kMomParts], smm[kMomParts];   // q C_m, q S_m, r^-(2m+1)
+#pragma unroll
+    for (int j = 0; j < kMomParts; ++j) {
+        r2[j] = x[j] * x[j] + y[j] * y[j] + z[j] * z[j];
+        inv_r2[j] = 1.0 / r2[j];
+        smm[j] = 1.0 / sqrt(r2[j]);
+        cq[j] = q[j];
+        sq[j] = 0.0;
     }
 
     double *wb = buf[w];
-    // writer: lane -> its entry of a row
-    double *wr = wb + (lane >> 4) * kQuarterOff + (lane & 15);
-    // reader: lane pair v = 4 rr + rq (row rr = 2 s + j of the batch: slot s,
-    // its channel j; quarter rq) sums that quarter row; part t of it
-    const int v = lane >> 1, t = lane & 1;
-    const int rr = v >> 2, rq = v & 3;
-    const int rs = rr >> 1;
-    const double *rd = wb + rr * kRowLen + rq * kQuarterOff + t * kPartials;
-    // quarters rq = 0 (interior h0) and 1 (exterior h0) pass on the
-    // whole-tile sums; 0 and 3 (exterior h1) store their own sums
-    double *hdst_own = Ht + (rq == 0 ? 1 : 3) * C;
-    const int pad0 = L & 1;             // zero channel after the m = 0 block
-    const int n_pos = C + pad0;         // padded channel positions
-    int slot = 0, base = 0;             // base: padded position of slot 0
-    int xb = 0, xbase = 0;              // the exchange's batches, its first position
-    // an exchange's lane: side io (0: interior, 1: exterior), entry xj; the
-    // weights of the four tiles' sums in its in-group sum
-    const bool x_on = lane < 2 * kXLen;
-    const int io = (lane / kXLen) & 1, xj = lane & (kXLen - 1);
-    double xw[kWavesPerBlock];
+    double *wr = wb + (lane >> 3) * kMomHalfOff + (lane & 7);
+    // reader: channel rc of the batch, side rio, half h (in scan order: the
+    // exterior sums are scanned from the last tile to the first)
+    const int rc = lane >> 4, rio = (lane >> 3) & 1, ro = lane & 7;
+    const int h = rio ? kMomHalves - 1 - ro : ro;
+    const double2 *rd =
+        reinterpret_cast<const double2 *>(wb + (2 * rc + rio) * kMomRow + h * kMomHalfOff);
+    double *hdst = Hg + (size_t)(h >> 1) * kp.HW + 4 * rc + 2 * rio;
+    double *gdst = Gs + rio * C + rc;
+    const bool odd_tile = (lane & 2) != 0;
+    // sums of the batch of n_ch channels from stream position ch0 on
+    auto flush = [&](int ch0, int n_ch) {
+        wave_lds_sync();
+        double2 v[kMomLanes / 2];
 #pragma unroll
-    for (int k = 0; k < kWavesPerBlock; ++k) xw[k] = (io == 0 ? k < w : k > w) ? 1.0 : 0.0;
-    const bool own_q = halves && tile_ok && t == 0 && (rq == 0 || rq == 3);
-    auto exchange = [&]() {
-        __syncthreads();
-        const int pos = xbase + xj;
-        double v[kWavesPerBlock];
+        for (int k = 0; k < kMomLanes / 2; ++k) v[k] = rd[k];
+        double own = 0.0;
+        {
+            double a[kMomLanes / 2];
 #pragma unroll
-        for (int k = 0; k < kWavesPerBlock; ++k) v[k] = xch[k][io][xj];
-        // interior: the tiles before this one; exterior: those after it (the
-        // 0/1 weights make the FMAs plain sums)
-        double sp = 0.0;
-#pragma unroll
-        for (int k = 0; k < kWavesPerBlock; ++k) sp = fma(xw[k], v[k], sp);
-        const int ch = pos < L ? pos : pos - pad0;
-        if (x_on && tile_ok && pos < xbase + xb * 2 * kSlots && pos < n_pos &&
-            !(pad0 && pos == L)) {
-            Ht[2 * io * C + ch] = sp;
-            if (io == 0 && w == kWavesPerBlock - 1) Gs[ch] = sp + v[kWavesPerBlock - 1];
-            if (io == 1 && w == 0) Gs[C + ch] = sp + v[0];
+            for (int k = 0; k < kMomLanes / 2; ++k) a[k] = v[k].x + v[k].y;
+            own = (a[0] + a[1]) + (a[2] + a[3]);
         }
-        __syncthreads();
-        xbase += xb * 2 * kSlots;
-        xb = 0;
-    };
-    auto flush = [&]() {
+        // the tile's sum, then the exclusive scan over the group's four tiles
+        const double t = own + dpp_quad<0xB1>(own);
+        const double tx = dpp_quad<0x4E>(t);           // the pair's other tile
+        const double pair = t + tx;
+        const double below = dpp_shr4_odd_banks(pair);
+        const double excl = below + (odd_tile ? tx : 0.0);
+        if (rc < n_ch) {
+            if ((lane & 1) == 0)
+                *reinterpret_cast<double2 *>(hdst + 4 * ch0) = double2{excl, own};
+            if (ro == 4) gdst[ch0] = below + pair;
+        }
         wave_lds_sync();
-        double acc = rd[0];
-#pragma unroll
-        for (int k = 1; k < kPartials; ++k) acc += rd[k];
-        acc += dpp_quad<0xB1>(acc);
-        const double whole = acc + dpp_row_shl4(acc);   // quarters 0, 1: + quarters 2, 3
-        if (t == 0 && rq < 2) xch[w][rq][xb * 2 * kSlots + rr] = whole;
-        const int pos = base + rr;      // padded position
-        // padded position -> channel: the m = 0 block is positions 0..L-1
-        const int ch = pos < L ? pos : pos - pad0;
-        if (own_q && rs < slot && pos < n_pos && !(pad0 && pos == L))
-            hdst_own[ch] = acc;
-        wave_lds_sync();
-        base += 2 * kSlots;
-        slot = 0;
-        if (++xb == kXBatches) exchange();
     };
-    // one slot from two channels (R, I each)
-    auto put2 = [&](double r0, double i0, double r1, double i1) {
-        swap_rows16(r0, i0);
-        swap_rows16(r1, i1);
-        double *row = wr + slot * 2 * kRowLen;
-        row[0] = r0 + i0;
-        row[kRowLen] = r1 + i1;
-        if (++slot == kSlots) flush();
+    // one channel's interior and exterior sums of this lane's particles
+    auto put = [&](int slot, double r, double i) {
+        wr[2 * slot * kMomRow] = r;
+        wr[(2 * slot + 1) * kMomRow] = i;
     };
-
     // gamma_lm of the stream-order table, read one entry ahead of its use
     // through a running pointer (the read after the last entry lands on the
     // table's zero entry after the triangle; its value is never used)
-    const double *ahead = reinterpret_cast<const double *>(tb.fq4 + 1);   // entry after the one held
-    double ng = ld_const(reinterpret_cast<const double *>(tb.fq4), 0);   // the next entry to use
+    const double *ahead = reinterpret_cast<const double *>(
+        tb.fq4 + (m_begin * (L + 1) - (m_begin * (m_begin - 1)) / 2));
+    double ng = ld_const(ahead, 0);   // the next entry to use
+    ahead += 4;
     auto next_gamma = [&]() {
         const double g = ng;
         ng = ld_const(ahead, 0);
         ahead += 4;
         return g;
     };
-    // m = 0: channels l = 1..L (Qh_0^0 = 1 only seeds the recurrence; l = 0
-    // is Gauss's law in the field kernel), two degrees per slot; the two Qh
-    // registers trade roles instead of being copied
-    {
-        (void)next_gamma();                     // l = 0
-        double Qa = 1.0, Qb = 0.0;              // Qh_{l-1}, Qh_{l-2}
-        double sl = inv_r * inv_r2;             // r^-(2l+1) at l = 1
+    // Qh_{l-1} -> Qh_l into the registers of Qh_{l-2}
+    auto step_q = [&](const double *q1, double *q2) {
+        const double g = next_gamma();
+#pragma unroll
+        for (int j = 0; j < kMomParts; ++j) q2[j] = z[j] * q1[j] - (g * r2[j]) * q2[j];
+    };
+    int ch = 0;   // stream position of the batch's first channel
+    int m = m_begin;
+    if (m == 0) {
+        // channels l = 1..L (Qh_0^0 = 1 only seeds the recurrence; l = 0 is
+        // Gauss's law in the field kernel), the charge in the seed
+        double qa[kMomParts], qb[kMomParts], sl[kMomParts];
+#pragma unroll
+        for (int j = 0; j < kMomParts; ++j) {
+            qa[j] = q[j];
+            qb[j] = 0.0;
+            sl[j] = smm[j] * inv_r2[j];     // r^-(2l+1) at l = 1
+        }
+        (void)next_gamma();                 // l = 0
+        int slot = 0;
+        auto emit = [&](const double *qv) {
+            double r = qv[0], i = qv[0] * sl[0];
+#pragma unroll
+            for (int j = 1; j < kMomParts; ++j) {
+                r += qv[j];
+                i = fma(qv[j], sl[j], i);
+            }
+#pragma unroll
+            for (int j = 0; j < kMomParts; ++j) sl[j] *= inv_r2[j];
+            put(slot, r, i);
+            if (++slot == kMomSlots) {
+                flush(ch, kMomSlots);
+                ch += kMomSlots;
+                slot = 0;
+            }
+        };
         int l = 1;
         for (; l < L; l += 2) {
-            Qb = z * Qa - next_gamma() * r2 * Qb;   // Qh_l
-            const double r0 = q * Qb, i0 = r0 * sl;
-            sl *= inv_r2;
-            Qa = z * Qb - next_gamma() * r2 * Qa;   // Qh_{l+1}
-            const double r1 = q * Qa, i1 = r1 * sl;
-            sl *= inv_r2;
-            put2(r0, i0, r1, i1);
+            step_q(qa, qb);
+            emit(qb);
+            step_q(qb, qa);
+            emit(qa);
         }
         if (l == L) {
-            Qb = z * Qa - next_gamma() * r2 * Qb;
-            const double r0 = q * Qb;
-            put2(r0, r0 * sl, 0.0, 0.0);
+            step_q(qa, qb);
+            emit(qb);
+        }
+        if (slot > 0) flush(ch, slot);   // the other slots hold older values
+        ch = L;
+        m = 1;
+    } else if (FULL) {
+        ch = (m - 1) * (2 * L + 2 - m) + L;   // sum of 2 (L - k + 1), k = 1..m-1, after m = 0
+        // powers m - 1 of x + i y and of r^-2, step by step (a member's sums
+        // do not depend on how the orders are sliced)
+        for (int k = 1; k < m; ++k) {
+#pragma unroll
+            for (int j = 0; j < kMomParts; ++j) {
+                const double c = cq[j], s = sq[j];
+                cq[j] = x[j] * c - y[j] * s;
+                sq[j] = x[j] * s + y[j] * c;
+                smm[j] *= inv_r2[j];
+            }
         }
     }
     if (FULL) {
-        double Cm = 1.0, Sm = 0.0;
-        double s_mm = inv_r;  // r^-(2m+1)
-        for (int m = 1; m <= L; ++m) {
-            const double nc = x * Cm - y * Sm;
-            const double ns = x * Sm + y * Cm;
-            Cm = nc;
-            Sm = ns;
-            s_mm *= inv_r2;
-            const double qc = q * Cm, qs = q * Sm;
-            double sl = s_mm;
-            // cos and sin of one (l, m) fill one slot
-            auto emit = [&](double Qv) {
-                const double rc = Qv * qc, rs = Qv * qs;
-                put2(rc, rc * sl, rs, rs * sl);
-                sl *= inv_r2;
+        bool second = false;   // the batch's second pair of channels is next
+        for (; m < m_end; ++m) {
+            double qa[kMomParts], qb[kMomParts], sl[kMomParts];
+#pragma unroll
+            for (int j = 0; j < kMomParts; ++j) {
+                const double c = cq[j], s = sq[j];
+                cq[j] = x[j] * c - y[j] * s;
+                sq[j] = x[j] * s + y[j] * c;
+                smm[j] *= inv_r2[j];
+                sl[j] = smm[j];
+                qa[j] = 1.0;
+                qb[j] = 0.0;
+            }
+            // cos and sin of one (l, m) are two channels
+            auto emit = [&](const double *qv) {
+                double s0 = qv[0] * sl[0];
+                double rcs = qv[0] * cq[0], rsn = qv[0] * sq[0];
+                double ics = s0 * cq[0], isn = s0 * sq[0];
+#pragma unroll
+                for (int j = 1; j < kMomParts; ++j) {
+                    s0 = qv[j] * sl[j];
+                    rcs = fma(qv[j], cq[j], rcs);
+                    rsn = fma(qv[j], sq[j], rsn);
+                    ics = fma(s0, cq[j], ics);
+                    isn = fma(s0, sq[j], isn);
+                }
+#pragma unroll
+                for (int j = 0; j < kMomParts; ++j) sl[j] *= inv_r2[j];
+                const int slot = second ? 2 : 0;
+                put(slot, rcs, ics);
+                put(slot + 1, rsn, isn);
+                if (second) {
+                    flush(ch, kMomSlots);
+                    ch += kMomSlots;
+                }
+                second = !second;
             };
             (void)next_gamma();                     // l = m: Qh_m^m = 1
-            double Qa = 1.0, Qb = 0.0;
-            emit(Qa);
+            emit(qa);
             int l = m + 1;
             for (; l < L; l += 2) {
-                Qb = z * Qa - next_gamma() * r2 * Qb;
-                emit(Qb);
-                Qa = z * Qb - next_gamma() * r2 * Qa;
-                emit(Qa);
+                step_q(qa, qb);
+                emit(qb);
+                step_q(qb, qa);
+                emit(qa);
             }
             if (l == L) {
-                Qb = z * Qa - next_gamma() * r2 * Qb;
-                emit(Qb);
+                step_q(qa, qb);
+                emit(qb);
             }
         }
+        if (second) flush(ch, 2);
     }
-    if (slot > 0) flush();   // last, partial batch: slots >= slot hold stale values
-    if (xb > 0) exchange();
 }
 
 // ---------------------------------------------------------------------------
@@ -1764,10 +1775,12 @@ __global__ __launch_bounds__(kBlock, FP32 && !NEAR64 ? 6 : 4) void k_field_push(
                     // the exterior sums of those after it, and the halves' own
                     // sums
                     const double *Ht = Hg + w * kp.HW;
-                    yin[u] = Ht[c];
-                    yout[u] = Ht[2 * C + c];
-                    hin[u] = split ? Ht[C + c] : 0.0;
-                    hout[u] = split ? Ht[3 * C + c] : 0.0;
+                    const double2 hi = reinterpret_cast<const double2 *>(Ht)[2 * c];
+                    const double2 ho = reinterpret_cast<const double2 *>(Ht)[2 * c + 1];
+                    yin[u] = hi.x;
+                    yout[u] = ho.x;
+                    hin[u] = split ? hi.y : 0.0;
+                    hout[u] = split ? ho.y : 0.0;
                     ci[u] = CRg[c];
                     co[u] = CRg[C + c];
                     gsc[u] = tb.chg[c] * inv_nt;
@@ -2496,6 +2509,52 @@ std::vector<double> build_tables(const sim_params &p, const Layout &lo)
     return t;
 }
 
+// Cuts m = 0..l_max into slices of near-equal work for the moments kernel and
+// returns the blocks per group: a slice per wave of one block, and more blocks
+// per group while the groups alone leave the chip's 256 CUs idle (each slice
+// repeats the particles' loads and powers, so no more than that).
+unsigned slice_orders(const Layout &lo, int n_groups, uint8_t *m_slice)
+{
+    const int top = lo.full ? lo.L : 0;   // the last order
+    int ny = 1;
+    while (lo.full && ny * kWavesPerBlock < kMaxMSlices && 2 * ny * kWavesPerBlock <= top &&
+           n_groups * ny < 512)
+        ny *= 2;
+    const int ns = ny * kWavesPerBlock;
+    // (l, m) pairs of an order, and about one pair's worth for its start (the
+    // walk to a slice's first order, half a pair per step, is left out)
+    auto cost = [&](int m) { return m == 0 ? 0.6 * lo.L + 1.0 : lo.L - m + 2.0; };
+    double lo_c = 0.0, hi_c = 0.0;
+    for (int m = 0; m <= top; ++m) {
+        lo_c = std::max(lo_c, cost(m));
+        hi_c += cost(m);
+    }
+    // the smallest largest slice, by bisection
+    auto cut = [&](double most, uint8_t *out) {
+        int s = 0;
+        double sum = 0.0;
+        out[0] = 0;
+        for (int m = 0; m <= top; ++m) {
+            if (sum > 0.0 && sum + cost(m) > most) {
+                if (++s >= ns) return false;
+                out[s] = (uint8_t)m;
+                sum = 0.0;
+            }
+            sum += cost(m);
+        }
+        while (s < ns) out[++s] = (uint8_t)(top + 1);
+        return true;
+    };
+    uint8_t tmp[kMaxMSlices + 1];
+    for (int it = 0; it < 12; ++it) {
+        const double mid = 0.5 * (lo_c + hi_c);
+        if (cut(mid, tmp)) hi_c = mid;
+        else lo_c = mid;
+    }
+    cut(hi_c, m_slice);
+    return (unsigned)ny;
+}
+
 int launch_step(sim *h, hipStream_t s, bool field_only, hipEvent_t *ev)
 {
     const Layout &lo = h->lo;
@@ -2536,8 +2595,9 @@ int launch_step(sim *h, hipStream_t s, bool field_only, hipEvent_t *ev)
     mark(KN_SORT_RANK);
     k_sort_rank_move<<<gN, kBlock, 0, s>>>(mp, h->orec, h->off, h->A, h->B, kp);
     mark(KN_MOMENTS);
-    if (lo.full) k_moments<true><<<gT, kBlock, 0, s>>>(mp, h->B, h->tb, kp, h->H, h->GS);
-    else k_moments<false><<<gT, kBlock, 0, s>>>(mp, h->B, h->tb, kp, h->H, h->GS);
+    const unsigned gS = slice_orders(lo, (int)gT, kp.m_slice);
+    if (lo.full) k_moments<true><<<dim3(gT, gS), kBlock, 0, s>>>(mp, h->B, h->tb, kp, h->H, h->GS);
+    else k_moments<false><<<dim3(gT, gS), kBlock, 0, s>>>(mp, h->B, h->tb, kp, h->H, h->GS);
     mark(KN_CHUNK_SUMS);
     k_chunk_sums<<<dim3(ex.n_chunks, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkS, kp);
     mark(KN_CHUNK_SCAN);

@@ -1,0 +1,48 @@
+"""Kernel variants at the sizes where their splits can go wrong, against the
+CPU oracle.  FP64 bar: 1e-12 of the larger of the RMS field and the particle's
+own field.  (The own field counts because a pair at nearly equal place pushes
+with ~l_max^2 / sqrt(n) of the RMS field, whose rounding no split of the sum
+takes away: 300 particles at l_max 63 reach 7 times the RMS.)"""
+from __future__ import annotations
+
+import sys
+
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2111_13072_amd import sim as S
+from paper_2111_13072_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _params(n, L, mode=S.SIM_M_FULL, r_out=5.0, **kw):
+    nt = W.ntilde_for(n, r_out)
+    return (S.SimParams(ntilde=nt, l_max=L, m_mode=mode, r_out=r_out, **kw),
+            O.Params(ntilde=nt, l_max=L, m_mode=mode, r_out=r_out))
+
+
+def _err(E, Eo):
+    own = np.sqrt(np.sum(Eo * Eo, axis=1))
+    scale = np.maximum(own, np.sqrt(np.mean(own * own)))
+    return float(np.max(np.max(np.abs(E - Eo), axis=1) / scale))
+
+
+# One, two and four blocks of orders per group (l_max 8, 16, 32 on a few
+# groups), odd and even l_max (the channel batches end on one or two orders),
+# fewer orders than slices, and particle counts around a half, a tile and a
+# group.
+@pytest.mark.parametrize("n,L,mode", [
+    (1, 16, S.SIM_M_FULL), (31, 2, S.SIM_M_FULL), (33, 7, S.SIM_M_FULL), (255, 8, S.SIM_M_FULL),
+    (256, 9, S.SIM_M_FULL), (257, 15, S.SIM_M_FULL), (513, 33, S.SIM_M_FULL),
+    (300, 63, S.SIM_M_FULL), (257, 1, S.SIM_M_FULL), (255, 1, S.SIM_M_AXISYM),
+    (300, 31, S.SIM_M_AXISYM), (66, 64, S.SIM_M_AXISYM)])
+def test_order_slices_match_oracle(n, L, mode):
+    print(f"[gpu] order slices n={n} L={L} mode={mode}", file=sys.stderr, flush=True)
+    sp, op = _params(n, L, mode, q_surface0=-3.0)
+    st = W.uniform_shell(n, 600 + n, 5.0, 0.08)
+    with S.Sim(sp, st.pos, st.vel, np.array([0.2])) as sim:
+        E = sim.eval_field()
+    Eo, _ = O.field(op, st.pos, q_surface=-3.0, u_asy=0.2)
+    assert _err(E, Eo) <= 1e-12
