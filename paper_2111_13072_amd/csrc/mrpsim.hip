@@ -445,7 +445,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_single(uint32_t *in, uint32_t *
 // Per member: alive count (its buckets' share of the global offsets) and the
 // surface charge Q_S = q_surface0 + the charge absorbed so far, which enters
 // the field as an interior l = 0 charge (Q_S / (4 pi r), Sec. 3).  Done by
-// the first block of the rank kernel (after the offsets, before the moments).
+// the first block of the kernel that ranks (after the offsets, before the carries).
 __device__ inline void member_live(const Map &mp, const uint32_t *off, const KParams &kp)
 {
     for (int s = threadIdx.x; s < kp.n_members; s += blockDim.x) {
@@ -554,6 +554,154 @@ __global__ __launch_bounds__(kBlock) void k_sort_rank_move(Map mp, const OrdRec 
     B.uid[d] = u;
 }
 
+// The same ranking for the block of a group of slots (small launches, inside
+// the moments kernel): the window of whole buckets that holds the group's
+// positions, staged in LDS with the buckets' offsets where both fit.
+constexpr int kRankOffsets = 512;   // buckets
+
+struct RankLds {
+    uint64_t key[kRankWindow];
+    uint32_t uid[kRankWindow], idx[kRankWindow];
+    uint32_t off[kRankOffsets + 1];
+    uint32_t src[kGroupSlots];      // source slot of each of the group's positions
+};
+
+// Source slots of the positions first .. first + count - 1 of the bucket order
+// [p_first, ...) into r.src.  All threads of the block take part.
+__device__ inline void rank_group(const Seg &sg, const OrdRec *orec, const uint32_t *off,
+                                  uint32_t p_first, int count, RankLds &r)
+{
+    const uint32_t p_last = p_first + (uint32_t)count - 1;
+    auto bucket = [&](uint64_t key) {
+        return bucket_of(__longlong_as_double((long long)key), sg.inv_vol, sg.b0, sg.nb);
+    };
+    const uint32_t ba = uniform_u32(bucket(orec[p_first].key));
+    const uint32_t bb = uniform_u32(bucket(orec[p_last].key));
+    const uint32_t w0 = uniform_u32(off[ba]), w1 = uniform_u32(off[bb + 1]);
+    const uint32_t nw = w1 - w0, nbk = bb - ba + 1;
+    if (nw <= (uint32_t)kRankWindow) {
+        const bool off_staged = nbk <= (uint32_t)kRankOffsets;
+        if (off_staged)
+            for (uint32_t j = threadIdx.x; j <= nbk; j += kBlock) r.off[j] = off[ba + j] - w0;
+        for (uint32_t j = threadIdx.x; j < nw; j += kBlock) {
+            const OrdRec o = orec[w0 + j];
+            r.key[j] = o.key;
+            r.uid[j] = o.uid;
+            r.idx[j] = o.idx;
+        }
+        __syncthreads();
+        for (uint32_t j = threadIdx.x; j < nw; j += kBlock) {
+            const uint64_t k = r.key[j];
+            const uint32_t u = r.uid[j], bk = bucket(k);
+            const uint32_t lo = off_staged ? r.off[bk - ba] : off[bk] - w0;
+            const uint32_t hi = off_staged ? r.off[bk - ba + 1] : off[bk + 1] - w0;
+            uint32_t pos = lo + w0 - p_first;   // wraps below zero before the group's first
+            for (uint32_t i = lo; i < hi; ++i) {
+                const uint64_t ki = r.key[i];
+                pos += (ki < k) || (ki == k && r.uid[i] < u);
+            }
+            if (pos < (uint32_t)count) r.src[pos] = r.idx[j];
+        }
+        __syncthreads();
+        return;
+    }
+    // A window too large for LDS (a radial concentration far over the mean
+    // density): the keys (r^2, id) of the group's first and last position by
+    // bisection over their bits, one counting pass over the window per bit,
+    // then the records between them, at most a group, ranked in LDS.  96
+    // passes by the whole block are less than one pass per particle from 256
+    // particles on.
+    __shared__ uint32_t cnt[2], n_got;
+    uint64_t key0 = 0, key1 = 0;
+    uint32_t uid0 = 0, uid1 = 0;
+    const uint32_t r0 = p_first - w0, r1 = p_last - w0;
+    for (int bit = 95; bit >= 0; --bit) {
+        // the largest (key, id) with at most r0 (r1) records before it
+        const uint64_t kb = bit >= 32 ? 1ull << (bit - 32) : 0ull;
+        const uint32_t ub = bit >= 32 ? 0u : 1u << bit;
+        const uint64_t t0 = key0 | kb, t1 = key1 | kb;
+        const uint32_t v0 = uid0 | ub, v1 = uid1 | ub;
+        if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
+        __syncthreads();
+        uint32_t c0 = 0, c1 = 0;
+        for (uint32_t j = threadIdx.x; j < nw; j += kBlock) {
+            const OrdRec o = orec[w0 + j];
+            c0 += (o.key < t0) || (o.key == t0 && o.uid < v0);
+            c1 += (o.key < t1) || (o.key == t1 && o.uid < v1);
+        }
+        atomicAdd(&cnt[0], c0);
+        atomicAdd(&cnt[1], c1);
+        __syncthreads();
+        if (cnt[0] <= r0) {
+            key0 = t0;
+            uid0 = v0;
+        }
+        if (cnt[1] <= r1) {
+            key1 = t1;
+            uid1 = v1;
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) n_got = 0;
+    __syncthreads();
+    for (uint32_t j = threadIdx.x; j < nw; j += kBlock) {
+        const OrdRec o = orec[w0 + j];
+        const bool from = o.key > key0 || (o.key == key0 && o.uid >= uid0);
+        const bool upto = o.key < key1 || (o.key == key1 && o.uid <= uid1);
+        if (from && upto) {
+            const uint32_t at = atomicAdd(&n_got, 1u);
+            if (at < (uint32_t)kGroupSlots) {   // ids are distinct: exactly count records
+                r.key[at] = o.key;
+                r.uid[at] = o.uid;
+                r.idx[at] = o.idx;
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < (uint32_t)count) {
+        const uint64_t k = r.key[threadIdx.x];
+        const uint32_t u = r.uid[threadIdx.x];
+        uint32_t pos = 0;
+        for (int i = 0; i < count; ++i) pos += (r.key[i] < k) || (r.key[i] == k && r.uid[i] < u);
+        r.src[pos] = r.idx[threadIdx.x];
+    }
+    __syncthreads();
+}
+
+// Puts a group's particles in radial order: thread t gets the record of the
+// group's position t (t < the returned count) and writes it to the sorted
+// state.
+__device__ inline int place_group(const Seg &sg, const OrdRec *orec, const uint32_t *off,
+                                  const PRec *A, const State &B, uint32_t group, bool write,
+                                  RankLds &r, PRec &a)
+{
+    const uint32_t first = (group - sg.g0) * kGroupSlots;
+    const uint32_t o0 = uniform_u32(off[sg.b0]);
+    const uint32_t n = uniform_u32(off[sg.b0 + sg.nb]) - o0;   // the member's live particles
+    if (n <= first) return 0;
+    const int count = (int)min(n - first, (uint32_t)kGroupSlots);
+    rank_group(sg, orec, off, o0 + first, count, r);
+    if ((int)threadIdx.x < count) {
+        a = A[r.src[threadIdx.x]];
+        if (write) {
+            const size_t d = (size_t)group * kGroupSlots + threadIdx.x;
+            B.x[d] = a.x;
+            B.y[d] = a.y;
+            B.z[d] = a.z;
+            B.vx[d] = a.vx;
+            B.vy[d] = a.vy;
+            B.vz[d] = a.vz;
+            B.uid[d] = a.uid;
+        }
+    }
+    return count;
+}
+
+// Up to this many groups the moments kernel ranks its own group: 1e6 particles
+// at l_max 1 (3,907 groups) 219 -> 217 us per step, at l_max 32 1.113 -> 1.105
+// ms; 2e6 at l_max 16 0.837 -> 0.850 ms.
+constexpr int kRankFusedMaxGroups = 4096;
+
 // ---------------------------------------------------------------------------
 // Moments: per-tile sums of q R_lm and q I_lm
 // ---------------------------------------------------------------------------
@@ -630,33 +778,72 @@ __device__ inline double dpp_shr4_odd_banks(double v)
 // scan over its tiles inside a wave, without barriers, and lets a small launch
 // spread one group over several blocks (21,347 particles at l_max 32: the
 // evaluation 344 -> 222 us).  1.6e7 particles, l_max 16: 1.94 -> 1.29 ms.
-template <bool FULL>
-__global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, State B, Tables tb, KParams kp,
-                                                       double *H, double *GS)
+// RANK: the block first puts its group in radial order (place_group) and goes
+// on with the particles it has in LDS.  This saves a launch (evaluation of
+// 120,011 particles at l_max 16: 171 -> 156 us), but the ranking's chain of
+// dependent loads then runs at four blocks per CU instead of eight (2e6
+// particles: 272 us against 194 + 71), so large launches rank in a kernel of
+// their own (kRankFusedMaxGroups).
+template <bool FULL, bool RANK>
+__global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, const OrdRec *orec,
+                                                       const uint32_t *off, const PRec *A, State B,
+                                                       Tables tb, KParams kp, double *H, double *GS)
 {
-    __shared__ double buf[kWavesPerBlock][2 * kMomSlots * kMomRow];
+    struct Parts {
+        double x[kGroupSlots], y[kGroupSlots], z[kGroupSlots];
+        float q[kGroupSlots];
+    };
+    __shared__ union {
+        typename std::conditional<RANK, RankLds, double>::type rank;
+        double buf[kWavesPerBlock][2 * kMomSlots * kMomRow];
+    } lds;
+    __shared__ __attribute__((aligned(16))) typename std::conditional<RANK, Parts, double>::type part;
     const int lane = threadIdx.x & 63;
     const int w = (int)uniform_u32(threadIdx.x >> 6);
-    const uint32_t group = blockIdx.x;
+    // (neighbouring groups share gathered lines)
+    const uint32_t group = RANK ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+    if constexpr (RANK) {
+        if (blockIdx.x == 0 && blockIdx.y == 0) member_live(mp, off, kp);
+    }
     const uint32_t mb = uniform_u32(mp.tile_member[group * kTilesPerGroup]);
     if (mb == kNone || !member_runs(mp.seg[mb], mp.ctl[mb], kp)) return;
-    // the group's particles: slots first .. first + count of the member's n_live
-    const uint32_t first = (group - mp.seg[mb].g0) * kGroupSlots;
-    const uint32_t n = mp.ctl[mb].n_live;
-    const int count = n > first ? (int)min(n - first, (uint32_t)kGroupSlots) : 0;
-
     double x[kMomParts], y[kMomParts], z[kMomParts], q[kMomParts];
-    const size_t p = (size_t)group * kGroupSlots + kMomParts * lane;
     uint64_t ions[kMomParts];
+    int count;   // the group's particles
+    if constexpr (RANK) {
+        PRec a;
+        count = place_group(mp.seg[mb], orec, off, A, B, group, blockIdx.y == 0, lds.rank, a);
+        const int t = (int)threadIdx.x;
+        const bool valid = t < count;
+        part.x[t] = valid ? a.x : 0.0;
+        part.y[t] = valid ? a.y : 0.0;
+        part.z[t] = valid ? a.z : 2.0;
+        part.q[t] = valid ? ((a.uid & kIonBit) ? 1.0f : (float)kQ) : 0.0f;
+        __syncthreads();   // and the ranking's LDS is free for the sums from here on
 #pragma unroll
-    for (int j = 0; j < kMomParts; ++j) {
-        const bool valid = kMomParts * lane + j < count;
-        x[j] = valid ? B.x[p + j] : 0.0;
-        y[j] = valid ? B.y[p + j] : 0.0;
-        z[j] = valid ? B.z[p + j] : 2.0;
-        const bool ion = valid && (B.uid[p + j] & kIonBit) != 0;
-        q[j] = valid ? (ion ? 1.0 : kQ) : 0.0;
-        ions[j] = __ballot(ion);
+        for (int j = 0; j < kMomParts; ++j) {
+            const int i = kMomParts * lane + j;
+            x[j] = part.x[i];
+            y[j] = part.y[i];
+            z[j] = part.z[i];
+            q[j] = (double)part.q[i];
+            ions[j] = __ballot(q[j] > 0.0);
+        }
+    } else {
+        const uint32_t first = (group - mp.seg[mb].g0) * kGroupSlots;
+        const uint32_t n = mp.ctl[mb].n_live;
+        count = n > first ? (int)min(n - first, (uint32_t)kGroupSlots) : 0;
+        const size_t p = (size_t)group * kGroupSlots + kMomParts * lane;
+#pragma unroll
+        for (int j = 0; j < kMomParts; ++j) {
+            const bool valid = kMomParts * lane + j < count;
+            x[j] = valid ? B.x[p + j] : 0.0;
+            y[j] = valid ? B.y[p + j] : 0.0;
+            z[j] = valid ? B.z[p + j] : 2.0;
+            const bool ion = valid && (B.uid[p + j] & kIonBit) != 0;
+            q[j] = valid ? (ion ? 1.0 : kQ) : 0.0;
+            ions[j] = __ballot(ion);
+        }
     }
     const int L = kp.L, C = kp.C;
     double *Hg = H + (size_t)group * kTilesPerGroup * kp.HW;
@@ -685,14 +872,14 @@ __global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, State B, Tables t
     double cq[kMomParts], sq[kMomParts], smm[kMomParts];   // q C_m, q S_m, r^-(2m+1)
 #pragma unroll
     for (int j = 0; j < kMomParts; ++j) {
-        r2[j] = x[j] * x[j] + y[j] * y[j] + z[j] * z[j];
+        r2[j] = fma(z[j], z[j], fma(y[j], y[j], x[j] * x[j]));
         inv_r2[j] = 1.0 / r2[j];
         smm[j] = 1.0 / sqrt(r2[j]);
         cq[j] = q[j];
         sq[j] = 0.0;
     }
 
-    double *wb = buf[w];
+    double *wb = lds.buf[w];
     double *wr = wb + (lane >> 3) * kMomHalfOff + (lane & 7);
     // reader: channel rc of the batch, side rio, half h (in scan order: the
     // exterior sums are scanned from the last tile to the first)
@@ -751,7 +938,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, State B, Tables t
     auto step_q = [&](const double *q1, double *q2) {
         const double g = next_gamma();
 #pragma unroll
-        for (int j = 0; j < kMomParts; ++j) q2[j] = z[j] * q1[j] - (g * r2[j]) * q2[j];
+        for (int j = 0; j < kMomParts; ++j) q2[j] = fma(z[j], q1[j], -(g * r2[j]) * q2[j]);
     };
     int ch = 0;   // stream position of the batch's first channel
     int m = m_begin;
@@ -805,8 +992,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, State B, Tables t
 #pragma unroll
             for (int j = 0; j < kMomParts; ++j) {
                 const double c = cq[j], s = sq[j];
-                cq[j] = x[j] * c - y[j] * s;
-                sq[j] = x[j] * s + y[j] * c;
+                cq[j] = fma(x[j], c, -(y[j] * s));
+                sq[j] = fma(x[j], s, y[j] * c);
                 smm[j] *= inv_r2[j];
             }
         }
@@ -818,8 +1005,8 @@ __global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, State B, Tables t
 #pragma unroll
             for (int j = 0; j < kMomParts; ++j) {
                 const double c = cq[j], s = sq[j];
-                cq[j] = x[j] * c - y[j] * s;
-                sq[j] = x[j] * s + y[j] * c;
+                cq[j] = fma(x[j], c, -(y[j] * s));
+                sq[j] = fma(x[j], s, y[j] * c);
                 smm[j] *= inv_r2[j];
                 sl[j] = smm[j];
                 qa[j] = 1.0;
@@ -2593,11 +2780,21 @@ int launch_step(sim *h, hipStream_t s, bool field_only, hipEvent_t *ev)
     mark(KN_SORT_SCATTER);
     k_sort_scatter<<<gN, kBlock, 0, s>>>(mp, h->krec, h->off, h->orec, kp);
     mark(KN_SORT_RANK);
-    k_sort_rank_move<<<gN, kBlock, 0, s>>>(mp, h->orec, h->off, h->A, h->B, kp);
+    const bool fused = (int)gT <= kRankFusedMaxGroups;
+    if (!fused) k_sort_rank_move<<<gN, kBlock, 0, s>>>(mp, h->orec, h->off, h->A, h->B, kp);
     mark(KN_MOMENTS);
     const unsigned gS = slice_orders(lo, (int)gT, kp.m_slice);
-    if (lo.full) k_moments<true><<<dim3(gT, gS), kBlock, 0, s>>>(mp, h->B, h->tb, kp, h->H, h->GS);
-    else k_moments<false><<<dim3(gT, gS), kBlock, 0, s>>>(mp, h->B, h->tb, kp, h->H, h->GS);
+#define MRP_MOMENTS(FULLV, RANKV)                                                       \
+    k_moments<FULLV, RANKV><<<dim3(gT, gS), kBlock, 0, s>>>(mp, h->orec, h->off, h->A, h->B, \
+                                                            h->tb, kp, h->H, h->GS)
+    if (lo.full) {
+        if (fused) MRP_MOMENTS(true, true);
+        else MRP_MOMENTS(true, false);
+    } else {
+        if (fused) MRP_MOMENTS(false, true);
+        else MRP_MOMENTS(false, false);
+    }
+#undef MRP_MOMENTS
     mark(KN_CHUNK_SUMS);
     k_chunk_sums<<<dim3(ex.n_chunks, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkS, kp);
     mark(KN_CHUNK_SCAN);

@@ -46,3 +46,28 @@ def test_order_slices_match_oracle(n, L, mode):
         E = sim.eval_field()
     Eo, _ = O.field(op, st.pos, q_surface=-3.0, u_asy=0.2)
     assert _err(E, Eo) <= 1e-12
+
+
+# The group's ranking inside the moments kernel: windows of one record, of one
+# bucket per group, past the LDS window (every particle in two buckets, keys
+# that differ in their last digits and by the id alone) and at its edge.
+@pytest.mark.parametrize("n,bucket,spread", [(1, 8, 1.0), (257, 1, 1.0), (1024, 256, 1.0),
+                                             (1030, 8, 1e-9), (3000, 8, 1e-9),
+                                             (700, 256, 0.0)])
+def test_group_ranking_matches_oracle(n, bucket, spread):
+    print(f"[gpu] group ranking n={n} bucket={bucket} spread={spread}", file=sys.stderr, flush=True)
+    sp, op = _params(n, 4, sort_bucket=bucket)
+    st = W.uniform_shell(n, 700 + n, 5.0, 0.08)
+    r = np.linalg.norm(st.pos, axis=1)
+    pos = st.pos * ((2.0 + spread * (r - 2.0)) / r)[:, None]
+    if spread == 0.0:   # the same radius to the last bit: signed permutations of one point
+        p = np.array([1.1, 0.7, 1.5])
+        perms = [p[list(o)] * np.array(s) for o in ((0, 1, 2), (1, 0, 2))
+                 for s in ((1, 1, 1), (-1, 1, 1), (1, -1, 1), (1, 1, -1))]
+        pos = np.array([perms[i % len(perms)] for i in range(n)])
+        pos[: n // 2] *= 1.25
+    ids = np.random.default_rng(n).permutation(n).astype(np.uint32) * 3
+    with S.Sim(sp, pos, st.vel, np.array([0.0]), ids=ids) as sim:
+        E = sim.eval_field()
+    Eo, _ = O.field(op, pos, ids=ids)
+    assert _err(E, Eo) <= 1e-12
