@@ -141,8 +141,6 @@ struct Tables {
     const double *wl;       // 1 / (2l+1)
     const double *drive_w;  // c_l b^P_l sqrt(4 pi / (2l+1)) for odd l, else 0
     const double *self_w;   // f_l / (4 pi)
-    const double *nfA;      // (2l+1)/(l+1)
-    const double *nfB;      // l/(l+1)
     const double4 *nf4;     // {(2l+1)/(l+1), l/(l+1), 2l+1, l}, one wide load per l
     const int *chl;         // degree l of each channel in stream order
     // per channel: the factor that turns a sum of rescaled harmonics (Qh) into
@@ -162,7 +160,6 @@ struct Tables {
     const double4 *fq4;
     const double *chn;
     // FP32 copies of the field kernel's tables for the FP32-compensated mode
-    const float4 *nf4_32;
     const float4 *lg4_32;
     const float4 *fq4_32;
     // FP32 near field's Legendre recurrence on D_l = P_l - P_{l-1}, per l:
@@ -1408,7 +1405,7 @@ struct CfView {
 // exact to O(ulp^2)), and the per-m quantities C_m, S_m, r^-(2m+1) and the
 // directions are formed in FP64 and rounded once; what remains are the
 // independent roundings of the FP32 arithmetic.
-template <bool FULL, typename R, typename R4, typename Stage>
+template <typename R, typename R4, typename Stage>
 __device__ inline void far_field(Stage &&stage, int L, const R4 *fq, double xd, double yd,
                                  double zd, R &gx, R &gy, R &gz)
 {
@@ -1458,7 +1455,7 @@ __device__ inline void far_field(Stage &&stage, int L, const R4 *fq, double xd, 
             sl *= inv_r2;
         }
     }
-    if (FULL) {
+    {
         // C_m, S_m and C_{m-1}, S_{m-1} are common to all l of one m: the l
         // loop sums the cos and sin parts separately, combined once per m
         double Cmd = 1, Smd = 0, s_mmd = inv_rd;
@@ -1535,103 +1532,105 @@ __device__ inline void far_field(Stage &&stage, int L, const R4 *fq, double xd, 
 
 // Near field: the direct part of G~_L between the particles of one block of
 // W = 32 (a half tile) or 64 (the tile) radially consecutive particles (the
-// pairs across blocks go through the coefficients), pair by pair.  For the pair (k, j) with
-// rho = r_< / r_>, u = angular argument:
+// pairs across blocks go through the coefficients), pair by pair.  For the
+// pair (k, j) with rho = r_< / r_>, u = xh_k . xh_j and v = xh_other - u xh:
 //   outer one: grad D = (1/r_>^2)       sum_l rho^l [-(l+1) P_l xh + P'_l v]
 //   inner one: grad D = (1/(r_< r_>))   sum_l rho^l [ l P_l xh     + P'_l v]
-// where v = xh_other - u xh (full) or e_z - cos(th) xh (axisymmetric).  The
-// three sums are symmetric in (k, j), so each pair is evaluated once: at step
-// s lane k takes partner k + s (mod W, inside its block) and hands the
+// The three sums are symmetric in (k, j), so each pair is evaluated once: at
+// step s lane k takes partner k + s (mod W, inside its block) and hands the
 // partner's gradient to it through a lane rotation.  Each term carries the
 // charge of its source (the other particle of the pair).  Pair terms in R,
 // accumulated in FP64.  The rows hold each block twice (entries h + i and
 // h + i + W for the i-th particle of the block starting at entry h = 2 W b),
 // so the partner of every shift is a plain offset.
-template <bool FULL, typename R, typename NF>
-__device__ inline void near_field(int lane, int W, int jn, int L, const NF *nf, const R *sxh,
-                                  const R *syh, const R *szh, const R *sr, const R *sir,
-                                  const R *sq, R xh, R yh, R zh, R r, R inv_r, R qk, double &ax,
-                                  double &ay, double &az)
+
+// The value that a DPP control brings to this lane, zero where it brings none
+// (no source lane, or a row of 16 lanes outside kRows).
+template <int kCtrl, int kRows = 0xF>
+__device__ inline double dpp_or_zero(double v)
 {
-    const R inv_r2 = inv_r * inv_r;
-    const int hl = lane & (W - 1), hb = 2 * (lane & W);
-    for (int sft = 1; sft <= W / 2; ++sft) {
-        const int jl = (lane & W) | ((hl + sft) & (W - 1));   // partner lane
-        const int j = hb + hl + sft;
-        const bool active = lane < jn && jl < jn && (sft < W / 2 || hl < W / 2);
-        const R xj = sxh[j], yj = syh[j], zj = szh[j];
-        const R rj = sr[j], irj = sir[j];
-        const R qj = sq[j];
-        // a block's lanes are in radial order (key (r^2, id)): the partner
-        // is the inner one when it wraps below this lane
-        const bool k_outer = hl + sft >= W;
-        const R rho = k_outer ? rj * inv_r : r * irj;
-        const R sc_out = k_outer ? inv_r2 : irj * irj;   // 1 / r_>^2
-        const R sc_in = inv_r * irj;                     // 1 / (r_< r_>)
-        const R u = FULL ? xh * xj + yh * yj + zh * zj : zh;
-        R S1 = 0, Sl = 0, SBk = 0, SBj = 0;
-        R P0 = 1, P1 = u, dP0 = 0, dP1 = 1;      // P_l(u) (own cos th if axisymmetric)
-        R Q0 = 1, Q1 = zj, dQ0 = 0, dQ1 = 1;     // partner P_l(cos th_j), axisymmetric only
-        R rl = rho;                              // l = 0 is Gauss's law in the caller
-#pragma unroll 2
-        for (int l = 1; l <= L; ++l) {
-            const NF cl = nf[l];   // {(2l+1)/(l+1), l/(l+1), 2l+1, l}
-            const R A = cl.x, Bc = cl.y, tl1 = cl.z, dl = cl.w;
-            if (FULL) {
-                const R t = rl * P1;
-                S1 += t;
-                Sl += dl * t;
-                SBk += rl * dP1;
-            } else {
-                const R t = rl * P1 * Q1;
-                S1 += t;
-                Sl += dl * t;
-                SBk += rl * dP1 * Q1;
-                SBj += rl * P1 * dQ1;
-                const R Q2 = A * zj * Q1 - Bc * Q0;
-                const R dQ2 = dQ0 + tl1 * Q1;
-                Q0 = Q1;
-                Q1 = Q2;
-                dQ0 = dQ1;
-                dQ1 = dQ2;
-            }
-            const R P2 = A * u * P1 - Bc * P0;
-            const R dP2 = dP0 + tl1 * P1;
-            P0 = P1;
-            P1 = P2;
-            dP0 = dP1;
-            dP1 = dP2;
-            rl *= rho;
-        }
-        if (FULL) SBj = SBk;
-        const R S_out = -(Sl + S1), S_in = Sl;
-        const R SAk = k_outer ? S_out : S_in, sck = qj * (k_outer ? sc_out : sc_in);
-        const R SAj = k_outer ? S_in : S_out, scj = qk * (k_outer ? sc_in : sc_out);
-        R vkx, vky, vkz, vjx, vjy, vjz;
-        if (FULL) {
-            vkx = xj - u * xh; vky = yj - u * yh; vkz = zj - u * zh;
-            vjx = xh - u * xj; vjy = yh - u * yj; vjz = zh - u * zj;
-        } else {
-            vkx = -zh * xh; vky = -zh * yh; vkz = 1 - zh * zh;
-            vjx = -zj * xj; vjy = -zj * yj; vjz = 1 - zj * zj;
-        }
-        R gjx = scj * (SAj * xj + SBj * vjx);
-        R gjy = scj * (SAj * yj + SBj * vjy);
-        R gjz = scj * (SAj * zj + SBj * vjz);
-        if (active) {
-            ax += (double)(sck * (SAk * xh + SBk * vkx));
-            ay += (double)(sck * (SAk * yh + SBk * vky));
-            az += (double)(sck * (SAk * zh + SBk * vkz));
-        } else {
-            gjx = 0;
-            gjy = 0;
-            gjz = 0;
-        }
-        const int src = (lane & W) | ((hl - sft) & (W - 1));
-        ax += (double)__shfl(gjx, src);
-        ay += (double)__shfl(gjy, src);
-        az += (double)__shfl(gjz, src);
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, kCtrl, kRows, 0xF, false);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), kCtrl, kRows, 0xF, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ inline double readlane(double v, int lane)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Sums over the lanes of the wave below this one, and above it.  Each runs in
+// its own direction and leaves the own lane out before it adds: the terms
+// span r^l over the tile, so a total less a part would cancel.
+__device__ inline double wave_sum_below(double v)
+{
+    v = dpp_or_zero<0x138>(v);            // wave_shr:1
+    v += dpp_or_zero<0x111>(v);           // row_shr:1, 2, 4, 8
+    v += dpp_or_zero<0x112>(v);
+    v += dpp_or_zero<0x114>(v);
+    v += dpp_or_zero<0x118>(v);
+    v += dpp_or_zero<0x142, 0xA>(v);      // row_bcast:15 into rows 1 and 3
+    v += dpp_or_zero<0x143, 0xC>(v);      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+__device__ inline double wave_sum_above(double v, int lane)
+{
+    v = dpp_or_zero<0x130>(v);            // wave_shl:1
+    v += dpp_or_zero<0x101>(v);           // row_shl:1, 2, 4, 8
+    v += dpp_or_zero<0x102>(v);
+    v += dpp_or_zero<0x104>(v);
+    v += dpp_or_zero<0x108>(v);
+    const double t3 = readlane(v, 48), t2 = t3 + readlane(v, 32), t1 = t2 + readlane(v, 16);
+    return v + (lane < 16 ? t1 : lane < 32 ? t2 : lane < 48 ? t3 : 0.0);
+}
+
+// The whole field of the l >= 1, m = 0 channels (the axisymmetric kernel): with
+// only l_max channels the tile's own pairs go through the radial scan too,
+// carried on from the tile's coefficients lane by lane: about 60 instructions
+// per degree where the pair sums took 18 per degree and pair shift (16 or 32
+// shifts).  In FP64 in both precision modes.  1e6 particles, l_max 1: the field
+// kernel 141 -> 130 us (of which the push's sort slots take 90).
+// Returns grad Phi; Ht is the tile's row of H, CRg the group's coefficients.
+__device__ inline void axisym_field(int lane, int L, const Tables &tb, double inv_nt, const double *Ht,
+                                    const double *CRg, double q, double x, double y, double z,
+                                    double &gx, double &gy, double &gz)
+{
+    const double r2 = x * x + y * y + z * z;
+    const double inv_r2 = 1.0 / r2, inv_r = 1.0 / sqrt(r2);
+    double Ga = 0.0, Gz = 0.0;
+    double Q1 = 1.0, Q2 = 0.0, D1 = 0.0, D2 = 0.0;   // Qh_{l-1}, Qh_{l-2} and their D_z
+    double sl = inv_r * inv_r2;                      // r^-(2l+1) at l = 1
+    for (int l = 1; l <= L; ++l) {
+        const double gr2 = ld_const(reinterpret_cast<const double *>(tb.fq4 + l), 0) * r2;
+        const double Qv = z * Q1 - gr2 * Q2;
+        const double Dz = (Q1 + z * D1) - gr2 * D2;
+        const double Qs = Qv * sl;
+        // sums of the lanes before (interior) and after (exterior) this one
+        const double below = wave_sum_below(q * Qv), above = wave_sum_above(q * Qs, lane);
+        const double g = ld_const(tb.chg, l - 1) * inv_nt;
+        const double a = ld_const(CRg, l - 1) + g * (ld_const(Ht, 4 * (l - 1)) + below);
+        const double b =
+            ld_const(CRg, L + l - 1) + g * (ld_const(Ht, 4 * (l - 1) + 2) + above);
+        Ga = fma((double)l * Qv, b, Ga);
+        Ga = fma(-(l + 1.0) * Qs, a, Ga);
+        Gz = fma(Dz, b, Gz);
+        Gz = fma(Dz * sl, a, Gz);
+        Q2 = Q1;
+        Q1 = Qv;
+        D2 = D1;
+        D1 = Dz;
+        sl *= inv_r2;
     }
+    const double xh = x * inv_r, yh = y * inv_r, c = z * inv_r;
+    const double radial = Ga * inv_r - c * Gz;
+    gx = xh * radial;
+    gy = yh * radial;
+    gz = c * Ga * inv_r + (xh * xh + yh * yh) * Gz;
 }
 
 // One wave's particles for the near field: each block's rows written twice
@@ -1817,7 +1816,7 @@ __device__ inline void near_field_full(int lane, int W, int L, const LG *lg, con
 // FP32 (half the LDS rows, fewer registers) runs at six waves per SIMD;
 // NEAR64: FP32 far field with the near field in FP64 (FP32 mode at high l_max)
 template <bool FULL, bool FIELD_ONLY, bool FP32, bool NEAR64>
-__global__ __launch_bounds__(kBlock, FP32 && !NEAR64 ? 6 : 4) void k_field_push(Map mp, State B, PRec *A, uint8_t *dead,
+__global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 ? 6 : 4) void k_field_push(Map mp, State B, PRec *A, uint8_t *dead,
                                                        Grave G, const double *H,
                                                        const double *CR, const double *qpre,
                                                        Tables tb, KParams kp, double *Eout,
@@ -1842,7 +1841,7 @@ __global__ __launch_bounds__(kBlock, FP32 && !NEAR64 ? 6 : 4) void k_field_push(
         NearRows<R> rows;
         RF cf[kLdsBytes / sizeof(RF)];
     };
-    __shared__ WaveLds lds[kWavesPerBlock];
+    __shared__ typename std::conditional<FULL, WaveLds, double>::type lds[kWavesPerBlock];
 
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
@@ -1863,7 +1862,6 @@ __global__ __launch_bounds__(kBlock, FP32 && !NEAR64 ? 6 : 4) void k_field_push(
     const uint32_t p = tile * kWave + lane;
     const uint32_t pl = lt * kWave + lane;
     const bool valid = tile_live && pl < n;
-    const int jn = tile_live ? (int)min((uint32_t)kWave, n - lt * kWave) : 0;
 
     // (the velocities are read at the push, so that they hold no registers
     // through the field evaluation)
@@ -1905,8 +1903,16 @@ __global__ __launch_bounds__(kBlock, FP32 && !NEAR64 ? 6 : 4) void k_field_push(
     }
     const double inv_rho = 1.0 / rho;
 
-    // ---- far field (all particles outside this lane's near-field block) ----
     double Ex, Ey, Ez;
+    if constexpr (!FULL) {
+        double gx, gy, gz;
+        axisym_field(lane, L, tb, inv_nt, Hg + w * kp.HW, CR + (size_t)group * kp.C2, valid ? qk : 0.0,
+                     x, y, z, gx, gy, gz);
+        Ex = -gx;
+        Ey = -gy;
+        Ez = -gz;
+    } else {
+    // ---- far field (all particles outside this lane's near-field block) ----
     {
         RF gx, gy, gz;
         const NFF *fq;
@@ -2007,7 +2013,7 @@ __global__ __launch_bounds__(kBlock, FP32 && !NEAR64 ? 6 : 4) void k_field_push(
             }
             return CfView<RF>{cbuf + (lane >= kHalf ? kH1 : 0), win0};
         };
-        far_field<FULL, RF>(stage, L, fq, xs, ys, zs, gx, gy, gz);
+        far_field<RF>(stage, L, fq, xs, ys, zs, gx, gy, gz);
         wave_lds_sync();   // read before the rows below overwrite them
         Ex = -(double)gx * inv_rho;
         Ey = -(double)gy * inv_rho;
@@ -2032,26 +2038,19 @@ __global__ __launch_bounds__(kBlock, FP32 && !NEAR64 ? 6 : 4) void k_field_push(
     wave_lds_sync();   // the rows are this wave's own
     {
         double ax = 0.0, ay = 0.0, az = 0.0;
-        if (L < 1) {
-            // monopole only: Gauss's law below
-        } else if constexpr (FULL) {
+        if (L >= 1) {   // else monopole only: Gauss's law below
             const NF *lg;
             if constexpr (std::is_same<R, float>::value) lg = tb.lw4_32;
             else lg = tb.lg4;
             near_field_full<R, NF>(lane, NW, L, lg, nr, (R)xh, (R)yh, (R)zh, (R)r, (R)inv_r,
                                    (R)(r * inv_rho - 1.0), (R)rho, valid ? (R)qk : (R)0, ax,
                                    ay, az);
-        } else {
-            const NF *nf;
-            if constexpr (std::is_same<R, float>::value) nf = tb.nf4_32;
-            else nf = tb.nf4;
-            near_field<FULL, R, NF>(lane, NW, jn, L, nf, nr.xh, nr.yh, nr.zh, nr.r, nr.ir, nr.q,
-                                    (R)xh, (R)yh, (R)zh, (R)r, (R)inv_r, (R)qk, ax, ay, az);
         }
         const double cn = -1.0 / (4.0 * kPi * ntilde);
         Ex += cn * ax;
         Ey += cn * ay;
         Ez += cn * az;
+    }
     }
 
     // ---- self-image correction: the totals T_lm include the particle's own
@@ -2074,8 +2073,9 @@ __global__ __launch_bounds__(kBlock, FP32 && !NEAR64 ? 6 : 4) void k_field_push(
             for (int l = 1; l <= L; ++l) {
                 sr += tb.self_w[l] * rl * P1 * (-(l + 1.0) * P1);
                 sz += tb.self_w[l] * rl * P1 * dP1;
-                const double P2 = tb.nfA[l] * zh * P1 - tb.nfB[l] * P0;
-                const double dP2 = dP0 + (2.0 * l + 1.0) * P1;
+                const double4 e = tb.nf4[l];
+                const double P2 = e.x * zh * P1 - e.y * P0;
+                const double dP2 = dP0 + e.z * P1;
                 P0 = P1;
                 P1 = P2;
                 dP0 = dP1;
@@ -2811,7 +2811,7 @@ int launch_step(sim *h, hipStream_t s, bool field_only, hipEvent_t *ev)
                                                             h->krec, h->hist)
 #define MRP_FIELD_P(FULLV, FO)                                           \
     do {                                                                 \
-        if (lo.near64) MRP_FIELD(FULLV, FO, true, true);                 \
+        if (FULLV && lo.near64) MRP_FIELD(FULLV, FO, true, FULLV);       \
         else if (lo.fp32) MRP_FIELD(FULLV, FO, true, false);             \
         else MRP_FIELD(FULLV, FO, false, false);                         \
     } while (0)
@@ -2959,15 +2959,12 @@ void bind_device_tables(sim *h)
     h->tb.wl = tb + (L + 1);
     h->tb.drive_w = tb + 2 * (L + 1);
     h->tb.self_w = tb + 3 * (L + 1);
-    h->tb.nfA = tb + 4 * (L + 1);
-    h->tb.nfB = tb + 5 * (L + 1);
     h->tb.nf4 = reinterpret_cast<const double4 *>(tb + nf4_offset(L));
     h->tb.lg4 = reinterpret_cast<const double4 *>(tb + lg4_offset(L));
     h->tb.fq4 = reinterpret_cast<const double4 *>(tb + fq4_offset(L));
     h->tb.chn = h->chn;
     h->tb.chl = h->chl;
     h->tb.chg = h->chg;
-    h->tb.nf4_32 = reinterpret_cast<const float4 *>(h->tables32 + nf4_32_offset(L));
     h->tb.lg4_32 = reinterpret_cast<const float4 *>(h->tables32 + lg4_32_offset(L));
     h->tb.fq4_32 = reinterpret_cast<const float4 *>(h->tables32 + fq4_32_offset(L));
     h->tb.lw4_32 = reinterpret_cast<const float4 *>(h->tables32 + lw4_32_offset(L));

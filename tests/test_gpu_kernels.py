@@ -71,3 +71,20 @@ def test_group_ranking_matches_oracle(n, bucket, spread):
         E = sim.eval_field()
     Eo, _ = O.field(op, pos, ids=ids)
     assert _err(E, Eo) <= 1e-12
+
+
+# The axisymmetric field's scan over the lanes of a tile: lanes of one row, of
+# every row, partly filled tiles, the largest degree; both precisions (it runs
+# in FP64 in either, so the FP32 mode's fields hold 1e-12 too, except for its
+# l = 0 term in plain FP64: its rounding of ~1e-16 of the monopole field is far
+# below that here).
+@pytest.mark.parametrize("precision", [S.SIM_FP64, S.SIM_FP32_COMP], ids=["fp64", "fp32c"])
+@pytest.mark.parametrize("n,L", [(1, 1), (2, 1), (17, 2), (49, 5), (64, 1), (65, 64), (300, 21)])
+def test_axisymmetric_scan_matches_oracle(n, L, precision):
+    print(f"[gpu] axisymmetric scan n={n} L={L} p={precision}", file=sys.stderr, flush=True)
+    sp, op = _params(n, L, S.SIM_M_AXISYM, precision=precision)
+    st = W.uniform_shell(n, 800 + n, 5.0, 0.08)
+    with S.Sim(sp, st.pos, st.vel, np.array([0.1])) as sim:
+        E = sim.eval_field()
+    Eo, _ = O.field(op, st.pos, u_asy=0.1)
+    assert _err(E, Eo) <= 1e-12
