@@ -300,15 +300,61 @@ struct alignas(16) OrdRec {
     uint32_t uid, idx;
 };
 
-// Key, bucket and slot inside the bucket, over all particle slots.  One
-// step moves a particle across ~10^2 buckets, so the lanes of a wave land in
-// almost distinct buckets: each takes its slot with its own atomic add.
+// Orders this wave's LDS accesses at this point: LDS instructions of one wave
+// complete in issue order, so rows a wave wrote are visible to its later
+// reads without a block barrier; the fences keep the compiler from moving
+// LDS accesses across.
+__device__ inline void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Slot inside bucket b, by the bucket's atomic count; all lanes of the wave call
+// it, `on` marks those with a particle.  The lanes of a wave are neighbours in
+// radius.  Where a step moves them little (cold plasma, ions, small time
+// steps) they land in a few buckets, and their atomics on the few cache lines
+// of those counts queue up: then the wave counts in LDS first and adds each
+// bucket's count once, neighbouring counts from neighbouring lanes.  1e6
+// electrons and ions at dt 0.01: the field and push kernel 130 -> 40 us, the key kernel
+// 51 -> 20.  Spread wider than
+// kSlotWindow buckets, the atomics already fall on distinct lines.
+constexpr uint32_t kSlotWindow = 256;
+
+__device__ inline uint32_t take_slot(int lane, bool on, uint32_t b, uint32_t *hist, uint32_t *cnt)
+{
+    const uint64_t any = __ballot(on);
+    if (!any) return 0;
+    const uint32_t mid =
+        (uint32_t)__builtin_amdgcn_readlane((int)b, (int)__builtin_ctzll(any));
+    const uint32_t base = mid - kSlotWindow / 2, d = b - base;
+    if (__ballot(on && d >= kSlotWindow)) return on ? atomicAdd(&hist[b], 1u) : 0u;
+#pragma unroll
+    for (uint32_t k = 0; k < kSlotWindow; k += kWave) cnt[k + lane] = 0u;
+    wave_lds_sync();
+    const uint32_t my = on ? atomicAdd(&cnt[d], 1u) : 0u;
+    wave_lds_sync();
+    uint32_t first[kSlotWindow / kWave];
+#pragma unroll
+    for (uint32_t k = 0; k < kSlotWindow / kWave; ++k) {
+        const uint32_t c = cnt[k * kWave + lane];
+        first[k] = c ? atomicAdd(&hist[base + k * kWave + lane], c) : 0u;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kSlotWindow / kWave; ++k) cnt[k * kWave + lane] = first[k];
+    wave_lds_sync();
+    return on ? my + cnt[d] : 0u;
+}
+
+// Key, bucket and slot inside the bucket, over all particle slots.
 // Members whose last push already produced this step's records (keys_for)
 // are skipped: the push kernel's tail does the same work for the particles
 // it moves, where the field's arithmetic hides the atomics' latency.
-__global__ void k_sort_key(Map mp, const PRec *A, const uint8_t *dead, KeyRec *krec,
-                           uint32_t *hist, KParams kp)
+__global__ __launch_bounds__(kBlock) void k_sort_key(Map mp, const PRec *A, const uint8_t *dead,
+                                                     KeyRec *krec, uint32_t *hist, KParams kp)
 {
+    __shared__ uint32_t cnt[kWavesPerBlock][kSlotWindow];
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     const uint32_t tile = i >> 6;
     if ((int)tile >= kp.n_tiles) return;   // whole waves: i < 64 * n_tiles
@@ -328,12 +374,15 @@ __global__ void k_sort_key(Map mp, const PRec *A, const uint8_t *dead, KeyRec *k
         }
     }
     KeyRec rec{0ull, 0u, kNone};
+    uint32_t b = 0;
     if (live) {
         const double r2 = key_r2(A[i].x, A[i].y, A[i].z);
         rec.key = (uint64_t)__double_as_longlong(r2);
         rec.uid = A[i].uid;
-        rec.sub = atomicAdd(&hist[bucket_of(r2, inv_vol, b0, nb)], 1u);
+        b = bucket_of(r2, inv_vol, b0, nb);
     }
+    const uint32_t sub = take_slot(threadIdx.x & 63, live, b, hist, cnt[threadIdx.x >> 6]);
+    if (live) rec.sub = sub;
     krec[i] = rec;
 }
 
@@ -724,17 +773,6 @@ constexpr int kMomHalves = kGroupSlots / kHalf;    // halves of a group
 constexpr int kMomHalfOff = kMomLanes + 2;
 constexpr int kMomRow = kMomHalves * kMomHalfOff;
 static_assert(2 * kMomSlots * kMomHalves == kWave, "one lane per sum of a batch");
-
-// Orders this wave's LDS accesses at this point: LDS instructions of one wave
-// complete in issue order, so rows a wave wrote are visible to its later
-// reads without a block barrier; the fences keep the compiler from moving
-// LDS accesses across.
-__device__ inline void wave_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // The value of another lane of this lane's quad, through DPP: kPerm is a
 // quad_perm control (0xB1: lane xor 1, 0x4E: lane xor 2).  A quad
@@ -1594,7 +1632,7 @@ __device__ inline double wave_sum_above(double v, int lane)
 // carried on from the tile's coefficients lane by lane: about 60 instructions
 // per degree where the pair sums took 18 per degree and pair shift (16 or 32
 // shifts).  In FP64 in both precision modes.  1e6 particles, l_max 1: the field
-// kernel 141 -> 130 us (of which the push's sort slots take 90).
+// kernel 141 -> 130 us.
 // Returns grad Phi; Ht is the tile's row of H, CRg the group's coefficients.
 __device__ inline void axisym_field(int lane, int L, const Tables &tb, double inv_nt, const double *Ht,
                                     const double *CRg, double q, double x, double y, double z,
@@ -1841,7 +1879,12 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 ? 6 : 4) void k
         NearRows<R> rows;
         RF cf[kLdsBytes / sizeof(RF)];
     };
-    __shared__ typename std::conditional<FULL, WaveLds, double>::type lds[kWavesPerBlock];
+    // (the axisymmetric kernel has neither; the push's slot counts come last)
+    struct Counts {
+        uint32_t c[kSlotWindow];
+    };
+    static_assert(sizeof(WaveLds) >= sizeof(Counts), "slot counts exceed the wave's LDS");
+    __shared__ typename std::conditional<FULL, WaveLds, Counts>::type lds[kWavesPerBlock];
 
     const int lane = threadIdx.x & 63;
     const int w = threadIdx.x >> 6;
@@ -2134,12 +2177,15 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 ? 6 : 4) void k
         }
         return;
     }
-    if (!valid) return;
-
     // ---- leapfrog (Sec. 4 equations of motion) ----
     const double qm = ion ? sg.ion_qm : kQ / kM;
     const double dt = sg.dt;
-    double vx = B.vx[p], vy = B.vy[p], vz = B.vz[p];
+    double vx = 0.0, vy = 0.0, vz = 0.0;
+    if (valid) {
+        vx = B.vx[p];
+        vy = B.vy[p];
+        vz = B.vz[p];
+    }
     vx = __dadd_rn(vx, __dmul_rn(qm * Ex, dt));
     vy = __dadd_rn(vy, __dmul_rn(qm * Ey, dt));
     vz = __dadd_rn(vz, __dmul_rn(qm * Ez, dt));
@@ -2152,7 +2198,7 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 ? 6 : 4) void k
     uint8_t absorbed = 0;
     const int64_t step = ct.step;
     const double r_out = sg.r_out;
-    if (rn <= 1.0 || rn >= r_out) {
+    if (valid && (rn <= 1.0 || rn >= r_out)) {
         const bool probe = rn <= 1.0;
         const int bc = probe ? sg.probe_bc : sg.wall_bc;
         if (probe && bc == SIM_BC_ABSORB) {
@@ -2187,29 +2233,34 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 ? 6 : 4) void k
             }
         }
     }
-    PRec out;
-    out.x = x;
-    out.y = y;
-    out.z = z;
-    out.vx = vx;
-    out.vy = vy;
-    out.vz = vz;
-    out.uid = uid;
-    out.pad[0] = out.pad[1] = out.pad[2] = 0u;
-    A[p] = out;
-    dead[p] = absorbed;
+    if (valid) {
+        PRec out;
+        out.x = x;
+        out.y = y;
+        out.z = z;
+        out.vx = vx;
+        out.vy = vy;
+        out.vz = vz;
+        out.uid = uid;
+        out.pad[0] = out.pad[1] = out.pad[2] = 0u;
+        A[p] = out;
+        dead[p] = absorbed;
+    }
     // the next step's sort record of this slot, when the member runs then
     // (the same key, bucket and atomic slot as the key kernel would take;
     // the histogram was cleared by this step's offsets kernel)
     if (kp.fuse_keys && step + 1 < sg.n_steps) {
+        const bool live = valid && !absorbed;
+        const double k2 = key_r2(x, y, z);
+        const uint32_t sub = take_slot(lane, live, bucket_of(k2, sg.inv_vol, sg.b0, sg.nb), hist,
+                                       reinterpret_cast<uint32_t *>(&lds[w]));
         KeyRec kr{0ull, 0u, kNone};
-        if (!absorbed) {
-            const double k2 = key_r2(x, y, z);
+        if (live) {
             kr.key = (uint64_t)__double_as_longlong(k2);
             kr.uid = uid;
-            kr.sub = atomicAdd(&hist[bucket_of(k2, sg.inv_vol, sg.b0, sg.nb)], 1u);
+            kr.sub = sub;
         }
-        krec[p] = kr;
+        if (valid) krec[p] = kr;
     }
     if (absorbed) {
         if (ion) atomicAdd(&ct.n_dead_ion, 1u);
