@@ -119,11 +119,11 @@ typedef struct {
      * of the radial carries (the autotuner's knobs; 0 = built-in choice):
      * sort_bucket: mean particles per radial sort bucket, 1..256 (built-in 8);
      * carry_chunk: groups of 256 particle slots per carry chunk, 8..1024
-     * (built-in: a power of two in [8, 64], about a member's groups / 256);
+     * (built-in: none up to 512 groups, which scan in one kernel; beyond, a
+     * power of two in [8, 64], about a member's groups / 256);
      * sort_keys: where the next step's radial sort keys and bucket slots
-     * are taken: 1 in the tail of the push, -1 in a pass of their own, 0 by
-     * launch size (the push from 2048 tiles of 64 particles on).  Results
-     * are bit-identical either way.
+     * are taken: 1 or 0 in the tail of the push, -1 in a pass of their own.
+     * Results are bit-identical either way.
      * near_split: the near field's pair sums run over blocks of 32 radially
      * consecutive particles (1) or 64 (-1), the pairs across blocks through
      * the radial scan; 0: by member, 32 in FP64 and, in FP32, where

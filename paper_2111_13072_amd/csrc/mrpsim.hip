@@ -102,9 +102,10 @@ struct Ctl {
     uint32_t n_dead;    // particles absorbed so far (graveyard fill)
     uint32_t n_dead_ion;  // of which ions
     double q_surface;   // Q_S used by this step's field
-    // the step whose sort keys, bucket slots and bucket counts the last push
-    // already produced (-1: none; the key kernel computes them)
-    int64_t keys_for = -1;
+    // the last push already produced this step's sort keys, bucket slots and
+    // bucket counts (else the key kernel computes them)
+    uint32_t keyed;
+    uint32_t pushed;    // this step is done once its kernels are; step and n_cur are yet to follow
 };
 
 // Per-member description (device table, written by the host between steps).
@@ -130,6 +131,7 @@ struct Seg {
     int32_t ion_k;
     int32_t near_w;     // particles of a near-field block: 32 (a half tile) or 64 (the tile)
     int32_t used;
+    int32_t one_carry;  // the carries in one kernel, without chunks (carry_member)
 };
 
 constexpr uint32_t kNone = 0xffffffffu;
@@ -192,12 +194,6 @@ struct KParams {
     // moments kernel: slice s of m is [m_slice[s], m_slice[s + 1])
     uint8_t m_slice[kMaxMSlices + 1];
 };
-
-// The push's tail takes over the key pass from this many tiles on: the
-// tail's atomic round trip costs ~3 us per step on a small launch (1e4
-// particles: 0.0658 -> 0.0674 ms), the key pass it replaces ~30 ns per
-// thousand particles plus its launch (2e6: 64 us against 16 in the push).
-constexpr int kFuseKeysMinTiles = 2048;
 
 // Device tables shared by the kernels.
 struct Map {
@@ -348,7 +344,7 @@ __device__ inline uint32_t take_slot(int lane, bool on, uint32_t b, uint32_t *hi
 }
 
 // Key, bucket and slot inside the bucket, over all particle slots.
-// Members whose last push already produced this step's records (keys_for)
+// Members whose last push already produced this step's records (keyed)
 // are skipped: the push kernel's tail does the same work for the particles
 // it moves, where the field's arithmetic hides the atomics' latency.
 __global__ __launch_bounds__(kBlock) void k_sort_key(Map mp, const PRec *A, const uint8_t *dead,
@@ -366,7 +362,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_key(Map mp, const PRec *A, cons
         const Seg &sg = mp.seg[mb];
         const Ctl &c = mp.ctl[mb];
         if (member_runs(sg, c, kp)) {
-            if (c.keys_for == c.step) return;   // wave-uniform
+            if (c.keyed) return;   // wave-uniform
             live = (i - sg.p0) < c.n_cur && !dead[i];
             inv_vol = sg.inv_vol;
             b0 = sg.b0;
@@ -409,8 +405,32 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t *total)
     return off + inc - v;
 }
 
-__global__ __launch_bounds__(kBlock) void k_scan_a(const uint32_t *in, uint32_t *bsum, int n)
+// Moves the members whose push is done on to their next step.  Part of the
+// first kernel of a step that does not look at the members (the bucket
+// offsets), so that it costs no launch of its own; k_step_finish does it where
+// another kernel comes before that.
+__device__ inline void finish_steps(const Map &mp, const KParams &kp)
 {
+    for (int s = threadIdx.x; s < kp.n_members; s += blockDim.x) {
+        Ctl &c = mp.ctl[s];
+        if (!mp.seg[s].used || !c.pushed) continue;
+        c.pushed = 0;
+        c.step += 1;
+        c.n_cur = c.n_live;
+        // the push produced the sort records of the step the member runs next
+        c.keyed = kp.fuse_keys && c.step < mp.seg[s].n_steps;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_step_finish(Map mp, KParams kp)
+{
+    finish_steps(mp, kp);
+}
+
+__global__ __launch_bounds__(kBlock) void k_scan_a(Map mp, KParams kp, const uint32_t *in,
+                                                   uint32_t *bsum, int n)
+{
+    if (blockIdx.x == 0) finish_steps(mp, kp);
     const int base = blockIdx.x * kScanPerBlock;
     uint32_t s = 0;
     for (int k = threadIdx.x; k < kScanPerBlock; k += kBlock) {
@@ -460,8 +480,10 @@ __global__ __launch_bounds__(kBlock) void k_scan_c(uint32_t *in, const uint32_t 
 // replaces the two kernels above by one launch (small runs are launch-bound).
 constexpr int kScanSingleMaxBlocks = 4;
 
-__global__ __launch_bounds__(kBlock) void k_scan_single(uint32_t *in, uint32_t *out, int n)
+__global__ __launch_bounds__(kBlock) void k_scan_single(Map mp, KParams kp, uint32_t *in,
+                                                        uint32_t *out, int n)
 {
+    finish_steps(mp, kp);
     constexpr int per = kScanPerBlock / kBlock;
     uint32_t carry = 0;
     for (int base0 = 0; base0 < n; base0 += kScanPerBlock) {
@@ -498,7 +520,10 @@ __device__ inline void member_live(const Map &mp, const uint32_t *off, const KPa
         const Seg &sg = mp.seg[s];
         Ctl &c = mp.ctl[s];
         if (!member_runs(sg, c, kp)) continue;
-        c.keys_for = -1;   // this step's sort records are consumed
+        c.keyed = 0;   // this step's sort records are consumed
+        // the next step's first kernel finds this one's push done (set here, not
+        // in the push: a store there makes the field's table loads vector loads)
+        if (!kp.field_only) c.pushed = 1;
         c.n_live = off[sg.b0 + sg.nb] - off[sg.b0];
         c.q_surface =
             (sg.q_surface0 + kQ * (double)(c.n_dead - c.n_dead_ion)) + (double)c.n_dead_ion;
@@ -1100,6 +1125,7 @@ __device__ inline bool chunk_groups(const Map &mp, const KParams &kp, int j, uin
     const uint32_t m = mp.chunk_member[j];
     if (m == kNone || !member_runs(mp.seg[m], mp.ctl[m], kp)) return false;
     const Seg &sg = mp.seg[m];
+    if (sg.one_carry) return false;
     *mb = m;
     *g0 = (int)(sg.g0 + (uint32_t)(j - (int)sg.c0) * sg.cl);
     *g1 = min(*g0 + (int)sg.cl, (int)(sg.g0 + sg.ng));
@@ -1129,12 +1155,147 @@ struct CompSum {
 // keep the group order.
 constexpr int kCarryBatch = 8;
 
-__global__ __launch_bounds__(kBlock) void k_chunk_sums(Map mp, const double *__restrict__ GS,
-                                                       double *__restrict__ chunkS, KParams kp)
+// A channel's weights: interior sums of Qh = Q / N_lm to coefficients
+// (carry * w + k) * nrm, with the image response of the exterior total and
+// the drive in k; exterior ones carry * w_out.
+struct ChannelWeights {
+    double w, k, nrm, w_out;
+};
+
+__device__ inline ChannelWeights channel_weights(const Tables &tb, const Seg &sg, int c, int L,
+                                                 double total, bool in_run, int64_t step)
 {
+    const int l = tb.chl[c];
+    ChannelWeights cw;
+    cw.nrm = tb.chn[c];
+    cw.w = tb.wl[l] * sg.inv_ntilde * cw.nrm;
+    cw.w_out = cw.w * cw.nrm;
+    cw.k = -tb.ftil[l] * total * cw.w;
+    if (c < L && in_run) cw.k += sg.u_asy[step] * tb.drive_w[l];
+    return cw;
+}
+
+// All carries of a member of few groups in one kernel: a block takes kOneCols
+// channels, both sides, with the member's groups in kOneSegs segments of scan
+// order, one (column, segment) per thread; the segments' sums meet in LDS.  Up
+// to kOneCarryGroups groups this replaces three launches of one HBM round trip
+// or two each (10,000 particles, l_max 8: the step 52.8 -> 45.2 us together with
+// the two launches that the steps' ends and the sort keys took; 100,117
+// particles, l_max 16: 97.2 -> 93.5 us).  At 392 groups the kernel takes 12.5 us
+// against 14.6 us for the three; beyond about 512 the segments' walks are longer.
+constexpr int kOneCols = 8, kOneSegs = kBlock / (2 * kOneCols);
+constexpr int kOneCarryGroups = 512;
+
+__host__ __device__ inline int one_carry_blocks(int C) { return C / kOneCols + 2; }
+
+__device__ inline void carry_member(const Seg &sg, const Ctl &ct, int block, const double *GS,
+                                    const Tables &tb, const KParams &kp, double *CR, double *qpre)
+{
+    __shared__ double ps[kOneSegs][2 * kOneCols], pe[kOneSegs][2 * kOneCols], tot[kOneCols];
+    const int col = threadIdx.x & (2 * kOneCols - 1), sgm = threadIdx.x / (2 * kOneCols);
+    const int side = col / kOneCols, j = col & (kOneCols - 1);
+    const int ng = (int)sg.ng, per = (ng + kOneSegs - 1) / kOneSegs;
+    const int q0 = min(sgm * per, ng), q1 = min(q0 + per, ng);
+    const size_t sw = (size_t)kp.SW;
+    const double *src = GS + (size_t)sg.g0 * sw;
+    const int64_t step = ct.step;
+    const bool in_run = step >= 0 && step < sg.n_steps;
+    // calls f(group, value) over this thread's segment of a column, in scan
+    // order, with the loads of kCarryBatch groups issued ahead (a segment held
+    // in registers between its two walks: no faster, and 188 VGPRs)
+    auto walk = [&](int column, bool up, auto f) {
+        const double *at = src + column;
+        for (int q = q0; q < q1; q += kCarryBatch) {
+            double v[kCarryBatch];
+#pragma unroll
+            for (int k = 0; k < kCarryBatch; ++k) {
+                const int i = min(q + k, q1 - 1);
+                v[k] = at[(size_t)(up ? i : ng - 1 - i) * sw];
+            }
+#pragma unroll
+            for (int k = 0; k < kCarryBatch; ++k)
+                if (q + k < q1) f(up ? q + k : ng - 1 - q - k, v[k]);
+        }
+    };
+    auto add = [](CompSum &s, double v, double e) {
+        s.add(v);
+        s.e += e;
+    };
+    if (block == one_carry_blocks(kp.C) - 1) {
+        // the probe response: totals of the m = 0 channels of odd l, 16 at a time
+        double acc = 0.0;
+        for (int l0 = 1; l0 <= kp.L; l0 += 4 * kOneCols) {
+            const int l = l0 + 2 * col;
+            CompSum part;
+            if (l <= kp.L) walk(kp.C + l - 1, true, [&](int, double t) { part.add(t); });
+            __syncthreads();
+            ps[sgm][col] = part.s;
+            pe[sgm][col] = part.e;
+            __syncthreads();
+            if (threadIdx.x < 2 * kOneCols) {
+                CompSum t;
+                for (int k = 0; k < kOneSegs; ++k) add(t, ps[k][col], pe[k][col]);
+                ps[0][col] = l <= kp.L ? tb.drive_w[l] * tb.chn[l - 1] * t.value() : 0.0;
+            }
+            __syncthreads();
+            if (threadIdx.x == 0)
+                for (int k = 0; k < 2 * kOneCols; ++k) acc += ps[0][k];
+        }
+        if (threadIdx.x == 0 && in_run) sg.qdiff[step] = -acc / sg.ntilde;
+        return;
+    }
+    const int c = block * kOneCols + j;
+    const bool charge = c == kp.C && side == 0;   // the column past the last channel
+    const bool on = c < kp.C || charge;
+    const int column = charge ? kp.C2 : side * kp.C + c;
+    CompSum part;
+    if (on) walk(column, side == 0, [&](int, double t) { part.add(t); });
+    ps[sgm][col] = part.s;
+    pe[sgm][col] = part.e;
+    __syncthreads();
+    CompSum run;
+    for (int k = 0; k < sgm; ++k) add(run, ps[k][col], pe[k][col]);
+    if (side == 1 && sgm == kOneSegs - 1) {
+        CompSum t = run;
+        add(t, part.s, part.e);
+        tot[j] = t.value();
+    }
+    __syncthreads();
+    if (!on) return;
+    if (charge) {   // charge of the member's particles before each group
+        walk(column, true, [&](int g, double t) {
+            qpre[sg.g0 + g] = run.value();
+            run.add(t);
+        });
+        return;
+    }
+    const ChannelWeights cw = channel_weights(tb, sg, c, kp.L, tot[j], in_run, step);
+    double *dst = CR + (size_t)sg.g0 * kp.C2 + column;
+    walk(column, side == 0, [&](int g, double t) {
+        const double carry = run.value();
+        dst[(size_t)g * kp.C2] = side == 0 ? (carry * cw.w + cw.k) * cw.nrm : carry * cw.w_out;
+        run.add(t);
+    });
+}
+
+// Blocks past the n_chunks chunks: the carries of the members of few groups.
+__global__ __launch_bounds__(kBlock) void k_chunk_sums(Map mp, const double *__restrict__ GS,
+                                                       double *__restrict__ chunkS, Tables tb,
+                                                       KParams kp, int n_chunks, double *CR,
+                                                       double *qpre)
+{
+    const int j = blockIdx.x;
+    if (j >= n_chunks) {
+        const int i = (j - n_chunks) * (int)gridDim.y + (int)blockIdx.y;
+        const int per = one_carry_blocks(kp.C), m = i / per;
+        if (m >= kp.n_members) return;
+        const Seg &sg = mp.seg[m];
+        if (!sg.one_carry || !member_runs(sg, mp.ctl[m], kp)) return;
+        carry_member(sg, mp.ctl[m], i % per, GS, tb, kp, CR, qpre);
+        return;
+    }
     const int c = blockIdx.y * kBlock + threadIdx.x;
     if (c >= kp.SW) return;
-    const int j = blockIdx.x;
     uint32_t mb;
     int g0, g1;
     if (!chunk_groups(mp, kp, j, &mb, &g0, &g1)) return;
@@ -1167,7 +1328,7 @@ __global__ __launch_bounds__(kBlock) void k_chunk_scan(Map mp, const double *chu
     const int s = blockIdx.y;
     if (c >= kp.SW) return;
     const Seg &sg = mp.seg[s];
-    if (!member_runs(sg, mp.ctl[s], kp)) return;
+    if (sg.one_carry || !member_runs(sg, mp.ctl[s], kp)) return;
     const int nc = (int)sg.nc;
     const bool interior = c < kp.C || c == kp.C2;
     const double *cS = chunkS + (size_t)sg.c0 * kp.SW + c;
@@ -1229,7 +1390,6 @@ __global__ __launch_bounds__(kBlock) void k_chunk_apply(Map mp, const double *__
         sg.qdiff[step] = -acc / sg.ntilde;
     }
     if (c >= kp.SW) return;
-    const double inv_nt = sg.inv_ntilde;
     const size_t sw = (size_t)kp.SW;
     CompSum run;
     run.s = chunkC[(size_t)j * kp.SW + c];
@@ -1259,16 +1419,12 @@ __global__ __launch_bounds__(kBlock) void k_chunk_apply(Map mp, const double *__
     if (c == kp.C2) {   // charge of the member's particles before each group
         walk(1, [&](int g, double carry) { qpre[g] = carry; });
     } else if (c < kp.C) {
-        const int l = tb.chl[c];
-        const double nrm = tb.chn[c];
-        const double w = tb.wl[l] * inv_nt * nrm;   // the sums are of Qh = Q / N_lm
-        double k = -tb.ftil[l] * Ts[c] * w;
-        if (c < kp.L && in_run) k += sg.u_asy[step] * tb.drive_w[l];
-        walk(1, [&](int g, double carry) { CR[(size_t)g * kp.C2 + c] = (carry * w + k) * nrm; });
+        const ChannelWeights cw = channel_weights(tb, sg, c, kp.L, Ts[c], in_run, step);
+        walk(1, [&](int g, double carry) {
+            CR[(size_t)g * kp.C2 + c] = (carry * cw.w + cw.k) * cw.nrm;
+        });
     } else {
-        const int l = tb.chl[c - kp.C];
-        const double nrm = tb.chn[c - kp.C];
-        const double w = tb.wl[l] * inv_nt * nrm * nrm;   // sums of Qh; the field's Qh
+        const double w = channel_weights(tb, sg, c - kp.C, kp.L, 0.0, false, step).w_out;
         walk(-1, [&](int g, double carry) { CR[(size_t)g * kp.C2 + c] = carry * w; });
     }
 }
@@ -2275,19 +2431,6 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 ? 6 : 4) void k
     }
 }
 
-__global__ void k_step_finish(Map mp, KParams kp)
-{
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= kp.n_members) return;
-    Ctl &c = mp.ctl[s];
-    const Seg &sg = mp.seg[s];
-    if (!member_runs(sg, c, kp)) return;
-    c.step += 1;
-    c.n_cur = c.n_live;
-    // the push produced the sort records of the step the member runs next
-    if (kp.fuse_keys && c.step < sg.n_steps) c.keys_for = c.step;
-}
-
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
@@ -2363,10 +2506,11 @@ struct Layout {
 // cost of what it holds.
 struct Extent {
     int n_tiles = kTilesPerGroup, n_chunks = 1, nb = 1, nb_blocks = 1, n_members = 1;
+    bool one_carry = false, chunked = false;   // members of either kind of carries
     bool operator==(const Extent &o) const
     {
         return n_tiles == o.n_tiles && n_chunks == o.n_chunks && nb == o.nb &&
-               n_members == o.n_members;
+               n_members == o.n_members && one_carry == o.one_carry && chunked == o.chunked;
     }
 };
 
@@ -2391,6 +2535,13 @@ MemberShape member_shape(int64_t n, const Tuning &tu)
     m.nc = (m.ng + m.cl - 1) / m.cl;
     m.nb = (uint32_t)std::max<int64_t>(1, n / tu.bucket);
     return m;
+}
+
+// Whether a member's carries run in one kernel (by the member alone: the two
+// ways round differently).  A tuned chunk length asks for chunks.
+bool takes_one_carry(const Tuning &tu, uint32_t ng)
+{
+    return tu.chunk == 0 && ng <= (uint32_t)kOneCarryGroups;
 }
 
 bool check_common(const sim_params *p, std::string *why)
@@ -2576,6 +2727,8 @@ struct sim {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     bool failed = false;
+    bool stepped = false;      // a step has been enqueued
+    bool keys_needed = true;   // some running member has no sort keys for its next step
     size_t shared_bytes = 0;
     // one device allocation holds every array, the members' data pool last
     sim_allocator alloc{};      // caller's callbacks, or all NULL (hipMalloc / hipFree)
@@ -2793,38 +2946,58 @@ unsigned slice_orders(const Layout &lo, int n_groups, uint8_t *m_slice)
     return (unsigned)ny;
 }
 
-int launch_step(sim *h, hipStream_t s, bool field_only, hipEvent_t *ev)
+// The push prepares the next step's sort keys unless told otherwise.
+bool keys_in_push(const sim *h) { return h->lo.tu.keys >= 0; }
+
+// The kernels' parameters for the extent in use.
+KParams step_params(const sim *h, bool field_only)
 {
-    const Layout &lo = h->lo;
     const Extent &ex = h->ext;
     KParams kp = h->kp;
     kp.field_only = field_only ? 1 : 0;
-    kp.fuse_keys = lo.tu.keys != 0 ? (lo.tu.keys > 0 ? 1 : 0)
-                                   : (ex.n_tiles >= kFuseKeysMinTiles ? 1 : 0);
+    kp.fuse_keys = keys_in_push(h) ? 1 : 0;
     kp.n_tiles = ex.n_tiles;
     kp.n_groups = ex.n_tiles / kTilesPerGroup;
     kp.n_chunks = ex.n_chunks;
     kp.nb = ex.nb;
     kp.n_members = ex.n_members;
+    return kp;
+}
+
+// Sort keys of the members whose push did not prepare them.
+void launch_keys(sim *h, hipStream_t s, const KParams &kp)
+{
+    const unsigned n = (unsigned)h->ext.n_tiles * kWave;
+    if (h->stepped) k_step_finish<<<1, kBlock, 0, s>>>(h->map, kp);
+    k_sort_key<<<(n + kBlock - 1) / kBlock, kBlock, 0, s>>>(h->map, h->A, h->dead, h->krec, h->hist,
+                                                            kp);
+}
+
+// One step (or field evaluation).  with_keys: the key kernel comes first; not
+// needed where every running member's last push prepared its keys.
+int launch_step(sim *h, hipStream_t s, bool field_only, bool with_keys, hipEvent_t *ev)
+{
+    const Layout &lo = h->lo;
+    const Extent &ex = h->ext;
+    KParams kp = step_params(h, field_only);
     const Map &mp = h->map;
     const unsigned n = (unsigned)ex.n_tiles * kWave;
     const unsigned gN = (n + kBlock - 1) / kBlock;
     const unsigned gT = (unsigned)(ex.n_tiles / kTilesPerGroup);   // one block per group
     const unsigned gC = (unsigned)((lo.C2 + 1 + kBlock - 1) / kBlock);   // group-sum columns
-    const unsigned gM = (unsigned)((ex.n_members + kBlock - 1) / kBlock);
     int e = 0;
     auto mark = [&](int k) {
         if (ev) (void)hipEventRecord(ev[k], s);
     };
     mark(KN_SORT_KEY);
-    k_sort_key<<<gN, kBlock, 0, s>>>(mp, h->A, h->dead, h->krec, h->hist, kp);
+    if (with_keys) launch_keys(h, s, kp);
     if (ex.nb_blocks <= kScanSingleMaxBlocks) {
         mark(KN_SCAN_A);
         mark(KN_SCAN_C);
-        k_scan_single<<<1, kBlock, 0, s>>>(h->hist, h->off, ex.nb);
+        k_scan_single<<<1, kBlock, 0, s>>>(mp, kp, h->hist, h->off, ex.nb);
     } else {
         mark(KN_SCAN_A);
-        k_scan_a<<<ex.nb_blocks, kBlock, 0, s>>>(h->hist, h->bsum, ex.nb);
+        k_scan_a<<<ex.nb_blocks, kBlock, 0, s>>>(mp, kp, h->hist, h->bsum, ex.nb);
         mark(KN_SCAN_C);
         k_scan_c<<<ex.nb_blocks, kBlock, 0, s>>>(h->hist, h->bsum, h->off, ex.nb);
     }
@@ -2847,13 +3020,21 @@ int launch_step(sim *h, hipStream_t s, bool field_only, hipEvent_t *ev)
     }
 #undef MRP_MOMENTS
     mark(KN_CHUNK_SUMS);
-    k_chunk_sums<<<dim3(ex.n_chunks, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkS, kp);
+    const int chunks = ex.chunked ? ex.n_chunks : 0;
+    unsigned gOne = 0;   // block columns for the members of few groups
+    if (ex.one_carry)
+        gOne = (unsigned)((ex.n_members * one_carry_blocks(lo.C) + (int)gC - 1) / (int)gC);
+    if (chunks + gOne > 0)   // none in a handle without members
+        k_chunk_sums<<<dim3(chunks + gOne, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkS, h->tb, kp,
+                                                                chunks, h->CR, h->qpre);
     mark(KN_CHUNK_SCAN);
-    k_chunk_scan<<<dim3((lo.C2 + 1 + kWavesPerBlock - 1) / kWavesPerBlock, ex.n_members), kBlock, 0,
-                   s>>>(mp, h->chunkS, h->chunkC, h->T, kp);
+    if (ex.chunked)
+        k_chunk_scan<<<dim3((lo.C2 + 1 + kWavesPerBlock - 1) / kWavesPerBlock, ex.n_members),
+                       kBlock, 0, s>>>(mp, h->chunkS, h->chunkC, h->T, kp);
     mark(KN_CHUNK_APPLY);
-    k_chunk_apply<<<dim3(ex.n_chunks, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkC, h->T, h->tb, kp,
-                                                           h->CR, h->qpre);
+    if (ex.chunked)
+        k_chunk_apply<<<dim3(ex.n_chunks, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkC, h->T, h->tb,
+                                                               kp, h->CR, h->qpre);
     mark(KN_FIELD_PUSH);
 #define MRP_FIELD(FULLV, FO, F32, N64)                                                   \
     k_field_push<FULLV, FO, F32, N64><<<gT, kBlock, 0, s>>>(mp, h->B, h->A, h->dead, h->G, \
@@ -2872,9 +3053,8 @@ int launch_step(sim *h, hipStream_t s, bool field_only, hipEvent_t *ev)
     } else {
         if (lo.full) MRP_FIELD_P(true, false);
         else MRP_FIELD_P(false, false);
-        mark(KN_STEP_FINISH);
-        k_step_finish<<<gM, kBlock, 0, s>>>(mp, kp);
     }
+    mark(KN_STEP_FINISH);   // part of the next step's bucket offsets
     if (ev) (void)hipEventRecord(ev[KN_COUNT], s);
     hipError_t le = hipGetLastError();
     if (le != hipSuccess) e = fail(SIM_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(le));
@@ -2924,6 +3104,19 @@ int mark_failed(sim *h, int code)
 {
     if (code == SIM_EDEVICE) h->failed = true;
     return code;
+}
+
+// A member's control block (the handle's stream is idle), with a step whose
+// push is done counted as done.
+int read_ctl(sim *h, int32_t index, Ctl *c)
+{
+    if (hipMemcpy(c, h->ctl + index, sizeof(Ctl), hipMemcpyDeviceToHost) != hipSuccess)
+        return mark_failed(h, fail(SIM_EDEVICE, "copy of control block failed"));
+    if (c->pushed) {
+        c->step += 1;
+        c->n_cur = c->n_live;
+    }
+    return SIM_OK;
 }
 
 int check_member_index(sim *h, int32_t index)
@@ -3140,6 +3333,7 @@ int update_graph(sim *h)
         ex.n_chunks = std::max(ex.n_chunks, (int)(m.seg.c0 + m.seg.nc));
         ex.nb = std::max(ex.nb, (int)(m.seg.b0 + m.seg.nb));
         ex.n_members = std::max(ex.n_members, k + 1);
+        (m.seg.one_carry ? ex.one_carry : ex.chunked) = true;
     }
     ex.nb_blocks = (ex.nb + kScanPerBlock - 1) / kScanPerBlock;
     if (h->exec && ex == h->ext) return SIM_OK;
@@ -3150,7 +3344,8 @@ int update_graph(sim *h)
     h->ext = ex;
     if (hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
         return mark_failed(h, fail(SIM_EDEVICE, "hipStreamBeginCapture failed"));
-    int le = launch_step(h, h->cap_stream, false, nullptr);
+    h->stepped = true;   // from here on a step may be pending when keys are taken
+    int le = launch_step(h, h->cap_stream, false, !keys_in_push(h), nullptr);
     hipError_t ce = hipStreamEndCapture(h->cap_stream, &h->graph);
     if (le != SIM_OK) return mark_failed(h, le);
     if (ce != hipSuccess)
@@ -3269,6 +3464,7 @@ int engine_add(sim *h, const sim_member *m, Prepared &pr, int32_t *index)
     sg.n_steps = m->n_steps;
     sg.ion_qm = m->ion_mass > 0.0 ? 1.0 / m->ion_mass : 0.0;
     sg.near_w = near_width(h->lo.tu, h->lo.fp32, h->lo.L, n);
+    sg.one_carry = takes_one_carry(h->lo.tu, sh.ng) ? 1 : 0;
     sg.used = 1;
     auto undo = [&](int code) {
         free_member_arrays(h, mb);
@@ -3346,6 +3542,7 @@ int engine_add(sim *h, const sim_member *m, Prepared &pr, int32_t *index)
         return undo(fail(SIM_EDEVICE, "member upload failed"));
     }
     h->members[slot] = std::move(mb);
+    h->keys_needed = true;
     *index = slot;
     return SIM_OK;
 }
@@ -3380,6 +3577,15 @@ int engine_remove(sim *h, int32_t index)
 
 int enqueue_steps(sim *h, int64_t k)
 {
+    if (k > 0 && keys_in_push(h) && h->keys_needed) {
+        launch_keys(h, h->stream, step_params(h, false));
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) {
+            h->failed = true;
+            return fail(SIM_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(e));
+        }
+        h->keys_needed = false;
+    }
     for (int64_t i = 0; i < k; ++i) {
         hipError_t e = hipGraphLaunch(h->exec, h->stream);
         if (e != hipSuccess) {
@@ -3771,8 +3977,8 @@ int sim_member_read_state(sim_t *h, int32_t index, double *pos, double *vel, uin
     if (rc) return rc;
     const Member &mb = h->members[index];
     Ctl ctl;
-    if (hipMemcpy(&ctl, h->ctl + index, sizeof(Ctl), hipMemcpyDeviceToHost) != hipSuccess)
-        return mark_failed(h, fail(SIM_EDEVICE, "copy of control block failed"));
+    rc = read_ctl(h, index, &ctl);
+    if (rc) return rc;
     const int64_t n = mb.n;
     const size_t p0 = mb.seg.p0;
     const size_t na = ctl.n_cur, ng = ctl.n_dead;
@@ -3836,8 +4042,8 @@ int sim_member_counts(sim_t *h, int32_t index, int64_t *alive, int64_t *absorbed
     rc = sim_sync(h);
     if (rc) return rc;
     Ctl ctl;
-    if (hipMemcpy(&ctl, h->ctl + index, sizeof(Ctl), hipMemcpyDeviceToHost) != hipSuccess)
-        return mark_failed(h, fail(SIM_EDEVICE, "copy of control block failed"));
+    rc = read_ctl(h, index, &ctl);
+    if (rc) return rc;
     if (alive) *alive = h->members[index].n - (int64_t)ctl.n_dead;
     if (absorbed) *absorbed = (int64_t)ctl.n_dead;
     if (step) *step = ctl.step;
@@ -3857,14 +4063,15 @@ int sim_member_eval_field(sim_t *h, int32_t index, double *E)
     rc = check_member_index(h, index);
     if (rc) return rc;
     if (!E) return fail(SIM_EINVAL, "E is NULL");
-    rc = launch_step(h, h->stream, true, nullptr);
+    h->keys_needed = true;   // the evaluation uses up the keys of the next step
+    rc = launch_step(h, h->stream, true, true, nullptr);
     if (rc) return mark_failed(h, rc);
     rc = sim_sync(h);
     if (rc) return rc;
     const Member &mb = h->members[index];
     Ctl ctl;
-    if (hipMemcpy(&ctl, h->ctl + index, sizeof(Ctl), hipMemcpyDeviceToHost) != hipSuccess)
-        return mark_failed(h, fail(SIM_EDEVICE, "copy of control block failed"));
+    rc = read_ctl(h, index, &ctl);
+    if (rc) return rc;
     const size_t nl = ctl.n_live, p0 = mb.seg.p0;
     std::vector<double> e(3 * nl);
     std::vector<uint32_t> u(nl);
@@ -3950,13 +4157,14 @@ int sim_eval_field_static(const sim_params *p, int64_t n, const double *pos, dou
     sg.u_asy = reinterpret_cast<double *>(h.mdata);
     sg.qdiff = reinterpret_cast<double *>(h.mdata + kPoolUnit);
     sg.near_w = near_width(h.lo.tu, h.lo.fp32, h.lo.L, n);
+    sg.one_carry = takes_one_carry(h.lo.tu, sh.ng) ? 1 : 0;
+    (sg.one_carry ? h.ext.one_carry : h.ext.chunked) = true;
     sg.used = 1;
     Ctl ct{};
     ct.step = 0;
     ct.n_cur = (uint32_t)n;
     ct.n_live = (uint32_t)n;
     ct.q_surface = q_surface;
-    ct.keys_for = -1;
     hipStream_t s = (hipStream_t)hip_stream;
     const unsigned gSet = (unsigned)std::min<int64_t>(((int64_t)sh.nt * kWave + kBlock - 1) / kBlock, 4096);
     const unsigned gN = (unsigned)((n + kBlock - 1) / kBlock);
@@ -3974,7 +4182,7 @@ int sim_eval_field_static(const sim_params *p, int64_t n, const double *pos, dou
                            hipMemcpyHostToDevice, s));
     HIP_TRY(hipMemcpyAsync(h.tables32, ht.tab32.data(), sizeof(float) * ht.tab32.size(),
                            hipMemcpyHostToDevice, s));
-    if (int rc = launch_step(&h, s, true, nullptr)) return rc;
+    if (int rc = launch_step(&h, s, true, true, nullptr)) return rc;
     k_static_unpack<<<gN, kBlock, 0, s>>>(h.Eout, h.Eid, (uint32_t)n, E);
     const hipError_t le = hipGetLastError();
     if (le != hipSuccess) return fail(SIM_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(le));
@@ -3995,7 +4203,8 @@ int sim_profile(sim_t *h, int64_t k, double *kernel_ms, int32_t n_kernels)
         if (hipEventCreate(&ev[i]) != hipSuccess) return fail(SIM_EDEVICE, "hipEventCreate failed");
     std::vector<double> acc(KN_COUNT, 0.0);
     for (int64_t s = 0; s < k && rc == SIM_OK; ++s) {
-        rc = launch_step(h, h->stream, false, ev);
+        rc = launch_step(h, h->stream, false, !keys_in_push(h) || h->keys_needed, ev);
+        h->keys_needed = false;
         if (rc == SIM_OK && hipEventSynchronize(ev[KN_COUNT]) != hipSuccess)
             rc = fail(SIM_EDEVICE, "event sync failed");
         for (int i = 0; i < KN_COUNT && rc == SIM_OK; ++i) {

@@ -228,7 +228,7 @@ class SimParams:
     # launch sizes chosen by paper_2111_13072_amd.tune (0: built-in choice)
     sort_bucket: int = 0
     carry_chunk: int = 0
-    # where the sort keys are taken: 1 push, -1 own pass, 0 by launch size
+    # where the sort keys are taken: 0 or 1 push, -1 own pass
     sort_keys: int = 0
     # near-field block: 1 half tiles (32), -1 whole tiles (64), 0 by member
     near_split: int = 0

@@ -88,3 +88,29 @@ def test_axisymmetric_scan_matches_oracle(n, L, precision):
         E = sim.eval_field()
     Eo, _ = O.field(op, st.pos, u_asy=0.1)
     assert _err(E, Eo) <= 1e-12
+
+
+# The carries of a member in one kernel: segments of none, one and several
+# groups, columns and degrees past a block's, the last member size it takes and
+# the first it does not; Q_diff comes from a block of its own (l_max 33: two
+# passes over its columns).
+@pytest.mark.parametrize("n,L,mode", [(256 * 15, 4, S.SIM_M_FULL), (256 * 17 + 1, 7, S.SIM_M_FULL),
+                                      (600, 33, S.SIM_M_FULL), (300, 0, S.SIM_M_FULL),
+                                      (131_072, 3, S.SIM_M_FULL), (131_073, 3, S.SIM_M_FULL),
+                                      (90_001, 2, S.SIM_M_AXISYM)])
+def test_one_kernel_carries_match_chunked(n, L, mode):
+    """Against the chunked carries (a tuned chunk length asks for them), which
+    the oracle tests pin: the same compensated sums, one rounding apart."""
+    print(f"[gpu] one-kernel carries n={n} L={L} mode={mode}", file=sys.stderr, flush=True)
+    st = W.uniform_shell(n, 900 + L, 5.0, 0.08)
+    out = []
+    for chunk in (0, 8):
+        sp, _ = _params(n, L, mode, carry_chunk=chunk, q_surface0=-2.0)
+        with S.Sim(sp, st.pos, st.vel, np.array([0.3, 0.1, 0.0])) as sim:
+            E = sim.eval_field()
+            sim.step(3)
+            out.append((E, sim.read_response(0, 3), sim.read_state()["pos"]))
+    (E0, q0, p0), (E1, q1, p1) = out
+    assert _err(E0, E1) <= 1e-13
+    assert np.max(np.abs(q0 - q1)) <= 1e-13 * max(np.max(np.abs(q1)), 1e-300)
+    assert np.max(np.abs(p0 - p1)) <= 1e-13
