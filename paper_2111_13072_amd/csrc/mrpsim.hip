@@ -193,6 +193,9 @@ struct KParams {
     int fuse_keys;  // the push prepares the next step's sort records
     // moments kernel: slice s of m is [m_slice[s], m_slice[s + 1])
     uint8_t m_slice[kMaxMSlices + 1];
+    // field kernel: the same in kWavesPerBlock slices, their ends packed in bytes
+    // (an array here, indexed in a loop, would be copied to scratch memory)
+    uint32_t f_ends;
 };
 
 // Device tables shared by the kernels.
@@ -1642,7 +1645,21 @@ struct FarSums {
     }
 };
 
-// Adds the orders m0 <= m < m1 to the sums.  With t = b + s_l a and
+// C_{m-1}, S_{m-1} and r^-(2m-1) of the order m that comes next.
+template <typename R>
+struct FarPower {
+    double c = 1, s = 0, smm;
+    __device__ explicit FarPower(const FarPoint<R> &pt) : smm(pt.inv_rd) {}
+    __device__ void next(const FarPoint<R> &pt)
+    {
+        const double c1 = c, s1 = s;
+        c = fma(pt.xd, c1, -(pt.yd * s1));
+        s = fma(pt.xd, s1, pt.yd * c1);
+        smm *= pt.inv_r2d;
+    }
+};
+
+// Adds the order m = 0 to the sums.  With t = b + s_l a and
 // w = b - s_l a (s_l = r^-(2l+1)), each (l, m) adds Qh t to the sum for d/dx,
 // d/dy, t D_z Qh to the D_z sum, and to the radial sum
 // Qh [(l - m) b - (l + m + 1) s_l a] = (l + 1/2) Qh w - (m + 1/2) Qh t:
@@ -1652,59 +1669,58 @@ struct FarSums {
 // kernel at 1.6e7 particles, l_max 16, FP32 2.80 -> 2.67 ms, FP64 at 2e6 0.557 ->
 // 0.520 ms; errors against 64 bits the same, 1.2e-7 to 6e-7 in FP32.)
 template <typename R, typename R4, typename Stage>
+__device__ inline void far_order_zero(Stage &&stage, int L, const R4 *fq, const FarPoint<R> &pt,
+                                      FarSums<R> &g)
+{
+    // cos channels only, stream position k = l - 1; l = 0 only seeds the
+    // recurrence, its field is Gauss's law in the caller
+    R Q1 = 1, Q2 = 0, D1 = 0, D2 = 0;           // Qh_{l-1}, Qh_{l-2} and their D_z
+    R sl = (R)(pt.inv_rd * pt.inv_r2d);         // r^-(2l+1) at l = 1
+    R T = 0, Wr = 0;
+    const CfView<R> v = stage(0, L);
+#pragma unroll 2
+    for (int l = 1; l <= L; ++l) {
+        const R4 e = fq[l];
+        const R gr2 = pt.gam_r2(e.x);
+        const R Qv = pt.rec_q(Q1, Q2, gr2);
+        const R Dz = pt.rec_d(Q1, D1, D2, gr2);
+        const R ac = v.a(l - 1), bc = v.b(l - 1);
+        const R t = fma(sl, ac, bc), u = fma(-sl, ac, bc);
+        T = fma(Qv, t, T);
+        g.z = fma(Dz, t, g.z);
+        Wr = fma(e.y * Qv, u, Wr);
+        Q2 = Q1;
+        Q1 = Qv;
+        D2 = D1;
+        D1 = Dz;
+        sl *= pt.inv_r2;
+    }
+    g.a = fma((R)-0.5, T, g.a + Wr);
+}
+
+// The orders m0 <= m < m1, m0 >= 1, pw at m0.  Where m reaches a slice's end, the sums
+// so far go to tot and a new slice begins: the slices' sums are added
+// in their order whether one wave takes them all or four take one each.
+template <typename R, typename R4, typename Stage>
 __device__ inline void far_orders(Stage &&stage, int L, const R4 *fq, const FarPoint<R> &pt, int m0,
-                                  int m1, FarSums<R> &g)
+                                  int m1, uint32_t ends, FarPower<R> &pw, FarSums<R> &g,
+                                  FarSums<R> &tot)
 {
     int m = m0;
-    if (m == 0) {
-        // cos channels only, stream position k = l - 1; l = 0 only seeds the
-        // recurrence, its field is Gauss's law in the caller
-        R Q1 = 1, Q2 = 0, D1 = 0, D2 = 0;           // Qh_{l-1}, Qh_{l-2} and their D_z
-        R sl = (R)(pt.inv_rd * pt.inv_r2d);         // r^-(2l+1) at l = 1
-        R T = 0, Wr = 0;
-        const CfView<R> v = stage(0, L);
-#pragma unroll 2
-        for (int l = 1; l <= L; ++l) {
-            const R4 e = fq[l];
-            const R gr2 = pt.gam_r2(e.x);
-            const R Qv = pt.rec_q(Q1, Q2, gr2);
-            const R Dz = pt.rec_d(Q1, D1, D2, gr2);
-            const R ac = v.a(l - 1), bc = v.b(l - 1);
-            const R t = fma(sl, ac, bc), u = fma(-sl, ac, bc);
-            T = fma(Qv, t, T);
-            g.z = fma(Dz, t, g.z);
-            Wr = fma(e.y * Qv, u, Wr);
-            Q2 = Q1;
-            Q1 = Qv;
-            D2 = D1;
-            D1 = Dz;
-            sl *= pt.inv_r2;
-        }
-        g.a = fma((R)-0.5, T, g.a + Wr);
-        ++m;
-    }
-    // C_{m-1}, S_{m-1}, r^-(2m-1) of the next order
-    double cd = 1, sd = 0, smm = pt.inv_rd;
-    for (int i = 1; i < m; ++i) {
-        const double c1 = cd, s1 = sd;
-        cd = fma(pt.xd, c1, -(pt.yd * s1));
-        sd = fma(pt.xd, s1, pt.yd * c1);
-        smm *= pt.inv_r2d;
-    }
     int j = m * (L + 1) - (m * (m - 1)) / 2;   // stream index of (m, l = m)
     int k = L + (m - 1) * (2 * L + 2 - m);     // channel position of (m, l = m), cos then sin
     // C_m, S_m and C_{m-1}, S_{m-1} are common to all l of one m: the l
     // loop sums the cos and sin parts separately, combined once per m
     for (; m < m1; ++m) {
-        const R Cm1 = (R)cd, Sm1 = (R)sd;
-        {
-            const double c1 = cd, s1 = sd;
-            cd = fma(pt.xd, c1, -(pt.yd * s1));
-            sd = fma(pt.xd, s1, pt.yd * c1);
+        if (m == (int)(ends & 0xffu)) {
+            tot.add(g);
+            g = FarSums<R>();
+            ends >>= 8;
         }
-        smm *= pt.inv_r2d;
-        const R Cm = (R)cd, Sm = (R)sd;
-        R sl = (R)smm;
+        const R Cm1 = (R)pw.c, Sm1 = (R)pw.s;
+        pw.next(pt);
+        const R Cm = (R)pw.c, Sm = (R)pw.s;
+        R sl = (R)pw.smm;
         // l = m: Qh = 1, D_z Qh = 0
         R Wc, Ws, Tc, Ts, Zc = 0, Zs = 0;
         const CfView<R> v = stage(k, k + 2 * (L - m + 1));
@@ -1900,23 +1916,28 @@ __device__ inline float bpermute(int addr, float v)
 // so their terms vanish without masks.  In FP64 the Legendre sums use the
 // rescaled polynomials of the lg table (a two-operation recurrence; l = 1 is
 // peeled); in FP32 a recurrence on P_l - P_{l-1} driven by 1 - u (lw table).
+// The shifts come in kNearParts parts, each summed by itself and added in FP64
+// in their order, so that a wave each may take them (the field kernel's SPLIT
+// form) with the same result: this adds the parts p0 <= p < p1 to the sums.
+constexpr int kNearParts = kWavesPerBlock;
+
+struct NearSums {
+    double ck = 0.0, bx = 0.0, by = 0.0, bz = 0.0;   // along the own direction; the rest
+    __device__ void add(double c, double x, double y, double z)
+    {
+        ck += c;
+        bx += x;
+        by += y;
+        bz += z;
+    }
+};
+
 template <typename R, typename LG>
 __device__ inline void near_field_full(int lane, int W, int L, const LG *lg, const NearRows<R> &nr,
-                                       R xh, R yh, R zh, R r, R ir, R sk, R rho_t, R qk,
-                                       double &ax, double &ay, double &az)
+                                       R xh, R yh, R zh, R r, R ir, R sk, R rho_t, R qk, int p0,
+                                       int p1, NearSums &sum)
 {
-    double dck = 0.0, dbx = 0.0, dby = 0.0, dbz = 0.0;
     R ck = 0, bx = 0, by = 0, bz = 0;
-    auto flush = [&]() {   // partial sums of a few shifts into FP64 (FP32 mode)
-        dck += (double)ck;
-        dbx += (double)bx;
-        dby += (double)by;
-        dbz += (double)bz;
-        ck = 0;
-        bx = 0;
-        by = 0;
-        bz = 0;
-    };
     const LG c1 = lg[1];
     const int hl = lane & (W - 1), hb = 2 * (lane & W);
     auto shift = [&](const int sft, R qk_s, bool last) {
@@ -1974,38 +1995,38 @@ __device__ inline void near_field_full(int lane, int W, int L, const LG *lg, con
         } else {
             const R rmin = k_outer ? rj : r;   // r_<
             const R rho = rmin * irmx;
-            u = xh * xj + yh * yj + zh * zj;
+            u = fma(zh, zj, fma(yh, yj, xh * xj));
             // l = 1: P_1 = u, P'_1 = 1.  Then two degrees per pass with the
             // registers of Ph_l and Ph_{l-1} (and of P'_l, P'_{l-1}) trading
             // roles
             S1 = rho * u;
             Sl = S1;
             SB = rho;
-            R Pa = u * u - c1.z, Pb = u, dPa = c1.w * u, dPb = 1, rl = rho * rho;
+            R Pa = fma(u, u, -c1.z), Pb = u, dPa = c1.w * u, dPb = 1, rl = rho * rho;
             int l = 2;
             for (; l < L; l += 2) {
                 const LG ca = lg[l], cb = lg[l + 1];
                 R t = rl * Pa;   // degree l from Pa
-                S1 += ca.x * t;
-                Sl += ca.y * t;
-                SB += rl * dPa;
-                Pb = u * Pa - ca.z * Pb;   // Ph_{l+1}
-                dPb += ca.w * Pa;          // P'_{l+1}
+                S1 = fma(ca.x, t, S1);
+                Sl = fma(ca.y, t, Sl);
+                SB = fma(rl, dPa, SB);
+                Pb = fma(u, Pa, -(ca.z * Pb));   // Ph_{l+1}
+                dPb = fma(ca.w, Pa, dPb);        // P'_{l+1}
                 rl *= rho;
                 t = rl * Pb;     // degree l + 1 from Pb
-                S1 += cb.x * t;
-                Sl += cb.y * t;
-                SB += rl * dPb;
-                Pa = u * Pb - cb.z * Pa;   // Ph_{l+2}
-                dPa += cb.w * Pb;          // P'_{l+2}
+                S1 = fma(cb.x, t, S1);
+                Sl = fma(cb.y, t, Sl);
+                SB = fma(rl, dPb, SB);
+                Pa = fma(u, Pb, -(cb.z * Pa));   // Ph_{l+2}
+                dPa = fma(cb.w, Pb, dPa);        // P'_{l+2}
                 rl *= rho;
             }
             if (l == L) {
                 const LG ca = lg[l];
                 const R t = rl * Pa;
-                S1 += ca.x * t;
-                Sl += ca.y * t;
-                SB += rl * dPa;
+                S1 = fma(ca.x, t, S1);
+                Sl = fma(ca.y, t, Sl);
+                SB = fma(rl, dPa, SB);
             }
         }
         const R S_out = -(Sl + S1), S_in = Sl;
@@ -2028,29 +2049,31 @@ __device__ inline void near_field_full(int lane, int W, int L, const LG *lg, con
         by = fma(br, nr.yh[src], by);
         bz = fma(br, nr.zh[src], bz);
     };
-    if constexpr (sizeof(R) == 4) {
-        for (int s0 = 1; s0 < W / 2; s0 += 8) {
+    const int len = W / 2 / kNearParts;
+    for (int part = p0; part < p1; ++part) {
+        const int s1 = (part + 1) * len;
 #pragma unroll 1
-            for (int sft = s0; sft < min(s0 + 8, W / 2); ++sft) shift(sft, qk, false);
-            flush();
-        }
-    } else {
-#pragma unroll 1
-        for (int sft = 1; sft < W / 2; ++sft) shift(sft, qk, false);
+        for (int sft = part * len + 1; sft <= s1 && sft < W / 2; ++sft) shift(sft, qk, false);
+        // the pairs (k, k + W/2) and (k + W/2, k) of a block are one pair: the
+        // block's lanes below W/2 take it
+        if (s1 == W / 2) shift(W / 2, hl >= W / 2 ? (R)0 : qk, true);
+        sum.add((double)ck, (double)bx, (double)by, (double)bz);
+        ck = 0;
+        bx = 0;
+        by = 0;
+        bz = 0;
     }
-    // the pairs (k, k + W/2) and (k + W/2, k) of a block are one pair: the
-    // block's lanes below W/2 take it
-    shift(W / 2, hl >= W / 2 ? (R)0 : qk, true);
-    flush();
-    ax += dck * (double)xh + dbx;
-    ay += dck * (double)yh + dby;
-    az += dck * (double)zh + dbz;
 }
 
 // FP32 (half the LDS rows, fewer registers) runs at six waves per SIMD;
-// NEAR64: FP32 far field with the near field in FP64 (FP32 mode at high l_max)
-template <bool FULL, bool FIELD_ONLY, bool FP32, bool NEAR64>
-__global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 ? 6 : 4) void k_field_push(Map mp, State B, PRec *A, uint8_t *dead,
+// NEAR64: FP32 far field with the near field in FP64 (FP32 mode at high l_max).
+// A block is a group, one tile per wave, or, for launches too small to fill the
+// chip that way (SPLIT, split_max_tiles), one tile: each wave takes a slice of
+// the orders m and a part of the pair shifts for all 64 particles, and the
+// first wave adds the four and pushes.  Both forms add the same slices and
+// parts in the same order: a member's results do not depend on the form.
+template <bool FULL, bool FIELD_ONLY, bool FP32, bool NEAR64, bool SPLIT>
+__global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 && !SPLIT ? 6 : 4) void k_field_push(Map mp, State B, PRec *A, uint8_t *dead,
                                                        Grave G, const double *H,
                                                        const double *CR, const double *qpre,
                                                        Tables tb, KParams kp, double *Eout,
@@ -2083,9 +2106,10 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 ? 6 : 4) void k
     __shared__ typename std::conditional<FULL, WaveLds, Counts>::type lds[kWavesPerBlock];
 
     const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;
-    const uint32_t group = blockIdx.x;
-    const uint32_t tile = uniform_u32(group * kTilesPerGroup + w);
+    const int w = (int)uniform_u32(threadIdx.x >> 6);
+    const uint32_t tile = uniform_u32(SPLIT ? blockIdx.x : blockIdx.x * kTilesPerGroup + w);
+    const uint32_t group = tile / kTilesPerGroup;
+    const int tw = (int)(tile & (kTilesPerGroup - 1));   // the tile in its group
     // the tile's member: n = its alive count, pl = this lane's position in
     // its radial order
     uint32_t mb = kNone, n = 0, lt = 0;
@@ -2145,154 +2169,201 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 ? 6 : 4) void k
     double Ex, Ey, Ez;
     if constexpr (!FULL) {
         double gx, gy, gz;
-        axisym_field(lane, L, tb, inv_nt, Hg + w * kp.HW, CR + (size_t)group * kp.C2, valid ? qk : 0.0,
+        axisym_field(lane, L, tb, inv_nt, Hg + tw * kp.HW, CR + (size_t)group * kp.C2, valid ? qk : 0.0,
                      x, y, z, gx, gy, gz);
         Ex = -gx;
         Ey = -gy;
         Ez = -gz;
     } else {
-    // ---- far field (all particles outside this lane's near-field block) ----
-    {
-        RF gx, gy, gz;
-        const NFF *fq;
-        if constexpr (FP32) fq = tb.fq4_32;
-        else fq = tb.fq4;
-        const double xs = x * inv_rho, ys = y * inv_rho, zs = z * inv_rho;
-        // Coefficients of channel c for half h of this tile: the group's
-        // (carries of the groups before and after it, the image response and
-        // the drive) plus the sums of the group's own particles on each side:
-        //   interior: the tiles before this one, and for h = 1 half 0;
-        //   exterior: the tiles after this one, and for h = 0 half 1;
-        // (the halves' own terms only with a near field per half tile)
-        // as raw sums of Qh times N_lm^2 / ((2l+1) ntilde).  FP32: scaled to
-        // the tile's coordinates x / rho (interior rho^-(l+1), exterior
-        // rho^l) in FP64, then rounded once.  Every pass of every lane reads
-        // them, so they go to LDS (the far field reads them as broadcasts, one
-        // address per half), in windows of kWin channels (interior and
-        // exterior of both halves) that hold whole m blocks; a window moves on
-        // when the next block does not fit (never at l_max <= 16).  An m block
-        // has at most 2 l_max <= 128 channels.
-        constexpr int kWin = (kLdsBytes - kHalfPad) / (int)sizeof(RF) / 4;
-        constexpr int kH1 = 2 * kWin + kHalfPad / (int)sizeof(RF);   // half 1's offset
-        static_assert(kWin >= 2 * kMaxL, "an m block must fit a window");
-        RF *cbuf = reinterpret_cast<RF *>(lds[w].cf);
-        const int C = kp.C;
-        const double *CRg = CR + (size_t)group * kp.C2;
-        // FP32: rho^-(l+1) and rho^l of degree l = lane + 1, fetched per
-        // channel from the lane of its degree
-        double pw_in = 1.0, pw_out = 1.0;
-        if (FP32) {
-            const double lg = log2(rho);
-            pw_in = exp2(-(lane + 2.0) * lg);
-            pw_out = exp2((lane + 1.0) * lg);
-        }
-        int win0 = 0, win_len = -1;   // resident channels [win0, win0 + win_len)
-        // Fills the window with channels [k0, k0 + len), U channels per lane at a
-        // time with all their loads issued before the first use.  The first
-        // window is filled before the far field starts (no other work of the
-        // wave could hide its loads then, and few registers are live: U = 2);
-        // a window moved inside the far field fills two channels at a time at
-        // four waves per SIMD, one at six.
-        auto fill = [&](int k0, int len, auto u_tag) {
-            constexpr int U = decltype(u_tag)::value;
-            const int n_iter = (len + kWave - 1) / kWave;
-            for (int it0 = 0; it0 < n_iter; it0 += U) {
-                double yin[U], yout[U], hin[U], hout[U], ci[U], co[U], gsc[U];
-                int src[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int i = (it0 + u) * kWave + lane;
-                    const int c = k0 + (i < len ? i : 0);
-                    // the interior sums of the group's tiles before this one,
-                    // the exterior sums of those after it, and the halves' own
-                    // sums
-                    const double *Ht = Hg + w * kp.HW;
-                    const double2 hi = reinterpret_cast<const double2 *>(Ht)[2 * c];
-                    const double2 ho = reinterpret_cast<const double2 *>(Ht)[2 * c + 1];
-                    yin[u] = hi.x;
-                    yout[u] = ho.x;
-                    hin[u] = split ? hi.y : 0.0;
-                    hout[u] = split ? ho.y : 0.0;
-                    ci[u] = CRg[c];
-                    co[u] = CRg[C + c];
-                    gsc[u] = tb.chg[c] * inv_nt;
-                    src[u] = FP32 ? 4 * (tb.chl[c] - 1) : 0;
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int i = (it0 + u) * kWave + lane;
-                    double a0 = ci[u] + gsc[u] * yin[u], a1 = ci[u] + gsc[u] * (yin[u] + hin[u]);
-                    double b1 = co[u] + gsc[u] * yout[u], b0 = co[u] + gsc[u] * (yout[u] + hout[u]);
-                    if (FP32) {
-                        // every lane takes part in the fetches
-                        const double si = bpermute(src[u], pw_in), so = bpermute(src[u], pw_out);
-                        a0 *= si;
-                        a1 *= si;
-                        b0 *= so;
-                        b1 *= so;
-                    }
-                    if (i < len) {
-                        cbuf[2 * i] = (RF)a0;
-                        cbuf[2 * i + 1] = (RF)b0;
-                        cbuf[kH1 + 2 * i] = (RF)a1;
-                        cbuf[kH1 + 2 * i + 1] = (RF)b1;
-                    }
-                }
-            }
-            wave_lds_sync();
-            win0 = k0;
-            win_len = len;
-        };
-        fill(0, min(kWin, C), std::integral_constant<int, 2>());
-        auto stage = [&](int k0, int k1) {
-            if (k1 > win0 + win_len) {
-                wave_lds_sync();   // the old window's reads are done
-                // (the FP32 kernel at six waves per SIMD has no registers to spare)
-                fill(k0, min(kWin, C - k0), std::integral_constant<int, FP32 && !NEAR64 ? 1 : 2>());
-            }
-            return CfView<RF>{cbuf + (lane >= kHalf ? kH1 : 0), win0};
-        };
-        const FarPoint<RF> pt(xs, ys, zs);
+        // ---- far field (all particles outside this lane's near-field block) ----
         FarSums<RF> far;
-        far_orders<RF>(stage, L, fq, pt, 0, L + 1, far);
-        far_gradient(pt, far, gx, gy, gz);
-        wave_lds_sync();   // read before the rows below overwrite them
-        Ex = -(double)gx * inv_rho;
-        Ey = -(double)gy * inv_rho;
-        Ez = -(double)gz * inv_rho;
-    }
-
-    // ---- near field (own block); E += -(1 / (4 pi nt)) sum_j q_j grad D ----
-    NearRows<R> &nr = lds[w].rows;
-    {
-        const int e0 = 2 * (lane & NW) + (lane & (NW - 1));   // entries e0, e0 + NW
-        for (int c = 0; c < 2; ++c) {
-            const int i = e0 + c * NW;
-            nr.xh[i] = (R)xh;
-            nr.yh[i] = (R)yh;
-            nr.zh[i] = (R)zh;
-            nr.r[i] = (R)r;
-            nr.ir[i] = (R)inv_r;
-            nr.q[i] = valid ? (R)qk : (R)0;
-            if constexpr (sizeof(R) == 4) nr.s[i] = (R)(r * inv_rho - 1.0);
+        // the field from the far sums (taken at once without SPLIT, so that the
+        // point's factors hold no registers through the near field)
+        auto far_field = [&](const FarPoint<RF> &pt) {
+            RF gx, gy, gz;
+            far_gradient(pt, far, gx, gy, gz);
+            Ex = -(double)gx * inv_rho;
+            Ey = -(double)gy * inv_rho;
+            Ez = -(double)gz * inv_rho;
+        };
+        {
+            const FarPoint<RF> pt(x * inv_rho, y * inv_rho, z * inv_rho);
+            const NFF *fq;
+            if constexpr (FP32) fq = tb.fq4_32;
+            else fq = tb.fq4;
+            // Coefficients of channel c for half h of this tile: the group's
+            // (carries of the groups before and after it, the image response and
+            // the drive) plus the sums of the group's own particles on each side:
+            //   interior: the tiles before this one, and for h = 1 half 0;
+            //   exterior: the tiles after this one, and for h = 0 half 1;
+            // (the halves' own terms only with a near field per half tile)
+            // as raw sums of Qh times N_lm^2 / ((2l+1) ntilde).  FP32: scaled to
+            // the tile's coordinates x / rho (interior rho^-(l+1), exterior
+            // rho^l) in FP64, then rounded once.  Every pass of every lane reads
+            // them, so they go to LDS (the far field reads them as broadcasts, one
+            // address per half), in windows of kWin channels (interior and
+            // exterior of both halves) that hold whole m blocks; a window moves on
+            // when the next block does not fit (never at l_max <= 16).  An m block
+            // has at most 2 l_max <= 128 channels.
+            constexpr int kWin = (kLdsBytes - kHalfPad) / (int)sizeof(RF) / 4;
+            constexpr int kH1 = 2 * kWin + kHalfPad / (int)sizeof(RF);   // half 1's offset
+            static_assert(kWin >= 2 * kMaxL, "an m block must fit a window");
+            RF *cbuf = reinterpret_cast<RF *>(lds[w].cf);
+            const int C = kp.C;
+            const double *CRg = CR + (size_t)group * kp.C2;
+            // FP32: rho^-(l+1) and rho^l of degree l = lane + 1, fetched per
+            // channel from the lane of its degree
+            double pw_in = 1.0, pw_out = 1.0;
+            if (FP32) {
+                const double lg = log2(rho);
+                pw_in = exp2(-(lane + 2.0) * lg);
+                pw_out = exp2((lane + 1.0) * lg);
+            }
+            int win0 = 0, win_len = -1;   // resident channels [win0, win0 + win_len)
+            // Fills the window with channels [k0, k0 + len), U channels per lane at a
+            // time with all their loads issued before the first use.  The first
+            // window is filled before the far field starts (no other work of the
+            // wave could hide its loads then, and few registers are live: U = 2);
+            // a window moved inside the far field fills two channels at a time at
+            // four waves per SIMD, one at six.
+            auto fill = [&](int k0, int len, auto u_tag) {
+                constexpr int U = decltype(u_tag)::value;
+                const int n_iter = (len + kWave - 1) / kWave;
+                for (int it0 = 0; it0 < n_iter; it0 += U) {
+                    double yin[U], yout[U], hin[U], hout[U], ci[U], co[U], gsc[U];
+                    int src[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int i = (it0 + u) * kWave + lane;
+                        const int c = k0 + (i < len ? i : 0);
+                        // the interior sums of the group's tiles before this one,
+                        // the exterior sums of those after it, and the halves' own
+                        // sums
+                        const double *Ht = Hg + tw * kp.HW;
+                        const double2 hi = reinterpret_cast<const double2 *>(Ht)[2 * c];
+                        const double2 ho = reinterpret_cast<const double2 *>(Ht)[2 * c + 1];
+                        yin[u] = hi.x;
+                        yout[u] = ho.x;
+                        hin[u] = split ? hi.y : 0.0;
+                        hout[u] = split ? ho.y : 0.0;
+                        ci[u] = CRg[c];
+                        co[u] = CRg[C + c];
+                        gsc[u] = tb.chg[c] * inv_nt;
+                        src[u] = FP32 ? 4 * (tb.chl[c] - 1) : 0;
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int i = (it0 + u) * kWave + lane;
+                        double a0 = ci[u] + gsc[u] * yin[u], a1 = ci[u] + gsc[u] * (yin[u] + hin[u]);
+                        double b1 = co[u] + gsc[u] * yout[u], b0 = co[u] + gsc[u] * (yout[u] + hout[u]);
+                        if (FP32) {
+                            // every lane takes part in the fetches
+                            const double si = bpermute(src[u], pw_in), so = bpermute(src[u], pw_out);
+                            a0 *= si;
+                            a1 *= si;
+                            b0 *= so;
+                            b1 *= so;
+                        }
+                        if (i < len) {
+                            cbuf[2 * i] = (RF)a0;
+                            cbuf[2 * i + 1] = (RF)b0;
+                            cbuf[kH1 + 2 * i] = (RF)a1;
+                            cbuf[kH1 + 2 * i + 1] = (RF)b1;
+                        }
+                    }
+                }
+                wave_lds_sync();
+                win0 = k0;
+                win_len = len;
+            };
+            // this wave's orders, and their channels [c_begin, c_end)
+            auto slice_end = [&](int sl) { return (int)((kp.f_ends >> (8 * sl)) & 0xffu); };
+            const int m0 = SPLIT && w > 0 ? slice_end(w - 1) : 0;
+            const int m1 = SPLIT ? slice_end(w) : L + 1;
+            auto first_channel = [&](int m) { return m == 0 ? 0 : L + (m - 1) * (2 * L + 2 - m); };
+            const int c_begin = first_channel(m0), c_end = first_channel(m1);
+            fill(c_begin, min(kWin, c_end - c_begin), std::integral_constant<int, 2>());
+            auto stage = [&](int k0, int k1) {
+                if (k1 > win0 + win_len) {
+                    wave_lds_sync();   // the old window's reads are done
+                    // (the FP32 kernel at six waves per SIMD has no registers to spare)
+                    fill(k0, min(kWin, c_end - k0), std::integral_constant<int, FP32 && !NEAR64 ? 1 : 2>());
+                }
+                return CfView<RF>{cbuf + (lane >= kHalf ? kH1 : 0), win0};
+            };
+            FarPower<RF> pw(pt);
+            if constexpr (SPLIT) {
+                for (int m = 1; m < m0; ++m) pw.next(pt);
+                if (m0 == 0 && L > 0) far_order_zero<RF>(stage, L, fq, pt, far);
+                FarSums<RF> unused;
+                far_orders<RF>(stage, L, fq, pt, max(m0, 1), m1, 0u, pw, far, unused);
+            } else {
+                FarSums<RF> part;
+                if (L > 0) far_order_zero<RF>(stage, L, fq, pt, part);
+                far_orders<RF>(stage, L, fq, pt, 1, L + 1, kp.f_ends, pw, part, far);
+                far.add(part);
+                far_field(pt);
+            }
+            wave_lds_sync();   // read before the rows below overwrite them
         }
-    }
-    wave_lds_sync();   // the rows are this wave's own
-    {
-        double ax = 0.0, ay = 0.0, az = 0.0;
+
+        // ---- near field (own block); E += -(1 / (4 pi nt)) sum_j q_j grad D ----
+        NearRows<R> &nr = lds[w].rows;
+        {
+            const int e0 = 2 * (lane & NW) + (lane & (NW - 1));   // entries e0, e0 + NW
+            for (int c = 0; c < 2; ++c) {
+                const int i = e0 + c * NW;
+                nr.xh[i] = (R)xh;
+                nr.yh[i] = (R)yh;
+                nr.zh[i] = (R)zh;
+                nr.r[i] = (R)r;
+                nr.ir[i] = (R)inv_r;
+                nr.q[i] = valid ? (R)qk : (R)0;
+                if constexpr (sizeof(R) == 4) nr.s[i] = (R)(r * inv_rho - 1.0);
+            }
+        }
+        wave_lds_sync();   // the rows are this wave's own
+        NearSums near;
         if (L >= 1) {   // else monopole only: Gauss's law below
             const NF *lg;
             if constexpr (std::is_same<R, float>::value) lg = tb.lw4_32;
             else lg = tb.lg4;
             near_field_full<R, NF>(lane, NW, L, lg, nr, (R)xh, (R)yh, (R)zh, (R)r, (R)inv_r,
-                                   (R)(r * inv_rho - 1.0), (R)rho, valid ? (R)qk : (R)0, ax,
-                                   ay, az);
+                                   (R)(r * inv_rho - 1.0), (R)rho, valid ? (R)qk : (R)0,
+                                   SPLIT ? w : 0, SPLIT ? w + 1 : kNearParts, near);
+        }
+        if constexpr (SPLIT) {
+            // the waves' sums to the first wave
+            constexpr int kSums = 8;
+            static_assert(sizeof(WaveLds) >= kSums * kWave * sizeof(double), "sums exceed the wave's LDS");
+            wave_lds_sync();   // the rows' reads are done
+            double *mine = reinterpret_cast<double *>(&lds[w]) + lane;
+            const double v[kSums] = {(double)far.a, (double)far.z, (double)far.x, (double)far.y,
+                                     near.ck, near.bx, near.by, near.bz};
+#pragma unroll
+            for (int k = 0; k < kSums; ++k) mine[k * kWave] = v[k];
+            __syncthreads();
+            if (w != 0) return;
+            far = FarSums<RF>();
+            near = NearSums();
+#pragma unroll 1
+            for (int ww = 0; ww < kWavesPerBlock; ++ww) {
+                const double *o = reinterpret_cast<const double *>(&lds[ww]) + lane;
+                FarSums<RF> part;
+                part.a = (RF)o[0];
+                part.z = (RF)o[kWave];
+                part.x = (RF)o[2 * kWave];
+                part.y = (RF)o[3 * kWave];
+                far.add(part);
+                near.add(o[4 * kWave], o[5 * kWave], o[6 * kWave], o[7 * kWave]);
+            }
+            wave_lds_sync();
+            far_field(FarPoint<RF>(x * inv_rho, y * inv_rho, z * inv_rho));
         }
         const double cn = -1.0 / (4.0 * kPi * ntilde);
-        Ex += cn * ax;
-        Ey += cn * ay;
-        Ez += cn * az;
-    }
+        Ex = fma(cn, fma(near.ck, (double)xh, near.bx), Ex);
+        Ey = fma(cn, fma(near.ck, (double)yh, near.by), Ey);
+        Ez = fma(cn, fma(near.ck, (double)zh, near.bz), Ez);
     }
 
     // ---- self-image correction: the totals T_lm include the particle's own
@@ -2348,7 +2419,7 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 ? 6 : 4) void k
         const int n_below = __popcll(__ballot(valid) & below);
         const int i_below = __popcll(__ballot(ion) & below);
         // the group's particles before this tile (exact counts)
-        const double in_group = Hg[w * kp.HW + 4 * kp.C];
+        const double in_group = Hg[tw * kp.HW + 4 * kp.C];
         const double before =
             (qpre[group] + in_group) + ((double)i_below + kQ * (double)(n_below - i_below));
         double e;
@@ -2943,10 +3014,46 @@ std::vector<double> build_tables(const sim_params &p, const Layout &lo)
     return t;
 }
 
-// Cuts m = 0..l_max into slices of near-equal work for the moments kernel and
-// returns the blocks per group: a slice per wave of one block, and more blocks
-// per group while the groups alone leave the chip's 256 CUs idle (each slice
-// repeats the particles' loads and powers, so no more than that).
+// Cuts the orders m = 0..top into ns slices [out[s], out[s + 1]) of near-equal
+// work: the (l, m) pairs of an order (m = 0 has half the channels), and about
+// one pair's worth for its start (the walk to a slice's first order, half a
+// pair per step, is left out).
+void cut_orders(int L, int top, int ns, uint8_t *out)
+{
+    auto cost = [&](int m) { return m == 0 ? 0.6 * L + 1.0 : L - m + 2.0; };
+    auto cut = [&](double most, uint8_t *o) {
+        int s = 0;
+        double sum = 0.0;
+        o[0] = 0;
+        for (int m = 0; m <= top; ++m) {
+            if (sum > 0.0 && sum + cost(m) > most) {
+                if (++s >= ns) return false;
+                o[s] = (uint8_t)m;
+                sum = 0.0;
+            }
+            sum += cost(m);
+        }
+        while (s < ns) o[++s] = (uint8_t)(top + 1);
+        return true;
+    };
+    double lo = 0.0, hi = 0.0;   // the smallest largest slice, by bisection
+    for (int m = 0; m <= top; ++m) {
+        lo = std::max(lo, cost(m));
+        hi += cost(m);
+    }
+    uint8_t tmp[kMaxMSlices + 1];
+    for (int it = 0; it < 12; ++it) {
+        const double mid = 0.5 * (lo + hi);
+        if (cut(mid, tmp)) hi = mid;
+        else lo = mid;
+    }
+    cut(hi, out);
+}
+
+// The moments kernel's slices; returns its blocks per group: a slice per wave
+// of one block, and more blocks per group while the groups alone leave the
+// chip's 256 CUs idle (each slice repeats the particles' loads and powers, so
+// no more than that).
 unsigned slice_orders(const Layout &lo, int n_groups, uint8_t *m_slice)
 {
     const int top = lo.full ? lo.L : 0;   // the last order
@@ -2954,40 +3061,18 @@ unsigned slice_orders(const Layout &lo, int n_groups, uint8_t *m_slice)
     while (lo.full && ny * kWavesPerBlock < kMaxMSlices && 2 * ny * kWavesPerBlock <= top &&
            n_groups * ny < 512)
         ny *= 2;
-    const int ns = ny * kWavesPerBlock;
-    // (l, m) pairs of an order, and about one pair's worth for its start (the
-    // walk to a slice's first order, half a pair per step, is left out)
-    auto cost = [&](int m) { return m == 0 ? 0.6 * lo.L + 1.0 : lo.L - m + 2.0; };
-    double lo_c = 0.0, hi_c = 0.0;
-    for (int m = 0; m <= top; ++m) {
-        lo_c = std::max(lo_c, cost(m));
-        hi_c += cost(m);
-    }
-    // the smallest largest slice, by bisection
-    auto cut = [&](double most, uint8_t *out) {
-        int s = 0;
-        double sum = 0.0;
-        out[0] = 0;
-        for (int m = 0; m <= top; ++m) {
-            if (sum > 0.0 && sum + cost(m) > most) {
-                if (++s >= ns) return false;
-                out[s] = (uint8_t)m;
-                sum = 0.0;
-            }
-            sum += cost(m);
-        }
-        while (s < ns) out[++s] = (uint8_t)(top + 1);
-        return true;
-    };
-    uint8_t tmp[kMaxMSlices + 1];
-    for (int it = 0; it < 12; ++it) {
-        const double mid = 0.5 * (lo_c + hi_c);
-        if (cut(mid, tmp)) hi_c = mid;
-        else lo_c = mid;
-    }
-    cut(hi_c, m_slice);
+    cut_orders(lo.L, top, ny * kWavesPerBlock, m_slice);
     return (unsigned)ny;
 }
+
+// Up to this many tiles the field kernel takes a block per tile: a chip's worth
+// of waves hides the latencies that one wave per SIMD cannot, until the
+// repeated setup of four waves per tile costs more.  Field kernel, one form
+// and the other, in us: l_max 16 FP64 10,000 particles 37.6 / 17.0, 131,000 59.8
+// / 42.2, 200,000 69.7 / 60.6, 400,000 113 / 118; l_max 3 30,000 15.7 / 12.7,
+// 65,000 17.8 / 16.8, 131,000 24.4 / 27.9; l_max 8 131,000 32.0 / 32.0; l_max 32
+// FP32 10,000 104 / 35, 400,000 326 / 319.
+int split_max_tiles(int L) { return 600 + 200 * L; }
 
 // The push prepares the next step's sort keys unless told otherwise.
 bool keys_in_push(const sim *h) { return h->lo.tu.keys >= 0; }
@@ -3079,24 +3164,38 @@ int launch_step(sim *h, hipStream_t s, bool field_only, bool with_keys, hipEvent
         k_chunk_apply<<<dim3(ex.n_chunks, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkC, h->T, h->tb,
                                                                kp, h->CR, h->qpre);
     mark(KN_FIELD_PUSH);
-#define MRP_FIELD(FULLV, FO, F32, N64)                                                   \
-    k_field_push<FULLV, FO, F32, N64><<<gT, kBlock, 0, s>>>(mp, h->B, h->A, h->dead, h->G, \
-                                                            h->H, h->CR, h->qpre,          \
-                                                            h->tb, kp, h->Eout, h->Eid,    \
-                                                            h->krec, h->hist)
-#define MRP_FIELD_P(FULLV, FO)                                           \
-    do {                                                                 \
-        if (FULLV && lo.near64) MRP_FIELD(FULLV, FO, true, FULLV);       \
-        else if (lo.fp32) MRP_FIELD(FULLV, FO, true, false);             \
-        else MRP_FIELD(FULLV, FO, false, false);                         \
-    } while (0)
-    if (field_only) {
-        if (lo.full) MRP_FIELD_P(true, true);
-        else MRP_FIELD_P(false, true);
-    } else {
-        if (lo.full) MRP_FIELD_P(true, false);
-        else MRP_FIELD_P(false, false);
-    }
+    const bool split = lo.full && ex.n_tiles <= split_max_tiles(lo.L);
+    uint8_t cuts[kMaxMSlices + 1];
+    cut_orders(lo.L, lo.L, kWavesPerBlock, cuts);
+    kp.f_ends = 0;
+    for (int i = 0; i < kWavesPerBlock; ++i) kp.f_ends |= (uint32_t)cuts[i + 1] << (8 * i);
+    auto field = [&](auto full, auto fo, auto f32, auto n64, auto spl) {
+        constexpr bool kSplit = decltype(spl)::value;
+        k_field_push<decltype(full)::value, decltype(fo)::value, decltype(f32)::value,
+                     decltype(n64)::value, kSplit>
+            <<<kSplit ? (unsigned)ex.n_tiles : gT, kBlock, 0, s>>>(
+                mp, h->B, h->A, h->dead, h->G, h->H, h->CR, h->qpre, h->tb, kp, h->Eout, h->Eid,
+                h->krec, h->hist);
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    auto by_precision = [&](auto fo, auto spl) {
+        if (lo.near64) field(yes, fo, yes, yes, spl);
+        else if (lo.fp32) field(yes, fo, yes, no, spl);
+        else field(yes, fo, no, no, spl);
+    };
+    auto by_form = [&](auto fo) {
+        if (!lo.full) {
+            if (lo.fp32) field(no, fo, yes, no, no);
+            else field(no, fo, no, no, no);
+        } else if (split) {
+            by_precision(fo, yes);
+        } else {
+            by_precision(fo, no);
+        }
+    };
+    if (field_only) by_form(yes);
+    else by_form(no);
     mark(KN_STEP_FINISH);   // part of the next step's bucket offsets
     if (ev) (void)hipEventRecord(ev[KN_COUNT], s);
     hipError_t le = hipGetLastError();

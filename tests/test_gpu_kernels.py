@@ -114,3 +114,33 @@ def test_one_kernel_carries_match_chunked(n, L, mode):
     assert _err(E0, E1) <= 1e-13
     assert np.max(np.abs(q0 - q1)) <= 1e-13 * max(np.max(np.abs(q1)), 1e-300)
     assert np.max(np.abs(p0 - p1)) <= 1e-13
+
+
+# A small member steps in the one-tile-per-block form of the field kernel when
+# alone and in the one-tile-per-wave form beside a member of many tiles: the
+# same bits (FP64, FP32, FP32 with the near field in FP64; half and whole
+# tiles).  The sort, moments and carries differ in form too.
+@pytest.mark.parametrize("L,precision,split", [(16, S.SIM_FP64, 0), (5, S.SIM_FP64, -1),
+                                               (4, S.SIM_FP32_COMP, 0), (9, S.SIM_FP32_COMP, -1),
+                                               (21, S.SIM_FP32_COMP, 0), (0, S.SIM_FP64, 0)])
+def test_field_forms_agree_bitwise(L, precision, split):
+    print(f"[gpu] field forms L={L} p={precision} split={split}", file=sys.stderr, flush=True)
+    common = S.SimParams(l_max=L, precision=precision, near_split=split)
+
+    def member(n, seed):
+        st = W.uniform_shell(n, seed, 5.0, 0.2)
+        return S.Member(pos=st.pos, vel=st.vel, u_asy=np.array([0.3, 0.1, 0.0]),
+                        ntilde=W.ntilde_for(n, 5.0), q_surface0=-2.0)
+
+    small = member(577, 21)
+    out = []
+    for others in ([], [member(1_100_000 if L < 9 else 140_000, 22)]):
+        with S.Batch(common, [small] + others) as b:
+            E = b.eval_field(0)
+            b.step(3)
+            out.append((E, b.read_response(0, 0, 3), b.read_state(0)))
+    (E0, q0, s0), (E1, q1, s1) = out
+    np.testing.assert_array_equal(E0, E1)
+    np.testing.assert_array_equal(q0, q1)
+    for k in ("pos", "vel", "alive"):
+        np.testing.assert_array_equal(s0[k], s1[k])
