@@ -162,7 +162,6 @@ struct Tables {
     const double4 *fq4;
     const double *chn;
     // FP32 copies of the field kernel's tables for the FP32-compensated mode
-    const float4 *lg4_32;
     const float4 *fq4_32;
     // FP32 near field's Legendre recurrence on D_l = P_l - P_{l-1}, per l:
     // {l / (l+1), -(2l+1) / (l+1), 2l+1, l+1}
@@ -233,8 +232,6 @@ __device__ inline bool member_runs(const Seg &sg, const Ctl &c, const KParams &k
 {
     return sg.used && (kp.field_only || c.step < sg.n_steps);
 }
-
-__host__ __device__ inline int tri(int l, int m) { return l * (l + 1) / 2 + m; }
 
 __device__ inline uint32_t uniform_u32(uint32_t v)
 {
@@ -2439,11 +2436,12 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 && !SPLIT ? 6 :
     }
 
     if (FIELD_ONLY) {
-        if (valid) {
-            Eout[3 * (size_t)p + 0] = Ex;
-            Eout[3 * (size_t)p + 1] = Ey;
-            Eout[3 * (size_t)p + 2] = Ez;
-            Eid[p] = uid;
+        if (valid) {   // by sorted position, or by id where no ids are asked for
+            const size_t at = Eid ? (size_t)p : (size_t)uid;
+            Eout[3 * at + 0] = Ex;
+            Eout[3 * at + 1] = Ey;
+            Eout[3 * at + 2] = Ez;
+            if (Eid) Eid[p] = uid;
         }
         return;
     }
@@ -2543,6 +2541,154 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 && !SPLIT ? 6 :
         G.vz[slot] = vz;
         G.uid[slot] = uid;
     }
+}
+
+// ---------------------------------------------------------------------------
+// Constant tables, filled on the device (no copies: an evaluation without a
+// handle fills them on each call)
+// ---------------------------------------------------------------------------
+
+// Layout of the FP64 table block: room for nine per-l arrays (ftil, wl,
+// drive_w, self_w in use) and two (l, m) triangles, then at 32-byte aligned
+// offsets the near-field constants (nf4, lg4) and the rescaled recurrence
+// (fq4) with its zero entry.
+__host__ __device__ inline size_t nf4_offset(int L)
+{
+    const size_t base = (size_t)9 * (L + 1) + 2 * (size_t)((L + 1) * (L + 2) / 2);
+    return (base + 3) & ~size_t(3);
+}
+__host__ __device__ inline size_t lg4_offset(int L) { return nf4_offset(L) + 4 * (size_t)(L + 1); }
+__host__ __device__ inline size_t fq4_offset(int L) { return lg4_offset(L) + 4 * (size_t)(L + 1); }
+// one zero entry after the fq4 triangle: the moments kernel reads one ahead
+size_t tables_len(int L) { return fq4_offset(L) + 4 * (size_t)((L + 1) * (L + 2) / 2 + 1); }
+
+// FP32 tables of the field kernel, each at a 16-byte aligned offset: the
+// far-field recurrence and the full near field's Legendre constants, after
+// room for two more per-l tables.
+__host__ __device__ inline size_t fq4_32_offset(int L) { return 8 * (size_t)(L + 1); }
+__host__ __device__ inline size_t lw4_32_offset(int L)
+{
+    return fq4_32_offset(L) + 4 * (size_t)((L + 1) * (L + 2) / 2);
+}
+size_t tables32_len(int L) { return lw4_32_offset(L) + 4 * (size_t)(L + 1); }
+
+struct TableDst {
+    double *tab;
+    float *tab32;
+    int *chl;
+    double *chn, *chg;
+    double d, eps_r;
+    int L, C;
+};
+
+// The entries i0, i0 + stride, ... of every table.  f_l and b^P_l are the
+// closed forms of App. A and Sec. 3 (R = 1, R_E = 1 - d); c_l, the Legendre
+// coefficients of the electrode data 1/2 sgn(cos th), are taken as
+// (P_{l-1}(0) - P_{l+1}(0)) / 2.  Every entry comes from products of its own,
+// so the threads share nothing; no contraction, so that the tables of two
+// kernels are the same bits.
+__device__ inline void fill_tables(const TableDst &t, int i0, int stride)
+{
+#pragma clang fp contract(off)
+    const int L = t.L, n = L + 1, tri_n = (L + 1) * (L + 2) / 2;
+    double *ftil = t.tab, *wl = ftil + n, *drive = wl + n, *selfw = drive + n;
+    double *nf4 = t.tab + nf4_offset(L), *lg4 = t.tab + lg4_offset(L), *fq4 = t.tab + fq4_offset(L);
+    float *fq32 = t.tab32 + fq4_32_offset(L), *lw32 = t.tab32 + lw4_32_offset(L);
+    for (int l = i0; l <= L; l += stride) {
+        const double eps = t.eps_r, dl = (double)l;
+        double al = 1.0, base = 1.0 - t.d;   // a^l by squaring
+        for (int e = l; e > 0; e >>= 1) {
+            if (e & 1) al *= base;
+            base *= base;
+        }
+        const double a = 1.0 - t.d, a2l1 = al * al * a;
+        const double f = (dl * (eps - 1.0) + (dl + eps + dl * eps) * a2l1) /
+                         ((dl + 1.0 + dl * eps) + (dl + 1.0) * (eps - 1.0) * a2l1);
+        const double bP = (2.0 * dl + 1.0) * eps * (al * a) /
+                          ((dl + 1.0) * (eps - 1.0) * a2l1 + dl * eps + dl + 1.0);
+        double c = 0.0;
+        if (l & 1) {
+            double p0 = 1.0;   // P_{l-1}(0); P_{l+1}(0) = -l / (l+1) P_{l-1}(0)
+            for (int k = 1; k < l - 1; k += 2) p0 = -(double)k / (k + 1.0) * p0;
+            c = 0.5 * (p0 - -dl / (dl + 1.0) * p0);
+        }
+        ftil[l] = l == 0 ? 0.0 : f;
+        wl[l] = 1.0 / (2.0 * dl + 1.0);
+        drive[l] = c * bP * sqrt(4.0 * kPi / (2.0 * dl + 1.0));
+        selfw[l] = l == 0 ? 0.0 : f / (4.0 * kPi);
+        nf4[4 * l + 0] = (2.0 * dl + 1.0) / (dl + 1.0);
+        nf4[4 * l + 1] = dl / (dl + 1.0);
+        nf4[4 * l + 2] = 2.0 * dl + 1.0;
+        nf4[4 * l + 3] = dl;
+        // P_l = c_l Ph_l with c_0 = 1, c_l = c_{l-1} (2l-1)/l: the three-term
+        // recurrence l P_l = (2l-1) u P_{l-1} - (l-1) P_{l-2} becomes
+        // Ph_l = u Ph_{l-1} - gamma_l Ph_{l-2}, gamma_l = (l-1)^2 / ((2l-1)(2l-3));
+        // P'_{l+1} = P'_{l-1} + (2l+1) c_l Ph_l
+        double cl = 1.0;
+        for (int k = 1; k <= l; ++k) cl *= (2.0 * k - 1.0) / k;
+        lg4[4 * l + 0] = cl;
+        lg4[4 * l + 1] = dl * cl;
+        lg4[4 * l + 2] = dl * dl / ((2.0 * dl + 1.0) * (2.0 * dl - 1.0));
+        lg4[4 * l + 3] = (2.0 * dl + 1.0) * cl;
+        lw32[4 * l + 0] = (float)(1.0 / (dl + 1.0));
+        lw32[4 * l + 1] = 0.0f;
+        lw32[4 * l + 2] = (float)(2.0 * dl + 1.0);
+        lw32[4 * l + 3] = (float)(dl + 1.0);
+    }
+    // (l, m) in stream order: Q_l^m = N_lm Qh_l^m, with N_lm^2 = (2 - [m = 0]) /
+    // (4 pi) prod_{k <= m} (2k+1)/(2k) prod_{m < k <= l} (4k^2-1)/(k^2-m^2) and
+    // gamma_lm = ((l-1)^2 - m^2) / ((2l-1)(2l-3))
+    for (int i = i0; i <= tri_n; i += stride) {
+        int m = 0, j = i;
+        while (m < L && j >= n - m) {
+            j -= n - m;
+            ++m;
+        }
+        const int l = m + j;
+        double gamma = 0.0, half = 0.0;
+        if (i < tri_n) {
+            half = (double)l + 0.5;
+            if (l >= m + 2)
+                gamma = (double)((l - 1) * (l - 1) - m * m) / ((2.0 * l - 1.0) * (2.0 * l - 3.0));
+            fq32[4 * i] = (float)gamma;
+            fq32[4 * i + 1] = (float)half;
+            fq32[4 * i + 2] = 0.0f;
+            fq32[4 * i + 3] = 0.0f;
+        }
+        fq4[4 * i] = gamma;
+        fq4[4 * i + 1] = half;
+        fq4[4 * i + 2] = 0.0;
+        fq4[4 * i + 3] = 0.0;
+        // the channels of this (l, m): cos, and sin for m > 0
+        if (i == tri_n || l == 0) continue;
+        const int ch = m == 0 ? l - 1 : L + (m - 1) * (2 * L + 2 - m) + 2 * (l - m);
+        if (ch >= t.C) continue;   // axisymmetric: m = 0 only
+        double num = m > 0 ? 2.0 : 1.0, den = 4.0 * kPi;
+        for (int k = 1; k <= m; ++k) {
+            num *= 2.0 * k + 1.0;
+            den *= 2.0 * k;
+        }
+        for (int k = m + 1; k <= l; ++k) {
+            num *= (double)(4 * k * k - 1);
+            den *= (double)(k * k - m * m);
+        }
+        const double n2 = num / den;
+        for (int q = 0; q < (m > 0 ? 2 : 1); ++q) {
+            t.chl[ch + q] = l;
+            t.chn[ch + q] = sqrt(n2);
+            t.chg[ch + q] = n2 / (2.0 * l + 1.0);   // a raw sum of Qh to a coefficient
+        }
+    }
+    if (i0 == 0 && t.C == 0) {
+        t.chl[0] = 0;
+        t.chn[0] = 0.0;
+        t.chg[0] = 0.0;
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_tables(TableDst t)
+{
+    fill_tables(t, (int)(blockIdx.x * kBlock + threadIdx.x), (int)(gridDim.x * kBlock));
 }
 
 // ---------------------------------------------------------------------------
@@ -2863,39 +3009,6 @@ namespace {
         }                                                                             \
     } while (0)
 
-// Layout of the table block: 9 per-l arrays (ftil, wl, drive_w, self_w, nfA,
-// nfB, lval, tl1, qmm, in this order), the two (l, m) triangles a_lm, b_lm
-// (host side: N_lm and gamma_lm come from them), then at 32-byte aligned
-// offsets the near-field constants (nf4, lg4) and the rescaled recurrence
-// (fq4) with its zero entry.
-constexpr int kQmmArray = 8;   // index of qmm among the per-l arrays
-
-size_t nf4_offset(int L)
-{
-    const size_t base = (size_t)9 * (L + 1) + 2 * (size_t)((L + 1) * (L + 2) / 2);
-    return (base + 3) & ~size_t(3);
-}
-
-size_t lg4_offset(int L) { return nf4_offset(L) + 4 * (size_t)(L + 1); }   // 32-byte aligned
-
-size_t fq4_offset(int L) { return lg4_offset(L) + 4 * (size_t)(L + 1); }
-
-// one zero entry after the fq4 triangle: the moments kernel reads one ahead
-size_t tables_len(int L) { return fq4_offset(L) + 4 * (size_t)((L + 1) * (L + 2) / 2 + 1); }
-
-// FP32 copies of the field kernel's tables, each at a 16-byte aligned offset:
-// the axisymmetric near-field constants, the full near-field Legendre
-// constants, the far-field recurrence.
-size_t nf4_32_offset(int) { return 0; }
-
-size_t lg4_32_offset(int L) { return nf4_32_offset(L) + 4 * (size_t)(L + 1); }
-
-size_t fq4_32_offset(int L) { return lg4_32_offset(L) + 4 * (size_t)(L + 1); }
-
-size_t lw4_32_offset(int L) { return fq4_32_offset(L) + 4 * (size_t)((L + 1) * (L + 2) / 2); }
-
-size_t tables32_len(int L) { return lw4_32_offset(L) + 4 * (size_t)(L + 1); }
-
 void plan_alloc(sim *h, Alloc &al, size_t pool_bytes)
 {
     const Layout &lo = h->lo;
@@ -2932,86 +3045,6 @@ void plan_alloc(sim *h, Alloc &al, size_t pool_bytes)
     al.add(&h->tile_member, (size_t)lo.n_tiles);
     al.add(&h->chunk_member, (size_t)lo.n_chunks);
     al.add(&h->mdata, std::max<size_t>(pool_bytes, kPoolUnit));
-}
-
-// Host-side coefficient tables.  f_l and b^P_l are the closed forms of App. A
-// and Sec. 3 (R = 1, R_E = a); c_l, the Legendre coefficients of the
-// electrode data 1/2 sgn(cos th), are taken as (P_{l-1}(0) - P_{l+1}(0))/2.
-std::vector<double> build_tables(const sim_params &p, const Layout &lo)
-{
-    const int L = lo.L;
-    const double a = 1.0 - p.d, eps = p.eps_r;
-    std::vector<double> t(tables_len(L), 0.0);
-    double *ftil = t.data(), *wl = ftil + (L + 1), *drive = wl + (L + 1), *selfw = drive + (L + 1),
-           *nfA = selfw + (L + 1), *nfB = nfA + (L + 1), *lval = nfB + (L + 1), *tl1 = lval + (L + 1),
-           *qmm = tl1 + (L + 1), *alm = qmm + (L + 1),
-           *blm = alm + (L + 1) * (L + 2) / 2, *nf4 = t.data() + nf4_offset(L);
-    // Legendre values at 0 up to L + 1
-    std::vector<double> p0(L + 3, 0.0);
-    p0[0] = 1.0;
-    if (L + 2 >= 1) p0[1] = 0.0;
-    for (int l = 1; l + 1 <= L + 2; ++l) p0[l + 1] = -(double)l / (l + 1.0) * p0[l - 1];
-    for (int l = 0; l <= L; ++l) {
-        const double a2l1 = std::pow(a, 2.0 * l + 1.0);
-        const double f = (l * (eps - 1.0) + (l + eps + l * eps) * a2l1) /
-                         ((l + 1.0 + l * eps) + (l + 1.0) * (eps - 1.0) * a2l1);
-        const double bP = (2.0 * l + 1.0) * eps * std::pow(a, l + 1.0) /
-                          ((l + 1.0) * (eps - 1.0) * a2l1 + l * eps + l + 1.0);
-        const double c = (l % 2 == 1) ? 0.5 * (p0[l - 1] - p0[l + 1]) : 0.0;
-        ftil[l] = (l == 0) ? 0.0 : f;
-        wl[l] = 1.0 / (2.0 * l + 1.0);
-        drive[l] = c * bP * std::sqrt(4.0 * kPi / (2.0 * l + 1.0));
-        selfw[l] = (l == 0) ? 0.0 : f / (4.0 * kPi);
-        nfA[l] = (2.0 * l + 1.0) / (l + 1.0);
-        nfB[l] = (double)l / (l + 1.0);
-        lval[l] = (double)l;
-        tl1[l] = 2.0 * l + 1.0;
-        nf4[4 * l + 0] = nfA[l];
-        nf4[4 * l + 1] = nfB[l];
-        nf4[4 * l + 2] = tl1[l];
-        nf4[4 * l + 3] = lval[l];
-    }
-    // Q_m^m = sqrt((2m+1)/(4 pi) / (2m)!) (2m-1)!! (sqrt 2 for m > 0)
-    qmm[0] = 1.0 / std::sqrt(4.0 * kPi);
-    for (int m = 1; m <= L; ++m) {
-        double v = qmm[m - 1] * std::sqrt((2.0 * m + 1.0) / (2.0 * m));
-        if (m == 1) v *= std::sqrt(2.0);
-        qmm[m] = v;
-    }
-    for (int m = 0; m <= L; ++m) {
-        for (int l = m + 1; l <= L; ++l) {
-            const double l2 = (double)l * l, m2 = (double)m * m;
-            alm[tri(l, m)] = std::sqrt((4.0 * l2 - 1.0) / (l2 - m2));
-            blm[tri(l, m)] = (l >= m + 2)
-                ? std::sqrt(((l - 1.0) * (l - 1.0) - m2) * (2.0 * l + 1.0) / ((l2 - m2) * (2.0 * l - 3.0)))
-                : 0.0;
-        }
-    }
-    // P_l = c_l Ph_l with c_0 = 1, c_l = c_{l-1} (2l-1)/l: the three-term
-    // recurrence l P_l = (2l-1) u P_{l-1} - (l-1) P_{l-2} becomes
-    // Ph_l = u Ph_{l-1} - gamma_l Ph_{l-2}, gamma_l = (l-1)^2 / ((2l-1)(2l-3));
-    // P'_{l+1} = P'_{l-1} + (2l+1) c_l Ph_l
-    double *lg = t.data() + lg4_offset(L);
-    for (int l = 0; l <= L; ++l) {
-        double c = 1.0;
-        for (int k = 1; k <= l; ++k) c *= (2.0 * k - 1.0) / k;
-        lg[4 * l + 0] = c;
-        lg[4 * l + 1] = l * c;
-        lg[4 * l + 2] = (double)l * l / ((2.0 * l + 1.0) * (2.0 * l - 1.0));
-        lg[4 * l + 3] = (2.0 * l + 1.0) * c;
-    }
-    // rescaled far-field recurrence: Q_l^m = N_lm Qh_l^m with N_mm = Q_m^m and
-    // N_lm = a_lm N_{l-1,m}, so gamma_lm = b_lm / (a_lm a_{l-1,m})
-    double *fq = t.data() + fq4_offset(L);
-    for (int m = 0, j = 0; m <= L; ++m) {
-        for (int l = m; l <= L; ++l, ++j) {
-            fq[4 * j] = (l >= m + 2) ? blm[tri(l, m)] / (alm[tri(l, m)] * alm[tri(l - 1, m)]) : 0.0;
-            fq[4 * j + 1] = (double)l + 0.5;
-            fq[4 * j + 2] = 0.0;
-            fq[4 * j + 3] = 0.0;
-        }
-    }
-    return t;
 }
 
 // Cuts the orders m = 0..top into ns slices [out[s], out[s + 1]) of near-equal
@@ -3268,70 +3301,9 @@ int check_member_index(sim *h, int32_t index)
     return SIM_OK;
 }
 
-// The host-side constant tables of a layout: the FP64 block of
-// build_tables, its FP32 copies, and the degree and normalisation of each
-// channel in stream order.
-struct HostTables {
-    std::vector<double> tab;
-    std::vector<float> tab32;
-    std::vector<int> chl;
-    std::vector<double> chn, chg;
-};
-
-int make_host_tables(const sim_params &p, const Layout &lo, HostTables *ht)
+TableDst table_dst(const sim *h, const sim_params &p)
 {
-    const int L = lo.L;
-    ht->tab = build_tables(p, lo);
-    const std::vector<double> &tab = ht->tab;
-    std::vector<float> &tab32 = ht->tab32;
-    tab32.assign(tables32_len(L), 0.f);
-    {
-        const size_t ntri = (size_t)(L + 1) * (L + 2) / 2;
-        const double *nf4 = tab.data() + nf4_offset(L);
-        for (int i = 0; i < 4 * (L + 1); ++i) tab32[nf4_32_offset(L) + i] = (float)nf4[i];
-        const double *lg = tab.data() + lg4_offset(L);
-        for (int i = 0; i < 4 * (L + 1); ++i) tab32[lg4_32_offset(L) + i] = (float)lg[i];
-        const double *fq = tab.data() + fq4_offset(L);
-        for (size_t i = 0; i < 4 * ntri; ++i) tab32[fq4_32_offset(L) + i] = (float)fq[i];
-        float *lw = tab32.data() + lw4_32_offset(L);
-        for (int l = 0; l <= L; ++l) {
-            lw[4 * l + 0] = (float)(1.0 / (l + 1.0));
-            lw[4 * l + 1] = 0.0f;
-            lw[4 * l + 2] = (float)(2.0 * l + 1.0);
-            lw[4 * l + 3] = (float)(l + 1.0);
-        }
-    }
-    // degree of each channel in stream order (m outer, l = max(m,1)..L inner)
-    // and its far-field normalisation N_lm
-    std::vector<int> &chl = ht->chl;
-    std::vector<double> &chn = ht->chn;
-    chl.clear();
-    chn.clear();
-    {
-        const double *qmm = tab.data() + kQmmArray * (L + 1);
-        const double *alm = qmm + (L + 1);
-        for (int m = 0; m <= (lo.full ? L : 0); ++m) {
-            double nlm = qmm[m];   // N_mm
-            for (int l = m; l <= L; ++l) {
-                if (l > m) nlm *= alm[tri(l, m)];
-                if (l == 0) continue;
-                for (int sc = 0; sc < (m > 0 ? 2 : 1); ++sc) {
-                    chl.push_back(l);
-                    chn.push_back(nlm);
-                }
-            }
-        }
-    }
-    if ((int)chl.size() != lo.C) return fail(SIM_EDEVICE, "channel count mismatch");
-    // N_lm^2 / (2l+1): a raw sum of Qh to a field coefficient (times 1 / ntilde)
-    ht->chg.resize(chl.size());
-    for (size_t c = 0; c < chl.size(); ++c) ht->chg[c] = chn[c] * chn[c] / (2.0 * chl[c] + 1.0);
-    if (chl.empty()) {
-        chl.push_back(0);
-        chn.push_back(0.0);
-        ht->chg.push_back(0.0);
-    }
-    return SIM_OK;
+    return TableDst{h->tables, h->tables32, h->chl, h->chn, h->chg, p.d, p.eps_r, h->lo.L, h->lo.C};
 }
 
 // Point the kernels' table, parameter and map views at the handle's carved
@@ -3351,7 +3323,6 @@ void bind_device_tables(sim *h)
     h->tb.chn = h->chn;
     h->tb.chl = h->chl;
     h->tb.chg = h->chg;
-    h->tb.lg4_32 = reinterpret_cast<const float4 *>(h->tables32 + lg4_32_offset(L));
     h->tb.fq4_32 = reinterpret_cast<const float4 *>(h->tables32 + fq4_32_offset(L));
     h->tb.lw4_32 = reinterpret_cast<const float4 *>(h->tables32 + lw4_32_offset(L));
     KParams &kp = h->kp;
@@ -3434,8 +3405,6 @@ int engine_init(sim *h, const sim_params *p, const Layout &lo, void *hip_stream,
     if (hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) != hipSuccess)
         return fail(SIM_EDEVICE, "hipStreamCreate failed");
 
-    HostTables ht;
-    if (int rc = make_host_tables(*p, lo, &ht)) return rc;
     bind_device_tables(h);
     h->groups.reset((uint32_t)lo.n_groups);
     h->chunks.reset((uint32_t)lo.n_chunks);
@@ -3445,12 +3414,8 @@ int engine_init(sim *h, const sim_params *p, const Layout &lo, void *hip_stream,
     std::vector<Seg> segs((size_t)lo.n_members);   // used = 0
     std::vector<Ctl> ctls((size_t)lo.n_members);
     std::vector<uint32_t> none_t((size_t)lo.n_tiles, kNone), none_c((size_t)lo.n_chunks, kNone);
-    if (hipMemcpy(h->tables, ht.tab.data(), sizeof(double) * ht.tab.size(), hipMemcpyHostToDevice) ||
-        hipMemcpy(h->chl, ht.chl.data(), sizeof(int) * ht.chl.size(), hipMemcpyHostToDevice) ||
-        hipMemcpy(h->chn, ht.chn.data(), sizeof(double) * ht.chn.size(), hipMemcpyHostToDevice) ||
-        hipMemcpy(h->chg, ht.chg.data(), sizeof(double) * ht.chg.size(), hipMemcpyHostToDevice) ||
-        hipMemcpy(h->tables32, ht.tab32.data(), sizeof(float) * ht.tab32.size(),
-                  hipMemcpyHostToDevice) ||
+    k_tables<<<8, kBlock, 0, h->stream>>>(table_dst(h, *p));
+    if (hipGetLastError() != hipSuccess ||
         hipMemcpy(h->seg, segs.data(), sizeof(Seg) * segs.size(), hipMemcpyHostToDevice) ||
         hipMemcpy(h->ctl, ctls.data(), sizeof(Ctl) * ctls.size(), hipMemcpyHostToDevice) ||
         hipMemcpy(h->tile_member, none_t.data(), 4 * none_t.size(), hipMemcpyHostToDevice) ||
@@ -3807,16 +3772,18 @@ int scratch_address(void **out)
 
 // The tables and control words a one-member handle would hold before its
 // first step, written by a kernel (the buffer keeps the previous call's
-// contents): the member's description, its control block, the tile and
-// chunk maps, the absorbed flags and the bucket histogram cleared, and the
+// contents): the constant tables, the member's description, its control
+// block, the tile and chunk maps and the bucket histogram cleared, and the
 // drive value of the evaluated step.
-__global__ void k_static_setup(Seg sg, Ctl ct, Seg *seg, Ctl *ctl, uint32_t *tile_member,
-                               uint32_t *chunk_member, uint8_t *dead, uint32_t *hist,
-                               double *u_dev, double u_asy, int n_tiles, int n_chunks, int nb)
+__global__ __launch_bounds__(kBlock) void k_static_setup(TableDst t, Seg sg, Ctl ct, Seg *seg,
+                                                         Ctl *ctl, uint32_t *tile_member,
+                                                         uint32_t *chunk_member, uint32_t *hist,
+                                                         double *u_dev, double u_asy, int n_tiles,
+                                                         int n_chunks, int nb)
 {
     const int stride = gridDim.x * blockDim.x;
     const int i0 = blockIdx.x * blockDim.x + threadIdx.x;
-    for (int i = i0; i < n_tiles * kWave; i += stride) dead[i] = 0;
+    fill_tables(t, i0, stride);
     for (int i = i0; i < n_tiles; i += stride) tile_member[i] = 0;
     for (int i = i0; i < n_chunks; i += stride) chunk_member[i] = 0;
     for (int i = i0; i <= nb; i += stride) hist[i] = 0;
@@ -3827,30 +3794,31 @@ __global__ void k_static_setup(Seg sg, Ctl ct, Seg *seg, Ctl *ctl, uint32_t *til
     }
 }
 
-// Particle records from positions [3n] (particle-major), id = index.
-__global__ void k_static_pack(const double *pos, uint32_t n, PRec *A)
+// Particle records and sort keys from positions [3n] (particle-major), id = index.
+__global__ __launch_bounds__(kBlock) void k_static_pack(const double *pos, uint32_t n, PRec *A,
+                                                        KeyRec *krec, uint32_t *hist,
+                                                        double inv_vol, uint32_t nb)
 {
+    __shared__ uint32_t cnt[kWavesPerBlock][kSlotWindow];
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    const bool on = i < n;
     PRec r;
-    r.x = pos[3 * (size_t)i];
-    r.y = pos[3 * (size_t)i + 1];
-    r.z = pos[3 * (size_t)i + 2];
-    r.vx = r.vy = r.vz = 0.0;
-    r.uid = i;
-    r.pad[0] = r.pad[1] = r.pad[2] = 0u;
-    A[i] = r;
-}
-
-// The field at sorted position p back to the particle's index (its id).
-__global__ void k_static_unpack(const double *Eout, const uint32_t *Eid, uint32_t n, double *E)
-{
-    const uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    const size_t k = Eid[p];
-    E[3 * k] = Eout[3 * (size_t)p];
-    E[3 * k + 1] = Eout[3 * (size_t)p + 1];
-    E[3 * k + 2] = Eout[3 * (size_t)p + 2];
+    KeyRec k{0ull, i, kNone};
+    uint32_t b = 0;
+    if (on) {
+        r.x = pos[3 * (size_t)i];
+        r.y = pos[3 * (size_t)i + 1];
+        r.z = pos[3 * (size_t)i + 2];
+        r.vx = r.vy = r.vz = 0.0;
+        r.uid = i;
+        r.pad[0] = r.pad[1] = r.pad[2] = 0u;
+        A[i] = r;
+        const double r2 = key_r2(r.x, r.y, r.z);
+        k.key = (uint64_t)__double_as_longlong(r2);
+        b = bucket_of(r2, inv_vol, 0, nb);
+    }
+    k.sub = take_slot(threadIdx.x & 63, on, b, hist, cnt[threadIdx.x >> 6]);
+    if (on) krec[i] = k;
 }
 
 }  // namespace
@@ -4265,8 +4233,6 @@ int sim_eval_field_static(const sim_params *p, int64_t n, const double *pos, dou
     void *base = nullptr;
     if (int rc = scratch_address(&base)) return rc;
     carve(al, base);
-    HostTables ht;
-    if (int rc = make_host_tables(*p, h.lo, &ht)) return rc;
     bind_device_tables(&h);
     h.ext.n_tiles = (int)sh.nt;
     h.ext.n_chunks = (int)sh.nc;
@@ -4308,27 +4274,17 @@ int sim_eval_field_static(const sim_params *p, int64_t n, const double *pos, dou
     ct.n_live = (uint32_t)n;
     ct.q_surface = q_surface;
     hipStream_t s = (hipStream_t)hip_stream;
-    const unsigned gSet = (unsigned)std::min<int64_t>(((int64_t)sh.nt * kWave + kBlock - 1) / kBlock, 4096);
+    // enough threads for the tables (153 entries at l_max 16, 2146 at 64) and the histogram
+    const unsigned gSet = 16;
     const unsigned gN = (unsigned)((n + kBlock - 1) / kBlock);
-    k_static_setup<<<gSet, kBlock, 0, s>>>(sg, ct, h.seg, h.ctl, h.tile_member, h.chunk_member,
-                                           h.dead, h.hist, const_cast<double *>(sg.u_asy), u_asy,
-                                           (int)sh.nt, (int)sh.nc, h.lo.nb);
-    k_static_pack<<<gN, kBlock, 0, s>>>(pos, (uint32_t)n, h.A);
-    HIP_TRY(hipMemcpyAsync(h.tables, ht.tab.data(), sizeof(double) * ht.tab.size(),
-                           hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(h.chl, ht.chl.data(), sizeof(int) * ht.chl.size(),
-                           hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(h.chn, ht.chn.data(), sizeof(double) * ht.chn.size(),
-                           hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(h.chg, ht.chg.data(), sizeof(double) * ht.chg.size(),
-                           hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(h.tables32, ht.tab32.data(), sizeof(float) * ht.tab32.size(),
-                           hipMemcpyHostToDevice, s));
-    if (int rc = launch_step(&h, s, true, true, nullptr)) return rc;
-    k_static_unpack<<<gN, kBlock, 0, s>>>(h.Eout, h.Eid, (uint32_t)n, E);
-    const hipError_t le = hipGetLastError();
-    if (le != hipSuccess) return fail(SIM_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(le));
-    // the host tables above are the copies' sources: done before they go
+    k_static_setup<<<gSet, kBlock, 0, s>>>(table_dst(&h, *p), sg, ct, h.seg, h.ctl, h.tile_member,
+                                           h.chunk_member, h.hist, const_cast<double *>(sg.u_asy),
+                                           u_asy, (int)sh.nt, (int)sh.nc, h.lo.nb);
+    k_static_pack<<<gN, kBlock, 0, s>>>(pos, (uint32_t)n, h.A, h.krec, h.hist, sg.inv_vol, sg.nb);
+    // the field goes straight to the caller's array, by id
+    h.Eout = E;
+    h.Eid = nullptr;
+    if (int rc = launch_step(&h, s, true, false, nullptr)) return rc;
     HIP_TRY(hipStreamSynchronize(s));
     return SIM_OK;
 }
