@@ -2543,6 +2543,37 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 && !SPLIT ? 6 :
     }
 }
 
+// The state of a member whose ids are its creation indices, in creation order:
+// the records not flagged absorbed, and the graveyard.
+__global__ __launch_bounds__(kBlock) void k_export_state(const PRec *A, const uint8_t *dead,
+                                                         uint32_t n_cur, Grave G, uint32_t p0,
+                                                         uint32_t n_dead, double *pos, double *vel,
+                                                         uint8_t *alive)
+{
+    const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
+    if (i < n_cur && !dead[p0 + i]) {
+        const PRec r = A[p0 + i];
+        const size_t k = r.uid;
+        pos[3 * k] = r.x;
+        pos[3 * k + 1] = r.y;
+        pos[3 * k + 2] = r.z;
+        vel[3 * k] = r.vx;
+        vel[3 * k + 1] = r.vy;
+        vel[3 * k + 2] = r.vz;
+        alive[k] = 1;
+    }
+    if (i < n_dead) {
+        const size_t g = p0 + i, k = G.uid[g];
+        pos[3 * k] = G.x[g];
+        pos[3 * k + 1] = G.y[g];
+        pos[3 * k + 2] = G.z[g];
+        vel[3 * k] = G.vx[g];
+        vel[3 * k + 1] = G.vy[g];
+        vel[3 * k + 2] = G.vz[g];
+        alive[k] = 0;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Constant tables, filled on the device (no copies: an evaluation without a
 // handle fills them on each call)
@@ -2954,6 +2985,7 @@ struct Member {
     int64_t start_step = 0;
     double q_surface0 = 0.0;
     std::vector<std::pair<uint32_t, int64_t>> id_index;  // (uid, creation index), sorted
+    bool ids_are_indices = false;   // ids 0..n-1 in creation order
 };
 
 }  // namespace
@@ -3467,6 +3499,7 @@ int update_graph(sim *h)
 struct Prepared {
     std::vector<uint32_t> uid;
     std::vector<std::pair<uint32_t, int64_t>> idx;
+    bool ids_are_indices = false;
 };
 
 // Validate a member completely (no device work).
@@ -3493,7 +3526,11 @@ int prepare_member(const sim_member *m, Prepared *pr)
             if (!std::isfinite(m->ion_profile[j]) || m->ion_profile[j] < 0.0)
                 return fail(SIM_EINVAL, "ion_profile values must be finite and >= 0");
     pr->uid.resize((size_t)n);
-    for (int64_t i = 0; i < n; ++i) pr->uid[i] = m->ids ? m->ids[i] : (uint32_t)i;
+    pr->ids_are_indices = true;
+    for (int64_t i = 0; i < n; ++i) {
+        pr->uid[i] = m->ids ? m->ids[i] : (uint32_t)i;
+        if (pr->uid[i] != (uint32_t)i) pr->ids_are_indices = false;
+    }
     if (!(m->ion_mass > 0.0))
         for (int64_t i = 0; i < n; ++i)
             if (pr->uid[i] & kIonBit) return fail(SIM_EINVAL, "ion ids (bit 31) need ion_mass > 0");
@@ -3545,6 +3582,7 @@ int engine_add(sim *h, const sim_member *m, Prepared &pr, int32_t *index)
     mb.start_step = m->start_step;
     mb.q_surface0 = m->q_surface0;
     mb.id_index = std::move(pr.idx);
+    mb.ids_are_indices = pr.ids_are_indices;
     Seg &sg = mb.seg;
     const uint32_t t0 = g0 * kTilesPerGroup;
     sg.p0 = g0 * kGroupSlots;
@@ -4092,6 +4130,31 @@ int sim_member_read_state(sim_t *h, int32_t index, double *pos, double *vel, uin
     const int64_t n = mb.n;
     const size_t p0 = mb.seg.p0;
     const size_t na = ctl.n_cur, ng = ctl.n_dead;
+    if (q_surface)
+        *q_surface = (mb.q_surface0 + kQ * (double)(ctl.n_dead - ctl.n_dead_ion)) +
+                     (double)ctl.n_dead_ion;
+    if (step) *step = ctl.step;
+    if (!pos && !vel && !alive) return SIM_OK;
+    if (mb.ids_are_indices) {
+        // Put in order on the device and copied once (a search per particle on
+        // the host took 10 of the 11 ms that 100,117 particles needed: now 0.41
+        // ms).  The sorted copy of the state, rewritten by the next step, is the
+        // room: three arrays of all slots hold the member's [3n] at 3 p0.
+        const unsigned count = (unsigned)std::max(na, ng);
+        double *dp = h->B.x + 3 * p0, *dv = h->B.vx + 3 * p0;
+        uint8_t *da = reinterpret_cast<uint8_t *>(h->Eid + p0);
+        hipStream_t st = h->stream;
+        if (count)
+            k_export_state<<<(count + kBlock - 1) / kBlock, kBlock, 0, st>>>(
+                h->A, h->dead, (uint32_t)na, h->G, (uint32_t)p0, (uint32_t)ng, dp, dv, da);
+        if (hipGetLastError() != hipSuccess ||
+            (pos && hipMemcpyAsync(pos, dp, 24 * n, hipMemcpyDeviceToHost, st)) ||
+            (vel && hipMemcpyAsync(vel, dv, 24 * n, hipMemcpyDeviceToHost, st)) ||
+            (alive && hipMemcpyAsync(alive, da, n, hipMemcpyDeviceToHost, st)) ||
+            hipStreamSynchronize(st) != hipSuccess)
+            return mark_failed(h, fail(SIM_EDEVICE, "state copy failed"));
+        return SIM_OK;
+    }
     std::vector<double> a[6], g[6];
     std::vector<uint32_t> au(na), gu(ng);
     std::vector<uint8_t> ad(na);
@@ -4136,10 +4199,6 @@ int sim_member_read_state(sim_t *h, int32_t index, double *pos, double *vel, uin
         put(k, a, i);
         if (alive) alive[k] = 1;
     }
-    if (q_surface)
-        *q_surface = (mb.q_surface0 + kQ * (double)(ctl.n_dead - ctl.n_dead_ion)) +
-                     (double)ctl.n_dead_ion;
-    if (step) *step = ctl.step;
     return SIM_OK;
 }
 

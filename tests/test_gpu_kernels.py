@@ -144,3 +144,30 @@ def test_field_forms_agree_bitwise(L, precision, split):
     np.testing.assert_array_equal(q0, q1)
     for k in ("pos", "vel", "alive"):
         np.testing.assert_array_equal(s0[k], s1[k])
+
+
+@pytest.mark.parametrize("n", [1, 255, 3000])
+def test_state_of_index_ids_equals_state_of_any_ids(n):
+    """Ids that are the creation indices are put in order on the device, others
+    on the host: the same run read both ways (the ids only break ties), with
+    absorbed particles, for one member among others."""
+    print(f"[gpu] state read n={n}", file=sys.stderr, flush=True)
+    st = W.uniform_shell(n, 30 + n, 3.0, 0.6)
+    other = W.uniform_shell(300, 31, 3.0, 0.1)
+    out = []
+    for ids in (None, np.arange(n, dtype=np.uint32) * 5 + 2):
+        ms = [S.Member(pos=p.pos, vel=p.vel, u_asy=np.zeros(9), ids=i, r_out=3.0,
+                       ntilde=W.ntilde_for(n, 3.0)) for p, i in ((other, None), (st, ids))]
+        with S.Batch(S.SimParams(l_max=3), ms) as b:
+            first = b.read_state(1)
+            b.step(6)
+            mid = b.read_state(1)
+            b.step(3)
+            out.append((first, mid, b.read_state(1)))
+    np.testing.assert_array_equal(out[0][0]["pos"], st.pos)
+    for a, c in zip(*out):
+        for k in ("pos", "vel", "alive"):
+            np.testing.assert_array_equal(a[k], c[k])
+        assert a["q_surface"] == c["q_surface"] and a["step"] == c["step"]
+    if n == 3000:
+        assert (out[0][2]["alive"] == 0).any()
