@@ -145,6 +145,7 @@ struct Tables {
     const double *wl;       // 1 / (2l+1)
     const double *drive_w;  // c_l b^P_l sqrt(4 pi / (2l+1)) for odd l, else 0
     const double *self_w;   // f_l / (4 pi)
+    const double *self_w1;  // (l+1) f_l / (4 pi)
     const double4 *nf4;     // {(2l+1)/(l+1), l/(l+1), 2l+1, l}, one wide load per l
     const int *chl;         // degree l of each channel in stream order
     // per channel: the factor that turns a sum of rescaled harmonics (Qh) into
@@ -1987,9 +1988,18 @@ __device__ inline void near_field_full(int lane, int W, int L, const LG *lg, con
                 SB = fmaf(rl, dPm, SB);
             };
             int l = 1;
-            for (; l + 1 < L; l += 2) {
-                degree(lg[l], Pa, Da, dPb, Pb, Db);       // degree l + 1
-                degree(lg[l + 1], Pb, Db, dPa, Pa, Da);   // degree l + 2
+#pragma unroll 1
+            for (; l + 3 < L; l += 4) {   // four degrees: one wait for their constants
+                const LG ca = lg[l], cb = lg[l + 1], cc = lg[l + 2], cd = lg[l + 3];
+                degree(ca, Pa, Da, dPb, Pb, Db);   // degree l + 1
+                degree(cb, Pb, Db, dPa, Pa, Da);   // degree l + 2
+                degree(cc, Pa, Da, dPb, Pb, Db);
+                degree(cd, Pb, Db, dPa, Pa, Da);
+            }
+            if (l + 1 < L) {
+                degree(lg[l], Pa, Da, dPb, Pb, Db);
+                degree(lg[l + 1], Pb, Db, dPa, Pa, Da);
+                l += 2;
             }
             if (l < L) degree(lg[l], Pa, Da, dPb, Pb, Db);
         } else {
@@ -2215,9 +2225,14 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 && !SPLIT ? 6 :
             // channel from the lane of its degree
             double pw_in = 1.0, pw_out = 1.0;
             if (FP32) {
-                const double lg = log2(rho);
-                pw_in = exp2(-(lane + 2.0) * lg);
-                pw_out = exp2((lane + 1.0) * lg);
+                // by squaring: 24 FP64 operations, log2 and exp2 took 124
+                double sq = rho;
+#pragma unroll
+                for (int k = 0; k < 7; ++k) {
+                    if ((lane + 1) >> k & 1) pw_out *= sq;
+                    sq *= sq;
+                }
+                pw_in = 1.0 / (pw_out * rho);
             }
             int win0 = 0, win_len = -1;   // resident channels [win0, win0 + win_len)
             // Fills the window with channels [k0, k0 + len), U channels per lane at a
@@ -2372,10 +2387,8 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 && !SPLIT ? 6 :
         double sr = 0.0, sz = 0.0;   // radial and (e_z - c xh) parts of grad Phi_self
         double rl = inv_r2 * inv_r2 * inv_r;   // r^-(2l+3) at l = 1
         if (FULL) {
-            for (int l = 1; l <= L; ++l) {
-                sr += tb.self_w[l] * (l + 1.0) * rl;
-                rl *= inv_r2;
-            }
+            for (int l = L; l >= 1; --l) sr = fma(sr, inv_r2, tb.self_w1[l]);
+            sr *= rl;
             // grad Phi_self = -q sum f_l (l+1)/(4 pi nt) r^-(2l+3) xh; E = -grad
             const double e = qk * inv_nt * sr;
             Ex += e * xh;
@@ -2583,7 +2596,7 @@ __global__ __launch_bounds__(kBlock) void k_export_state(const PRec *A, const ui
 // ---------------------------------------------------------------------------
 
 // Layout of the FP64 table block: room for nine per-l arrays (ftil, wl,
-// drive_w, self_w in use) and two (l, m) triangles, then at 32-byte aligned
+// drive_w, self_w, self_w1 in use) and two (l, m) triangles, then at 32-byte aligned
 // offsets the near-field constants (nf4, lg4) and the rescaled recurrence
 // (fq4) with its zero entry.
 __host__ __device__ inline size_t nf4_offset(int L)
@@ -2625,7 +2638,8 @@ __device__ inline void fill_tables(const TableDst &t, int i0, int stride)
 {
 #pragma clang fp contract(off)
     const int L = t.L, n = L + 1, tri_n = (L + 1) * (L + 2) / 2;
-    double *ftil = t.tab, *wl = ftil + n, *drive = wl + n, *selfw = drive + n;
+    double *ftil = t.tab, *wl = ftil + n, *drive = wl + n, *selfw = drive + n,
+           *selfw1 = selfw + n;
     double *nf4 = t.tab + nf4_offset(L), *lg4 = t.tab + lg4_offset(L), *fq4 = t.tab + fq4_offset(L);
     float *fq32 = t.tab32 + fq4_32_offset(L), *lw32 = t.tab32 + lw4_32_offset(L);
     for (int l = i0; l <= L; l += stride) {
@@ -2650,6 +2664,7 @@ __device__ inline void fill_tables(const TableDst &t, int i0, int stride)
         wl[l] = 1.0 / (2.0 * dl + 1.0);
         drive[l] = c * bP * sqrt(4.0 * kPi / (2.0 * dl + 1.0));
         selfw[l] = l == 0 ? 0.0 : f / (4.0 * kPi);
+        selfw1[l] = selfw[l] * (dl + 1.0);
         nf4[4 * l + 0] = (2.0 * dl + 1.0) / (dl + 1.0);
         nf4[4 * l + 1] = dl / (dl + 1.0);
         nf4[4 * l + 2] = 2.0 * dl + 1.0;
@@ -3344,6 +3359,7 @@ void bind_device_tables(sim *h)
     h->tb.wl = tb + (L + 1);
     h->tb.drive_w = tb + 2 * (L + 1);
     h->tb.self_w = tb + 3 * (L + 1);
+    h->tb.self_w1 = tb + 4 * (L + 1);
     h->tb.nf4 = reinterpret_cast<const double4 *>(tb + nf4_offset(L));
     h->tb.lg4 = reinterpret_cast<const double4 *>(tb + lg4_offset(L));
     h->tb.fq4 = reinterpret_cast<const double4 *>(tb + fq4_offset(L));
