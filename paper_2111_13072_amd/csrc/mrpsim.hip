@@ -551,6 +551,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_scatter(Map mp, const KeyRec *k
     orec[(SCAN ? lds_off[b] : off[b]) + r.sub] = OrdRec{r.key, r.uid, i};
 }
 
+// Ranking in a kernel of its own, for large mean buckets (kPlaceMaxBucket).
 // Final position = bucket start + number of bucket mates with a smaller
 // (r^2, id) key (independent of the order inside the bucket), moved into the
 // member's slot range; the particle's state moves there.  A block's positions
@@ -624,154 +625,6 @@ __global__ __launch_bounds__(kBlock) void k_sort_rank_move(Map mp, const OrdRec 
     B.uid[d] = u;
 }
 
-// The same ranking for the block of a group of slots (small launches, inside
-// the moments kernel): the window of whole buckets that holds the group's
-// positions, staged in LDS with the buckets' offsets where both fit.
-constexpr int kRankOffsets = 512;   // buckets
-
-struct RankLds {
-    uint64_t key[kRankWindow];
-    uint32_t uid[kRankWindow], idx[kRankWindow];
-    uint32_t off[kRankOffsets + 1];
-    uint32_t src[kGroupSlots];      // source slot of each of the group's positions
-};
-
-// Source slots of the positions first .. first + count - 1 of the bucket order
-// [p_first, ...) into r.src.  All threads of the block take part.
-__device__ inline void rank_group(const Seg &sg, const OrdRec *orec, const uint32_t *off,
-                                  uint32_t p_first, int count, RankLds &r)
-{
-    const uint32_t p_last = p_first + (uint32_t)count - 1;
-    auto bucket = [&](uint64_t key) {
-        return bucket_of(__longlong_as_double((long long)key), sg.inv_vol, sg.b0, sg.nb);
-    };
-    const uint32_t ba = uniform_u32(bucket(orec[p_first].key));
-    const uint32_t bb = uniform_u32(bucket(orec[p_last].key));
-    const uint32_t w0 = uniform_u32(off[ba]), w1 = uniform_u32(off[bb + 1]);
-    const uint32_t nw = w1 - w0, nbk = bb - ba + 1;
-    if (nw <= (uint32_t)kRankWindow) {
-        const bool off_staged = nbk <= (uint32_t)kRankOffsets;
-        if (off_staged)
-            for (uint32_t j = threadIdx.x; j <= nbk; j += kBlock) r.off[j] = off[ba + j] - w0;
-        for (uint32_t j = threadIdx.x; j < nw; j += kBlock) {
-            const OrdRec o = orec[w0 + j];
-            r.key[j] = o.key;
-            r.uid[j] = o.uid;
-            r.idx[j] = o.idx;
-        }
-        __syncthreads();
-        for (uint32_t j = threadIdx.x; j < nw; j += kBlock) {
-            const uint64_t k = r.key[j];
-            const uint32_t u = r.uid[j], bk = bucket(k);
-            const uint32_t lo = off_staged ? r.off[bk - ba] : off[bk] - w0;
-            const uint32_t hi = off_staged ? r.off[bk - ba + 1] : off[bk + 1] - w0;
-            uint32_t pos = lo + w0 - p_first;   // wraps below zero before the group's first
-            for (uint32_t i = lo; i < hi; ++i) {
-                const uint64_t ki = r.key[i];
-                pos += (ki < k) || (ki == k && r.uid[i] < u);
-            }
-            if (pos < (uint32_t)count) r.src[pos] = r.idx[j];
-        }
-        __syncthreads();
-        return;
-    }
-    // A window too large for LDS (a radial concentration far over the mean
-    // density): the keys (r^2, id) of the group's first and last position by
-    // bisection over their bits, one counting pass over the window per bit,
-    // then the records between them, at most a group, ranked in LDS.  96
-    // passes by the whole block are less than one pass per particle from 256
-    // particles on.
-    __shared__ uint32_t cnt[2], n_got;
-    uint64_t key0 = 0, key1 = 0;
-    uint32_t uid0 = 0, uid1 = 0;
-    const uint32_t r0 = p_first - w0, r1 = p_last - w0;
-    for (int bit = 95; bit >= 0; --bit) {
-        // the largest (key, id) with at most r0 (r1) records before it
-        const uint64_t kb = bit >= 32 ? 1ull << (bit - 32) : 0ull;
-        const uint32_t ub = bit >= 32 ? 0u : 1u << bit;
-        const uint64_t t0 = key0 | kb, t1 = key1 | kb;
-        const uint32_t v0 = uid0 | ub, v1 = uid1 | ub;
-        if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
-        __syncthreads();
-        uint32_t c0 = 0, c1 = 0;
-        for (uint32_t j = threadIdx.x; j < nw; j += kBlock) {
-            const OrdRec o = orec[w0 + j];
-            c0 += (o.key < t0) || (o.key == t0 && o.uid < v0);
-            c1 += (o.key < t1) || (o.key == t1 && o.uid < v1);
-        }
-        atomicAdd(&cnt[0], c0);
-        atomicAdd(&cnt[1], c1);
-        __syncthreads();
-        if (cnt[0] <= r0) {
-            key0 = t0;
-            uid0 = v0;
-        }
-        if (cnt[1] <= r1) {
-            key1 = t1;
-            uid1 = v1;
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) n_got = 0;
-    __syncthreads();
-    for (uint32_t j = threadIdx.x; j < nw; j += kBlock) {
-        const OrdRec o = orec[w0 + j];
-        const bool from = o.key > key0 || (o.key == key0 && o.uid >= uid0);
-        const bool upto = o.key < key1 || (o.key == key1 && o.uid <= uid1);
-        if (from && upto) {
-            const uint32_t at = atomicAdd(&n_got, 1u);
-            if (at < (uint32_t)kGroupSlots) {   // ids are distinct: exactly count records
-                r.key[at] = o.key;
-                r.uid[at] = o.uid;
-                r.idx[at] = o.idx;
-            }
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x < (uint32_t)count) {
-        const uint64_t k = r.key[threadIdx.x];
-        const uint32_t u = r.uid[threadIdx.x];
-        uint32_t pos = 0;
-        for (int i = 0; i < count; ++i) pos += (r.key[i] < k) || (r.key[i] == k && r.uid[i] < u);
-        r.src[pos] = r.idx[threadIdx.x];
-    }
-    __syncthreads();
-}
-
-// Puts a group's particles in radial order: thread t gets the record of the
-// group's position t (t < the returned count) and writes it to the sorted
-// state.
-__device__ inline int place_group(const Seg &sg, const OrdRec *orec, const uint32_t *off,
-                                  const PRec *A, const State &B, uint32_t group, bool write,
-                                  RankLds &r, PRec &a)
-{
-    const uint32_t first = (group - sg.g0) * kGroupSlots;
-    const uint32_t o0 = uniform_u32(off[sg.b0]);
-    const uint32_t n = uniform_u32(off[sg.b0 + sg.nb]) - o0;   // the member's live particles
-    if (n <= first) return 0;
-    const int count = (int)min(n - first, (uint32_t)kGroupSlots);
-    rank_group(sg, orec, off, o0 + first, count, r);
-    if ((int)threadIdx.x < count) {
-        a = A[r.src[threadIdx.x]];
-        if (write) {
-            const size_t d = (size_t)group * kGroupSlots + threadIdx.x;
-            B.x[d] = a.x;
-            B.y[d] = a.y;
-            B.z[d] = a.z;
-            B.vx[d] = a.vx;
-            B.vy[d] = a.vy;
-            B.vz[d] = a.vz;
-            B.uid[d] = a.uid;
-        }
-    }
-    return count;
-}
-
-// Up to this many groups the moments kernel ranks its own group: 1e6 particles
-// at l_max 1 (3,907 groups) 219 -> 217 us per step, at l_max 32 1.113 -> 1.105
-// ms; 2e6 at l_max 16 0.837 -> 0.850 ms.
-constexpr int kRankFusedMaxGroups = 4096;
-
 // ---------------------------------------------------------------------------
 // Moments: per-tile sums of q R_lm and q I_lm
 // ---------------------------------------------------------------------------
@@ -837,83 +690,16 @@ __device__ inline double dpp_shr4_odd_banks(double v)
 // scan over its tiles inside a wave, without barriers, and lets a small launch
 // spread one group over several blocks (21,347 particles at l_max 32: the
 // evaluation 344 -> 222 us).  1.6e7 particles, l_max 16: 1.94 -> 1.29 ms.
-// RANK: the block first puts its group in radial order (place_group) and goes
-// on with the particles it has in LDS.  This saves a launch (evaluation of
-// 120,011 particles at l_max 16: 171 -> 156 us), but the ranking's chain of
-// dependent loads then runs at four blocks per CU instead of eight (2e6
-// particles: 272 us against 194 + 71), so large launches rank in a kernel of
-// their own (kRankFusedMaxGroups).
-template <bool FULL, bool RANK>
-__global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, const OrdRec *orec,
-                                                       const uint32_t *off, const PRec *A, State B,
-                                                       Tables tb, KParams kp, double *H, double *GS,
-                                                       uint32_t *clear, int n_clear)
+template <bool FULL>
+__device__ inline void moment_sums(const double (&x)[kMomParts], const double (&y)[kMomParts],
+                                   const double (&z)[kMomParts], const double (&q)[kMomParts],
+                                   const uint64_t (&ions)[kMomParts], int count, int lane,
+                                   int slice, uint32_t group, const Tables &tb, const KParams &kp,
+                                   double *H, double *GS, double *wb)
 {
-    struct Parts {
-        double x[kGroupSlots], y[kGroupSlots], z[kGroupSlots];
-        float q[kGroupSlots];
-    };
-    __shared__ union {
-        typename std::conditional<RANK, RankLds, double>::type rank;
-        double buf[kWavesPerBlock][2 * kMomSlots * kMomRow];
-    } lds;
-    __shared__ __attribute__((aligned(16))) typename std::conditional<RANK, Parts, double>::type part;
-    const int lane = threadIdx.x & 63;
-    const int w = (int)uniform_u32(threadIdx.x >> 6);
-    // (neighbouring groups share gathered lines)
-    const uint32_t group = RANK ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
-    if constexpr (RANK) {
-        if (blockIdx.x == 0 && blockIdx.y == 0) {
-            member_live(mp, off, kp);
-            // the histogram, where the scatter kernel scanned it
-            for (int i = threadIdx.x; i < n_clear; i += kBlock) clear[i] = 0u;
-        }
-    }
-    const uint32_t mb = uniform_u32(mp.tile_member[group * kTilesPerGroup]);
-    if (mb == kNone || !member_runs(mp.seg[mb], mp.ctl[mb], kp)) return;
-    double x[kMomParts], y[kMomParts], z[kMomParts], q[kMomParts];
-    uint64_t ions[kMomParts];
-    int count;   // the group's particles
-    if constexpr (RANK) {
-        PRec a;
-        count = place_group(mp.seg[mb], orec, off, A, B, group, blockIdx.y == 0, lds.rank, a);
-        const int t = (int)threadIdx.x;
-        const bool valid = t < count;
-        part.x[t] = valid ? a.x : 0.0;
-        part.y[t] = valid ? a.y : 0.0;
-        part.z[t] = valid ? a.z : 2.0;
-        part.q[t] = valid ? ((a.uid & kIonBit) ? 1.0f : (float)kQ) : 0.0f;
-        __syncthreads();   // and the ranking's LDS is free for the sums from here on
-#pragma unroll
-        for (int j = 0; j < kMomParts; ++j) {
-            const int i = kMomParts * lane + j;
-            x[j] = part.x[i];
-            y[j] = part.y[i];
-            z[j] = part.z[i];
-            q[j] = (double)part.q[i];
-            ions[j] = __ballot(q[j] > 0.0);
-        }
-    } else {
-        const uint32_t first = (group - mp.seg[mb].g0) * kGroupSlots;
-        const uint32_t n = mp.ctl[mb].n_live;
-        count = n > first ? (int)min(n - first, (uint32_t)kGroupSlots) : 0;
-        const size_t p = (size_t)group * kGroupSlots + kMomParts * lane;
-#pragma unroll
-        for (int j = 0; j < kMomParts; ++j) {
-            const bool valid = kMomParts * lane + j < count;
-            x[j] = valid ? B.x[p + j] : 0.0;
-            y[j] = valid ? B.y[p + j] : 0.0;
-            z[j] = valid ? B.z[p + j] : 2.0;
-            const bool ion = valid && (B.uid[p + j] & kIonBit) != 0;
-            q[j] = valid ? (ion ? 1.0 : kQ) : 0.0;
-            ions[j] = __ballot(ion);
-        }
-    }
     const int L = kp.L, C = kp.C;
     double *Hg = H + (size_t)group * kTilesPerGroup * kp.HW;
     double *Gs = GS + (size_t)group * kp.SW;
-    const int turn = (int)(group & (kWavesPerBlock - 1));
-    const int slice = (int)blockIdx.y * kWavesPerBlock + ((w + turn) & (kWavesPerBlock - 1));
     if (slice == 0) {
         // charge of the group's tiles before each one, and of the group
         // (exact: counts of ions and electrons)
@@ -943,7 +729,6 @@ __global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, const OrdRec *ore
         sq[j] = 0.0;
     }
 
-    double *wb = lds.buf[w];
     double *wr = wb + (lane >> 3) * kMomHalfOff + (lane & 7);
     // reader: channel rc of the batch, side rio, half h (in scan order: the
     // exterior sums are scanned from the last tile to the first)
@@ -1116,6 +901,290 @@ __global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, const OrdRec *ore
         }
         if (second) flush(ch, 2);
     }
+}
+
+// A group's particles in LDS.
+struct __attribute__((aligned(16))) Parts {
+    double x[kGroupSlots], y[kGroupSlots], z[kGroupSlots];
+    float q[kGroupSlots];
+    __device__ void put(int i, double xx, double yy, double zz, float qq)
+    {
+        x[i] = xx;
+        y[i] = yy;
+        z[i] = zz;
+        q[i] = qq;
+    }
+    __device__ void load(int lane, double (&xx)[kMomParts], double (&yy)[kMomParts],
+                         double (&zz)[kMomParts], double (&qq)[kMomParts],
+                         uint64_t (&ions)[kMomParts]) const
+    {
+#pragma unroll
+        for (int j = 0; j < kMomParts; ++j) {
+            const int i = kMomParts * lane + j;
+            xx[j] = x[i];
+            yy[j] = y[i];
+            zz[j] = z[i];
+            qq[j] = (double)q[i];
+            ions[j] = __ballot(qq[j] > 0.0);
+        }
+    }
+};
+
+// The ranking inside the moments kernel: each wave of a
+// group's block places a tile, without barriers, its records' gathers issued
+// before the ranking.  Windows of whole buckets around a tile in LDS.
+constexpr int kPlaceWindow = 320;    // records
+constexpr int kPlaceMaxBucket = 32;  // larger mean buckets would not fit the window
+
+struct PlaceLds {
+    uint64_t key[kPlaceWindow];
+    uint32_t uid[kPlaceWindow];
+};
+
+// Places what the tile's positions of the bucket order hold (and what the
+// tile's slots take from outside the group): p_group is the group's first
+// position, count its particles, slot0 its first slot; q the tile; write: to the
+// sorted state too.
+__device__ inline void place_tile(const Seg &sg, const OrdRec *__restrict__ orec,
+                                  const uint32_t *__restrict__ off, const PRec *__restrict__ A,
+                                  const State &B, bool write, uint32_t p_group, int count,
+                                  size_t slot0, int q, int lane, PlaceLds &r, Parts &out)
+{
+    const int tc = min(max(count - q * kWave, 0), kWave);
+    if (lane >= tc) out.put(q * kWave + lane, 0.0, 0.0, 2.0, 0.0f);
+    if (tc == 0) return;
+    auto bucket = [&](uint64_t key) {
+        return bucket_of(__longlong_as_double((long long)key), sg.inv_vol, sg.b0, sg.nb);
+    };
+    auto store = [&](uint32_t slot, const PRec &a) {
+        out.put((int)slot, a.x, a.y, a.z, (a.uid & kIonBit) ? 1.0f : (float)kQ);
+        if (!write) return;
+        const size_t d = slot0 + slot;
+        B.x[d] = a.x;
+        B.y[d] = a.y;
+        B.z[d] = a.z;
+        B.vx[d] = a.vx;
+        B.vy[d] = a.vy;
+        B.vz[d] = a.vz;
+        B.uid[d] = a.uid;
+    };
+    const uint32_t pf = p_group + (uint32_t)(q * kWave), pl = pf + (uint32_t)tc - 1;
+    const bool on = lane < tc;
+    const OrdRec me = orec[on ? pf + (uint32_t)lane : pl];
+    const PRec a = A[me.idx];
+    const uint32_t b = bucket(me.key);
+    const uint32_t lo = off[b], hi = off[b + 1];
+    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)lo, 0);
+    const uint32_t h0 = (uint32_t)__builtin_amdgcn_readlane((int)hi, 0);
+    const uint32_t l1 = (uint32_t)__builtin_amdgcn_readlane((int)lo, tc - 1);
+    const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)hi, tc - 1);
+    const uint32_t nw = w1 - w0, before = pf - w0, extra = before + (w1 - 1 - pl);
+    if (nw <= (uint32_t)kPlaceWindow) {
+        // the window's records before and after the tile's positions
+        auto extra_at = [&](uint32_t e) { return e < before ? w0 + e : pl + 1 + (e - before); };
+        OrdRec ex{0ull, 0u, 0u};
+        if ((uint32_t)lane < extra) ex = orec[extra_at(lane)];
+        for (uint32_t e = (uint32_t)(lane + kWave); e < extra; e += kWave) {
+            const OrdRec o = orec[extra_at(e)];
+            r.key[extra_at(e) - w0] = o.key;
+            r.uid[extra_at(e) - w0] = o.uid;
+        }
+        if (on) {
+            r.key[before + lane] = me.key;
+            r.uid[before + lane] = me.uid;
+        }
+        if ((uint32_t)lane < extra) {
+            r.key[extra_at(lane) - w0] = ex.key;
+            r.uid[extra_at(lane) - w0] = ex.uid;
+        }
+        wave_lds_sync();
+        auto ranked = [&](uint64_t k, uint32_t u, uint32_t first, uint32_t end) {
+            uint32_t pos = first;
+            for (uint32_t i = first - w0; i < end - w0; ++i) {
+                const uint64_t ki = r.key[i];
+                pos += (ki < k) || (ki == k && r.uid[i] < u);
+            }
+            return pos - p_group;   // wraps for positions before the group
+        };
+        const uint32_t slot = ranked(me.key, me.uid, lo, hi);
+        if (on && slot < (uint32_t)count) store(slot, a);
+        // records of other groups' positions that rank into this one: in the
+        // buckets across the group's ends
+        for (uint32_t e = (uint32_t)lane; __ballot(e < extra); e += kWave) {
+            const uint32_t p = extra_at(e);
+            const bool out_of_group = e < extra && p - p_group >= (uint32_t)count;
+            if (!__ballot(out_of_group)) continue;
+            if (out_of_group) {
+                const OrdRec o = e < (uint32_t)kWave ? ex : orec[p];
+                const bool low = e < before;
+                const uint32_t es = ranked(o.key, o.uid, low ? w0 : l1, low ? h0 : w1);
+                if (es < (uint32_t)count) store(es, A[o.idx]);
+            }
+        }
+        wave_lds_sync();   // the window is read
+        return;
+    }
+    // A window too large for LDS (a radial concentration far over the mean
+    // density): the tile's slots by selection.  The keys (r^2, id) of its first
+    // and last position by bisection over the bits in which the window's keys
+    // differ, one counting pass of the wave per bit (the ids' bits only where
+    // keys are equal), then the records between them, ranked in LDS.
+    uint64_t all = ~0ull, any = 0ull;
+    for (uint32_t j = (uint32_t)lane; j < nw; j += kWave) {
+        const uint64_t k = orec[w0 + j].key;
+        all &= k;
+        any |= k;
+    }
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        all &= (uint64_t)__shfl_xor((unsigned long long)all, o);
+        any |= (uint64_t)__shfl_xor((unsigned long long)any, o);
+    }
+    const uint64_t differ = all ^ any;
+    const int top = differ ? 63 - __builtin_clzll(differ) : -1;   // highest differing bit
+    uint64_t key0 = top < 63 ? all >> (top + 1) << (top + 1) : 0ull, key1 = key0;
+    uint32_t uid0 = 0, uid1 = 0;
+    const uint32_t r0 = pf - w0, r1 = pl - w0;
+    auto count2 = [&](auto f0, auto f1, uint32_t *c0, uint32_t *c1) {
+        *c0 = *c1 = 0;
+        for (uint32_t j = 0; j < nw; j += kWave) {
+            bool s0 = false, s1 = false;
+            if (j + (uint32_t)lane < nw) {
+                const OrdRec o = orec[w0 + j + lane];
+                s0 = f0(o);
+                s1 = f1(o);
+            }
+            *c0 += (uint32_t)__popcll(__ballot(s0));
+            *c1 += (uint32_t)__popcll(__ballot(s1));
+        }
+    };
+    uint32_t c0, c1;
+    for (int bit = top; bit >= 0; --bit) {
+        const uint64_t t0 = key0 | 1ull << bit, t1 = key1 | 1ull << bit;
+        count2([&](const OrdRec &o) { return o.key < t0; },
+               [&](const OrdRec &o) { return o.key < t1; }, &c0, &c1);
+        if (c0 <= r0) key0 = t0;
+        if (c1 <= r1) key1 = t1;
+    }
+    count2([&](const OrdRec &o) { return o.key == key0; },
+           [&](const OrdRec &o) { return o.key == key1; }, &c0, &c1);
+    if (c0 <= 1 && c1 <= 1) {
+        uid1 = ~0u;
+    } else {
+        for (int bit = 31; bit >= 0; --bit) {
+            const uint32_t v0 = uid0 | 1u << bit, v1 = uid1 | 1u << bit;
+            count2([&](const OrdRec &o) { return o.key < key0 || (o.key == key0 && o.uid < v0); },
+                   [&](const OrdRec &o) { return o.key < key1 || (o.key == key1 && o.uid < v1); },
+                   &c0, &c1);
+            if (c0 <= r0) uid0 = v0;
+            if (c1 <= r1) uid1 = v1;
+        }
+    }
+    uint32_t got = 0;
+    OrdRec mine{0ull, 0u, 0u};
+    for (uint32_t j = 0; j < nw; j += kWave) {
+        bool in = false;
+        OrdRec o{0ull, 0u, 0u};
+        if (j + (uint32_t)lane < nw) {
+            o = orec[w0 + j + lane];
+            in = (o.key > key0 || (o.key == key0 && o.uid >= uid0)) &&
+                 (o.key < key1 || (o.key == key1 && o.uid <= uid1));
+        }
+        const uint64_t v = __ballot(in);
+        const uint32_t at = got + (uint32_t)__popcll(v & ((1ull << lane) - 1ull));
+        if (in && at < (uint32_t)kWave) {   // ids are distinct: exactly tc records
+            r.key[at] = o.key;
+            r.uid[at] = o.uid;
+            reinterpret_cast<uint32_t *>(r.key + kWave)[at] = o.idx;
+        }
+        got += (uint32_t)__popcll(v);
+    }
+    wave_lds_sync();
+    if (on && (uint32_t)lane < got) {
+        mine.key = r.key[lane];
+        mine.uid = r.uid[lane];
+        mine.idx = reinterpret_cast<uint32_t *>(r.key + kWave)[lane];
+        uint32_t rank = 0;
+        for (int i = 0; i < tc; ++i)
+            rank += (r.key[i] < mine.key) || (r.key[i] == mine.key && r.uid[i] < mine.uid);
+        store((uint32_t)(q * kWave) + rank, A[mine.idx]);
+    }
+    // and the small buckets' records at this tile's positions whose slots are
+    // in another tile of the group (that tile may not be selecting)
+    if (on && hi - lo <= (uint32_t)kPlaceWindow) {
+        uint32_t pos = lo;
+        for (uint32_t i = lo; i < hi; ++i) {
+            const OrdRec o = orec[i];
+            pos += (o.key < me.key) || (o.key == me.key && o.uid < me.uid);
+        }
+        const uint32_t slot = pos - p_group;
+        if (slot < (uint32_t)count && slot / kWave != (uint32_t)q) store(slot, a);
+    }
+    wave_lds_sync();
+}
+
+// RANK: the block first puts its group in radial order (place_tile) and goes
+// on with the particles it has in LDS.  Against a ranking kernel of its own
+// this saves a launch and the reads of the sorted state: evaluation of 120,011
+// particles at l_max 16 171 -> 156 us, 1e6 at l_max 1 112 -> 108 us per step, 4e6
+// at l_max 8 0.759 -> 0.742 ms, 1.6e7 at l_max 16 4.955 -> 4.935 ms.  Only mean
+// buckets over kPlaceMaxBucket rank apart.
+template <bool FULL, bool RANK>
+__global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, const OrdRec *orec,
+                                                       const uint32_t *off, const PRec *A, State B,
+                                                       Tables tb, KParams kp, double *H, double *GS,
+                                                       uint32_t *clear, int n_clear)
+{
+    __shared__ union {
+        typename std::conditional<RANK, PlaceLds, double>::type place[kWavesPerBlock];
+        double buf[kWavesPerBlock][2 * kMomSlots * kMomRow];
+    } lds;
+    __shared__ __attribute__((aligned(16))) typename std::conditional<RANK, Parts, double>::type part;
+    const int lane = threadIdx.x & 63;
+    const int w = (int)uniform_u32(threadIdx.x >> 6);
+    // (neighbouring groups share gathered lines)
+    const uint32_t group = RANK ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
+    if constexpr (RANK) {
+        if (blockIdx.x == 0 && blockIdx.y == 0) {
+            member_live(mp, off, kp);
+            // the histogram, where the scatter kernel scanned it
+            for (int i = threadIdx.x; i < n_clear; i += kBlock) clear[i] = 0u;
+        }
+    }
+    const uint32_t mb = uniform_u32(mp.tile_member[group * kTilesPerGroup]);
+    if (mb == kNone || !member_runs(mp.seg[mb], mp.ctl[mb], kp)) return;
+    double x[kMomParts], y[kMomParts], z[kMomParts], q[kMomParts];
+    uint64_t ions[kMomParts];
+    int count;   // the group's particles
+    if constexpr (RANK) {
+        const Seg &sg = mp.seg[mb];
+        const uint32_t first = (group - sg.g0) * kGroupSlots;
+        const uint32_t o0 = uniform_u32(off[sg.b0]);
+        const uint32_t live = uniform_u32(off[sg.b0 + sg.nb]) - o0;
+        count = live > first ? (int)min(live - first, (uint32_t)kGroupSlots) : 0;
+        place_tile(sg, orec, off, A, B, blockIdx.y == 0, o0 + first, count,
+                   (size_t)group * kGroupSlots, w, lane, lds.place[w], part);
+        __syncthreads();   // and the ranking's LDS is free for the sums from here on
+        part.load(lane, x, y, z, q, ions);
+    } else {
+        const uint32_t first = (group - mp.seg[mb].g0) * kGroupSlots;
+        const uint32_t n = mp.ctl[mb].n_live;
+        count = n > first ? (int)min(n - first, (uint32_t)kGroupSlots) : 0;
+        const size_t p = (size_t)group * kGroupSlots + kMomParts * lane;
+#pragma unroll
+        for (int j = 0; j < kMomParts; ++j) {
+            const bool valid = kMomParts * lane + j < count;
+            x[j] = valid ? B.x[p + j] : 0.0;
+            y[j] = valid ? B.y[p + j] : 0.0;
+            z[j] = valid ? B.z[p + j] : 2.0;
+            const bool ion = valid && (B.uid[p + j] & kIonBit) != 0;
+            q[j] = valid ? (ion ? 1.0 : kQ) : 0.0;
+            ions[j] = __ballot(ion);
+        }
+    }
+    const int turn = (int)(group & (kWavesPerBlock - 1));
+    const int slice = (int)blockIdx.y * kWavesPerBlock + ((w + turn) & (kWavesPerBlock - 1));
+    moment_sums<FULL>(x, y, z, q, ions, count, lane, slice, group, tb, kp, H, GS, lds.buf[w]);
 }
 
 // ---------------------------------------------------------------------------
@@ -2628,6 +2697,23 @@ struct TableDst {
     int L, C;
 };
 
+// A product of exact factors with its rounding errors carried along: the
+// tables' factors are good to about one rounding at any degree.
+struct ExactProduct {
+    double hi, lo = 0.0;
+    __device__ void mul(double a)
+    {
+        const double p = hi * a;
+        lo = fma(lo, a, fma(hi, a, -p));
+        hi = p;
+    }
+    __device__ double over(const ExactProduct &d) const
+    {
+        const double q = hi / d.hi;
+        return fma(q, lo / hi - d.lo / d.hi, fma(-q, d.hi, hi) / d.hi) + q;
+    }
+};
+
 // The entries i0, i0 + stride, ... of every table.  f_l and b^P_l are the
 // closed forms of App. A and Sec. 3 (R = 1, R_E = 1 - d); c_l, the Legendre
 // coefficients of the electrode data 1/2 sgn(cos th), are taken as
@@ -2673,8 +2759,12 @@ __device__ inline void fill_tables(const TableDst &t, int i0, int stride)
         // recurrence l P_l = (2l-1) u P_{l-1} - (l-1) P_{l-2} becomes
         // Ph_l = u Ph_{l-1} - gamma_l Ph_{l-2}, gamma_l = (l-1)^2 / ((2l-1)(2l-3));
         // P'_{l+1} = P'_{l-1} + (2l+1) c_l Ph_l
-        double cl = 1.0;
-        for (int k = 1; k <= l; ++k) cl *= (2.0 * k - 1.0) / k;
+        ExactProduct odd{1.0}, fac{1.0};
+        for (int k = 1; k <= l; ++k) {
+            odd.mul(2.0 * k - 1.0);
+            fac.mul((double)k);
+        }
+        const double cl = odd.over(fac);
         lg4[4 * l + 0] = cl;
         lg4[4 * l + 1] = dl * cl;
         lg4[4 * l + 2] = dl * dl / ((2.0 * dl + 1.0) * (2.0 * dl - 1.0));
@@ -2712,16 +2802,16 @@ __device__ inline void fill_tables(const TableDst &t, int i0, int stride)
         if (i == tri_n || l == 0) continue;
         const int ch = m == 0 ? l - 1 : L + (m - 1) * (2 * L + 2 - m) + 2 * (l - m);
         if (ch >= t.C) continue;   // axisymmetric: m = 0 only
-        double num = m > 0 ? 2.0 : 1.0, den = 4.0 * kPi;
+        ExactProduct num{m > 0 ? 2.0 : 1.0}, den{4.0 * kPi};
         for (int k = 1; k <= m; ++k) {
-            num *= 2.0 * k + 1.0;
-            den *= 2.0 * k;
+            num.mul(2.0 * k + 1.0);
+            den.mul(2.0 * k);
         }
         for (int k = m + 1; k <= l; ++k) {
-            num *= (double)(4 * k * k - 1);
-            den *= (double)(k * k - m * m);
+            num.mul((double)(4 * k * k - 1));
+            den.mul((double)(k * k - m * m));
         }
-        const double n2 = num / den;
+        const double n2 = num.over(den);
         for (int q = 0; q < (m > 0 ? 2 : 1); ++q) {
             t.chl[ch + q] = l;
             t.chn[ch + q] = sqrt(n2);
@@ -3200,7 +3290,7 @@ int launch_step(sim *h, hipStream_t s, bool field_only, bool with_keys, hipEvent
     };
     mark(KN_SORT_KEY);
     if (with_keys) launch_keys(h, s, kp);
-    const bool fused = (int)gT <= kRankFusedMaxGroups;
+    const bool fused = lo.tu.bucket <= kPlaceMaxBucket;
     const bool lds_scan = fused && ex.nb <= kScanLdsBuckets;
     mark(KN_SCAN_A);
     if (!lds_scan) k_scan_a<<<ex.nb_blocks, kBlock, 0, s>>>(mp, kp, h->hist, h->bsum, ex.nb);

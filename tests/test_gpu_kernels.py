@@ -171,3 +171,37 @@ def test_state_of_index_ids_equals_state_of_any_ids(n):
         assert a["q_surface"] == c["q_surface"] and a["step"] == c["step"]
     if n == 3000:
         assert (out[0][2]["alive"] == 0).any()
+
+
+# Members whose ranking takes the other ways through a tile's placement, among
+# them beside a member of more than a million particles, against the same
+# members ranked by the kernel for large buckets (sort_bucket 64): the order is
+# exact, so the runs are equal bit for bit.
+@pytest.mark.parametrize("n,spread,ties", [(5000, 1.0, False), (3000, 1e-5, False),
+                                           (2500, 0.05, True), (70, 1e-9, True)])
+def test_placement_equals_large_bucket_ranking(n, spread, ties):
+    print(f"[gpu] placement n={n} spread={spread} ties={ties}", file=sys.stderr, flush=True)
+    st = W.uniform_shell(n, 41 + n, 5.0, 0.1)
+    pos = st.pos.copy()
+    r = np.linalg.norm(pos, axis=1)
+    half = np.arange(n) % 2 == 0                      # half of them in a thin shell
+    pos[half] *= ((2.0 + spread * (r - 3.0) / 2.0) / r)[half, None]
+    if ties:                                          # equal radii: mirrored points
+        pos[1::4] = pos[0::4][: len(pos[1::4])] * np.array([-1.0, 1.0, 1.0])
+    ids = np.random.default_rng(n).permutation(n).astype(np.uint32)
+    big = W.uniform_shell(1_050_000, 5, 5.0, 0.1)
+    out = []
+    for bucket, with_big in ((8, False), (8, True), (64, False), (1, False), (32, False)):
+        ms = [S.Member(pos=pos, vel=st.vel, ids=ids, u_asy=np.array([0.2, 0.1, 0.0]),
+                       ntilde=W.ntilde_for(n, 5.0))]
+        if with_big:
+            ms.append(S.Member(pos=big.pos, vel=big.vel, u_asy=np.array([0.2, 0.1, 0.0]),
+                               ntilde=W.ntilde_for(1_050_000, 5.0)))
+        with S.Batch(S.SimParams(l_max=2, sort_bucket=bucket), ms) as b:
+            E = b.eval_field(0)
+            b.step(3)
+            s = b.read_state(0)
+            out.append((E, b.read_response(0, 0, 3), s["pos"], s["vel"], s["alive"]))
+    for o in out[1:]:
+        for a, c in zip(out[0], o):
+            np.testing.assert_array_equal(a, c)
