@@ -1205,6 +1205,28 @@ __device__ inline bool chunk_groups(const Map &mp, const KParams &kp, int j, uin
     return true;
 }
 
+// The value that a DPP control brings to this lane, zero where it brings none
+// (no source lane, or a row of 16 lanes outside kRows).
+template <int kCtrl, int kRows = 0xF>
+__device__ inline double dpp_or_zero(double v)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, kCtrl, kRows, 0xF, false);
+    const uint32_t hi =
+        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), kCtrl, kRows, 0xF, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// A lane's value to all.
+__device__ inline double readlane(double v, int lane)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
 // A running FP64 sum that carries its own rounding error (Knuth's
 // error-free TwoSum): the sum of n terms is good to about one rounding of
 // the result instead of ~sqrt(n) of them.  The carries sum the group sums of
@@ -1248,125 +1270,151 @@ __device__ inline ChannelWeights channel_weights(const Tables &tb, const Seg &sg
     return cw;
 }
 
-// All carries of a member of few groups in one kernel: a block takes kOneCols
-// channels, both sides, with the member's groups in kOneSegs segments of scan
-// order, one (column, segment) per thread; the segments' sums meet in LDS.  Up
-// to kOneCarryGroups groups this replaces three launches of one HBM round trip
-// or two each (10,000 particles, l_max 8: the step 52.8 -> 45.2 us together with
-// the two launches that the steps' ends and the sort keys took; 100,117
-// particles, l_max 16: 97.2 -> 93.5 us).  At 392 groups the kernel takes 12.5 us
-// against 14.6 us for the three; beyond about 512 the segments' walks are longer.
-constexpr int kOneCols = 8, kOneSegs = kBlock / (2 * kOneCols);
-constexpr int kOneCarryGroups = 512;
+// All carries of a member of few groups in one kernel.  A block takes
+// kOneChannels channels, both sides: their sums come to LDS in whole segments
+// of lines, a wave scans a channel's two columns (the groups in 64 runs of scan
+// order, one per lane, then the runs' sums across the wave), and the
+// coefficients go back the same way.  One round trip of loads, where the
+// chunked kernels' three launches take several: 100,117 particles (392 groups)
+// at l_max 16 14.6 us for the three, 10.1 here (4.4 of either are the events
+// around them).  Up to kOneCarryGroups groups (a
+// run of eight).
+constexpr int kOneCarryGroups = kWave * kCarryBatch;
+constexpr int kOneChannels = kWavesPerBlock;   // channels per block
+constexpr int kOneRow = kOneCarryGroups + 1;
 
-__host__ __device__ inline int one_carry_blocks(int C) { return C / kOneCols + 2; }
+// the channels' blocks, one for the charges, one for the response
+__host__ __device__ inline int one_carry_blocks(int C)
+{
+    return (C + kOneChannels - 1) / kOneChannels + 2;
+}
+
+// One step of the wave's inclusive scan of compensated sums.
+template <int kCtrl, int kRows = 0xF>
+__device__ inline void comp_scan_step(CompSum &v)
+{
+    const double ts = dpp_or_zero<kCtrl, kRows>(v.s), te = dpp_or_zero<kCtrl, kRows>(v.e);
+    v.add(ts);
+    v.e += te;
+}
+
+// The compensated sums of the lanes below this one, from the lanes' own.
+__device__ inline CompSum comp_sum_below(CompSum v, CompSum *total)
+{
+    comp_scan_step<0x111>(v);        // row_shr:1, 2, 4, 8
+    comp_scan_step<0x112>(v);
+    comp_scan_step<0x114>(v);
+    comp_scan_step<0x118>(v);
+    comp_scan_step<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+    comp_scan_step<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+    total->s = readlane(v.s, kWave - 1);
+    total->e = readlane(v.e, kWave - 1);
+    CompSum below;
+    below.s = dpp_or_zero<0x138>(v.s);   // wave_shr:1
+    below.e = dpp_or_zero<0x138>(v.e);
+    return below;
+}
 
 __device__ inline void carry_member(const Seg &sg, const Ctl &ct, int block, const double *GS,
                                     const Tables &tb, const KParams &kp, double *CR, double *qpre)
 {
-    __shared__ double ps[kOneSegs][2 * kOneCols], pe[kOneSegs][2 * kOneCols], tot[kOneCols];
-    const int col = threadIdx.x & (2 * kOneCols - 1), sgm = threadIdx.x / (2 * kOneCols);
-    const int side = col / kOneCols, j = col & (kOneCols - 1);
-    const int ng = (int)sg.ng, per = (ng + kOneSegs - 1) / kOneSegs;
-    const int q0 = min(sgm * per, ng), q1 = min(q0 + per, ng);
+    __shared__ double val[2 * kOneChannels][kOneRow];   // interior, exterior columns
+    const int lane = threadIdx.x & 63;
+    const int w = (int)uniform_u32(threadIdx.x >> 6);
+    const int ng = (int)sg.ng, per = (ng + kWave - 1) / kWave;
+    const int q0 = min(lane * per, ng), q1 = min(q0 + per, ng);   // this lane's run
     const size_t sw = (size_t)kp.SW;
     const double *src = GS + (size_t)sg.g0 * sw;
     const int64_t step = ct.step;
     const bool in_run = step >= 0 && step < sg.n_steps;
-    // calls f(group, value) over this thread's segment of a column, in scan
-    // order, with the loads of kCarryBatch groups issued ahead (a segment held
-    // in registers between its two walks: no faster, and 188 VGPRs)
-    auto walk = [&](int column, bool up, auto f) {
-        const double *at = src + column;
-        for (int q = q0; q < q1; q += kCarryBatch) {
-            double v[kCarryBatch];
-#pragma unroll
-            for (int k = 0; k < kCarryBatch; ++k) {
-                const int i = min(q + k, q1 - 1);
-                v[k] = at[(size_t)(up ? i : ng - 1 - i) * sw];
-            }
-#pragma unroll
-            for (int k = 0; k < kCarryBatch; ++k)
-                if (q + k < q1) f(up ? q + k : ng - 1 - q - k, v[k]);
+    const int n_blocks = one_carry_blocks(kp.C);
+    // the sums before each group of this lane's run of a column, given by
+    // get(group): run, and f(group, sum before it) over the run
+    auto scan = [&](bool up, auto get, CompSum *run, CompSum *total) {
+        CompSum part;
+        for (int q = q0; q < q1; ++q) part.add(get(up ? q : ng - 1 - q));
+        *run = comp_sum_below(part, total);
+    };
+    auto walk = [&](bool up, auto get, CompSum run, auto f) {
+        for (int q = q0; q < q1; ++q) {
+            const int g = up ? q : ng - 1 - q;
+            const double v = get(g);
+            f(g, run.value());
+            run.add(v);
         }
     };
-    auto add = [](CompSum &s, double v, double e) {
-        s.add(v);
-        s.e += e;
-    };
-    if (block == one_carry_blocks(kp.C) - 1) {
-        // the probe response: totals of the m = 0 channels of odd l, 16 at a time
+    CompSum run, total;
+    if (block == n_blocks - 1) {
+        // the probe response: totals of the m = 0 channels of odd l, a wave each
         double acc = 0.0;
-        for (int l0 = 1; l0 <= kp.L; l0 += 4 * kOneCols) {
-            const int l = l0 + 2 * col;
-            CompSum part;
-            if (l <= kp.L) walk(kp.C + l - 1, true, [&](int, double t) { part.add(t); });
-            __syncthreads();
-            ps[sgm][col] = part.s;
-            pe[sgm][col] = part.e;
-            __syncthreads();
-            if (threadIdx.x < 2 * kOneCols) {
-                CompSum t;
-                for (int k = 0; k < kOneSegs; ++k) add(t, ps[k][col], pe[k][col]);
-                ps[0][col] = l <= kp.L ? tb.drive_w[l] * tb.chn[l - 1] * t.value() : 0.0;
+        for (int l0 = 1; l0 <= kp.L; l0 += 2 * kWavesPerBlock) {
+            const int l = l0 + 2 * w;
+            double part = 0.0;
+            if (l <= kp.L) {
+                const double *col = src + kp.C + l - 1;
+                scan(true, [&](int g) { return col[(size_t)g * sw]; }, &run, &total);
+                part = tb.drive_w[l] * tb.chn[l - 1] * total.value();
             }
             __syncthreads();
+            if (lane == 0) val[0][w] = part;
+            __syncthreads();
             if (threadIdx.x == 0)
-                for (int k = 0; k < 2 * kOneCols; ++k) acc += ps[0][k];
+                for (int k = 0; k < kWavesPerBlock; ++k) acc += val[0][k];
         }
         if (threadIdx.x == 0 && in_run) sg.qdiff[step] = -acc / sg.ntilde;
         return;
     }
-    const int c = block * kOneCols + j;
-    const bool charge = c == kp.C && side == 0;   // the column past the last channel
-    const bool on = c < kp.C || charge;
-    const int column = charge ? kp.C2 : side * kp.C + c;
-    CompSum part;
-    if (on) walk(column, side == 0, [&](int, double t) { part.add(t); });
-    ps[sgm][col] = part.s;
-    pe[sgm][col] = part.e;
-    __syncthreads();
-    CompSum run;
-    for (int k = 0; k < sgm; ++k) add(run, ps[k][col], pe[k][col]);
-    if (side == 1 && sgm == kOneSegs - 1) {
-        CompSum t = run;
-        add(t, part.s, part.e);
-        tot[j] = t.value();
-    }
-    __syncthreads();
-    if (!on) return;
-    if (charge) {   // charge of the member's particles before each group
-        walk(column, true, [&](int g, double t) {
-            qpre[sg.g0 + g] = run.value();
-            run.add(t);
-        });
+    if (block == n_blocks - 2) {   // charge of the member's particles before each group
+        if (w != 0) return;
+        auto get = [&](int g) { return src[(size_t)g * sw + kp.C2]; };
+        scan(true, get, &run, &total);
+        walk(true, get, run, [&](int g, double carry) { qpre[sg.g0 + g] = carry; });
         return;
     }
-    const ChannelWeights cw = channel_weights(tb, sg, c, kp.L, tot[j], in_run, step);
-    double *dst = CR + (size_t)sg.g0 * kp.C2 + column;
-    walk(column, side == 0, [&](int g, double t) {
-        const double carry = run.value();
-        dst[(size_t)g * kp.C2] = side == 0 ? (carry * cw.w + cw.k) * cw.nrm : carry * cw.w_out;
-        run.add(t);
-    });
+    // thread -> column (interior, then exterior) and group of the copies
+    const int col = threadIdx.x & (2 * kOneChannels - 1), g_first = threadIdx.x / (2 * kOneChannels);
+    constexpr int kStride = kBlock / (2 * kOneChannels);
+    const int c0 = block * kOneChannels, cc = c0 + (col & (kOneChannels - 1));
+    const int column = col < kOneChannels ? cc : kp.C + cc;
+    if (cc < kp.C) {
+        constexpr int kLoads = kOneCarryGroups / kStride;
+        double v[kLoads];
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) {
+            const int g = g_first + k * kStride;
+            if (g < ng) v[k] = src[(size_t)g * sw + column];
+        }
+#pragma unroll
+        for (int k = 0; k < kLoads; ++k) {
+            const int g = g_first + k * kStride;
+            if (g < ng) val[col][g] = v[k];
+        }
+    }
+    __syncthreads();
+    const int c = c0 + w;
+    if (c < kp.C) {
+        double *in = val[w], *ex = val[kOneChannels + w];
+        auto get_ex = [&](int g) { return ex[g]; };
+        auto get_in = [&](int g) { return in[g]; };
+        CompSum run_in, total_in;
+        scan(false, get_ex, &run, &total);
+        scan(true, get_in, &run_in, &total_in);
+        const ChannelWeights cw = channel_weights(tb, sg, c, kp.L, total.value(), in_run, step);
+        walk(false, get_ex, run, [&](int g, double carry) { ex[g] = carry * cw.w_out; });
+        walk(true, get_in, run_in,
+             [&](int g, double carry) { in[g] = (carry * cw.w + cw.k) * cw.nrm; });
+    }
+    __syncthreads();
+    if (cc < kp.C) {
+        double *dst = CR + (size_t)sg.g0 * kp.C2 + column;
+        for (int g = g_first; g < ng; g += kStride) dst[(size_t)g * kp.C2] = val[col][g];
+    }
 }
 
-// Blocks past the n_chunks chunks: the carries of the members of few groups.
 __global__ __launch_bounds__(kBlock) void k_chunk_sums(Map mp, const double *__restrict__ GS,
-                                                       double *__restrict__ chunkS, Tables tb,
-                                                       KParams kp, int n_chunks, double *CR,
-                                                       double *qpre)
+                                                       double *__restrict__ chunkS, KParams kp)
 {
     const int j = blockIdx.x;
-    if (j >= n_chunks) {
-        const int i = (j - n_chunks) * (int)gridDim.y + (int)blockIdx.y;
-        const int per = one_carry_blocks(kp.C), m = i / per;
-        if (m >= kp.n_members) return;
-        const Seg &sg = mp.seg[m];
-        if (!sg.one_carry || !member_runs(sg, mp.ctl[m], kp)) return;
-        carry_member(sg, mp.ctl[m], i % per, GS, tb, kp, CR, qpre);
-        return;
-    }
     const int c = blockIdx.y * kBlock + threadIdx.x;
     if (c >= kp.SW) return;
     uint32_t mb;
@@ -1393,12 +1441,25 @@ __global__ __launch_bounds__(kBlock) void k_chunk_sums(Map mp, const double *__r
 // exterior ones, and the totals T_lm.  The member's chunks, in scan order, are cut into 64 consecutive runs,
 // one per lane: each lane sums its run, the wave scans the run sums, and each
 // lane then writes its run's carries.
+// The blocks past the n_cols of the columns carry the members of few groups
+// (beside this kernel's few blocks and long chains they cost least).
 __global__ __launch_bounds__(kBlock) void k_chunk_scan(Map mp, const double *chunkS,
-                                                       double *chunkC, double *T, KParams kp)
+                                                       double *chunkC, double *T, Tables tb,
+                                                       KParams kp, int n_cols, const double *GS,
+                                                       double *CR, double *qpre)
 {
+    const int s = blockIdx.y;
+    if ((int)blockIdx.x >= n_cols) {
+        const Seg &sg = mp.seg[s];
+        if (!sg.one_carry || !member_runs(sg, mp.ctl[s], kp)) return;
+        // (blocks of neighbouring columns share lines of GS and CR: one XCD)
+        carry_member(sg, mp.ctl[s],
+                     (int)xcd_block(blockIdx.x - (uint32_t)n_cols, gridDim.x - (uint32_t)n_cols),
+                     GS, tb, kp, CR, qpre);
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const int c = (int)uniform_u32(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6));
-    const int s = blockIdx.y;
     if (c >= kp.SW) return;
     const Seg &sg = mp.seg[s];
     if (sg.one_carry || !member_runs(sg, mp.ctl[s], kp)) return;
@@ -1863,26 +1924,6 @@ __device__ inline void far_gradient(const FarPoint<R> &pt, const FarSums<R> &g, 
 // accumulated in FP64.  The rows hold each block twice (entries h + i and
 // h + i + W for the i-th particle of the block starting at entry h = 2 W b),
 // so the partner of every shift is a plain offset.
-
-// The value that a DPP control brings to this lane, zero where it brings none
-// (no source lane, or a row of 16 lanes outside kRows).
-template <int kCtrl, int kRows = 0xF>
-__device__ inline double dpp_or_zero(double v)
-{
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo =
-        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, kCtrl, kRows, 0xF, false);
-    const uint32_t hi =
-        (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), kCtrl, kRows, 0xF, false);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
-__device__ inline double readlane(double v, int lane)
-{
-    const uint64_t u = (uint64_t)__double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), lane);
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-}
 
 // Sums over the lanes of the wave below this one, and above it.  Each runs in
 // its own direction and leaves the own lane out before it adds: the terms
@@ -2688,6 +2729,8 @@ __host__ __device__ inline size_t lw4_32_offset(int L)
 }
 size_t tables32_len(int L) { return lw4_32_offset(L) + 4 * (size_t)(L + 1); }
 
+constexpr unsigned kTableBlocks = 16;   // 4096 threads for up to 2146 entries (l_max 64)
+
 struct TableDst {
     double *tab;
     float *tab32;
@@ -3318,17 +3361,14 @@ int launch_step(sim *h, hipStream_t s, bool field_only, bool with_keys, hipEvent
     }
 #undef MRP_MOMENTS
     mark(KN_CHUNK_SUMS);
-    const int chunks = ex.chunked ? ex.n_chunks : 0;
-    unsigned gOne = 0;   // block columns for the members of few groups
-    if (ex.one_carry)
-        gOne = (unsigned)((ex.n_members * one_carry_blocks(lo.C) + (int)gC - 1) / (int)gC);
-    if (chunks + gOne > 0)   // none in a handle without members
-        k_chunk_sums<<<dim3(chunks + gOne, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkS, h->tb, kp,
-                                                                chunks, h->CR, h->qpre);
-    mark(KN_CHUNK_SCAN);
     if (ex.chunked)
-        k_chunk_scan<<<dim3((lo.C2 + 1 + kWavesPerBlock - 1) / kWavesPerBlock, ex.n_members),
-                       kBlock, 0, s>>>(mp, h->chunkS, h->chunkC, h->T, kp);
+        k_chunk_sums<<<dim3(ex.n_chunks, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkS, kp);
+    mark(KN_CHUNK_SCAN);
+    const unsigned n_cols = ex.chunked ? (lo.C2 + 1 + kWavesPerBlock - 1) / kWavesPerBlock : 0;
+    const unsigned n_one = ex.one_carry ? one_carry_blocks(lo.C) : 0;
+    if (n_cols + n_one > 0)   // none in a handle without members
+        k_chunk_scan<<<dim3(n_cols + n_one, ex.n_members), kBlock, 0, s>>>(
+            mp, h->chunkS, h->chunkC, h->T, h->tb, kp, (int)n_cols, h->GS, h->CR, h->qpre);
     mark(KN_CHUNK_APPLY);
     if (ex.chunked)
         k_chunk_apply<<<dim3(ex.n_chunks, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkC, h->T, h->tb,
@@ -3547,7 +3587,7 @@ int engine_init(sim *h, const sim_params *p, const Layout &lo, void *hip_stream,
     std::vector<Seg> segs((size_t)lo.n_members);   // used = 0
     std::vector<Ctl> ctls((size_t)lo.n_members);
     std::vector<uint32_t> none_t((size_t)lo.n_tiles, kNone), none_c((size_t)lo.n_chunks, kNone);
-    k_tables<<<8, kBlock, 0, h->stream>>>(table_dst(h, *p));
+    k_tables<<<kTableBlocks, kBlock, 0, h->stream>>>(table_dst(h, *p));
     if (hipGetLastError() != hipSuccess ||
         hipMemcpy(h->seg, segs.data(), sizeof(Seg) * segs.size(), hipMemcpyHostToDevice) ||
         hipMemcpy(h->ctl, ctls.data(), sizeof(Ctl) * ctls.size(), hipMemcpyHostToDevice) ||
@@ -3910,18 +3950,17 @@ int scratch_address(void **out)
 
 // The tables and control words a one-member handle would hold before its
 // first step, written by a kernel (the buffer keeps the previous call's
-// contents): the constant tables, the member's description, its control
-// block, the tile and chunk maps and the bucket histogram cleared, and the
-// drive value of the evaluated step.
-__global__ __launch_bounds__(kBlock) void k_static_setup(TableDst t, Seg sg, Ctl ct, Seg *seg,
-                                                         Ctl *ctl, uint32_t *tile_member,
+// contents): the member's description, its control block, the tile and chunk
+// maps and the bucket histogram cleared, and the drive value of the evaluated
+// step.
+__global__ __launch_bounds__(kBlock) void k_static_setup(Seg sg, Ctl ct, Seg *seg, Ctl *ctl,
+                                                         uint32_t *tile_member,
                                                          uint32_t *chunk_member, uint32_t *hist,
                                                          double *u_dev, double u_asy, int n_tiles,
                                                          int n_chunks, int nb)
 {
     const int stride = gridDim.x * blockDim.x;
     const int i0 = blockIdx.x * blockDim.x + threadIdx.x;
-    fill_tables(t, i0, stride);
     for (int i = i0; i < n_tiles; i += stride) tile_member[i] = 0;
     for (int i = i0; i < n_chunks; i += stride) chunk_member[i] = 0;
     for (int i = i0; i <= nb; i += stride) hist[i] = 0;
@@ -3932,11 +3971,18 @@ __global__ __launch_bounds__(kBlock) void k_static_setup(TableDst t, Seg sg, Ctl
     }
 }
 
-// Particle records and sort keys from positions [3n] (particle-major), id = index.
+// Particle records and sort keys from positions [3n] (particle-major), id =
+// index; the blocks past the particles fill the constant tables beside them.
 __global__ __launch_bounds__(kBlock) void k_static_pack(const double *pos, uint32_t n, PRec *A,
                                                         KeyRec *krec, uint32_t *hist,
-                                                        double inv_vol, uint32_t nb)
+                                                        double inv_vol, uint32_t nb, TableDst t)
 {
+    const uint32_t blocks = (n + kBlock - 1) / kBlock;
+    if (blockIdx.x >= blocks) {
+        fill_tables(t, (int)((blockIdx.x - blocks) * kBlock + threadIdx.x),
+                    (int)(kTableBlocks * kBlock));
+        return;
+    }
     __shared__ uint32_t cnt[kWavesPerBlock][kSlotWindow];
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     const bool on = i < n;
@@ -4433,13 +4479,13 @@ int sim_eval_field_static(const sim_params *p, int64_t n, const double *pos, dou
     ct.n_live = (uint32_t)n;
     ct.q_surface = q_surface;
     hipStream_t s = (hipStream_t)hip_stream;
-    // enough threads for the tables (153 entries at l_max 16, 2146 at 64) and the histogram
     const unsigned gSet = 16;
     const unsigned gN = (unsigned)((n + kBlock - 1) / kBlock);
-    k_static_setup<<<gSet, kBlock, 0, s>>>(table_dst(&h, *p), sg, ct, h.seg, h.ctl, h.tile_member,
-                                           h.chunk_member, h.hist, const_cast<double *>(sg.u_asy),
-                                           u_asy, (int)sh.nt, (int)sh.nc, h.lo.nb);
-    k_static_pack<<<gN, kBlock, 0, s>>>(pos, (uint32_t)n, h.A, h.krec, h.hist, sg.inv_vol, sg.nb);
+    k_static_setup<<<gSet, kBlock, 0, s>>>(sg, ct, h.seg, h.ctl, h.tile_member, h.chunk_member, h.hist,
+                                           const_cast<double *>(sg.u_asy), u_asy, (int)sh.nt,
+                                           (int)sh.nc, h.lo.nb);
+    k_static_pack<<<gN + kTableBlocks, kBlock, 0, s>>>(pos, (uint32_t)n, h.A, h.krec, h.hist,
+                                                       sg.inv_vol, sg.nb, table_dst(&h, *p));
     // the field goes straight to the caller's array, by id
     h.Eout = E;
     h.Eid = nullptr;
