@@ -4,14 +4,14 @@
 //
 // One time step (Sec. 3 field solver + Sec. 4 pusher) runs as these kernels:
 //   sort:    key (r^2, id) -> bucket histogram -> bucket offsets -> scatter
-//            -> exact rank inside each bucket -> permuted SoA copy
-//   moments: per tile of 64 radially consecutive particles, the sums of
+//   moments: exact rank inside each bucket and the permuted SoA copy, then per
+//            half tile of 32 radially consecutive particles the sums of
 //            q R_lm (regular solid harmonics) and q I_lm (irregular ones)
 //   carries: exclusive prefix of the interior sums and exclusive suffix of
-//            the exterior sums over tiles, totals T_lm, the boundary (image)
+//            the exterior sums over groups, totals T_lm, the boundary (image)
 //            response, the surface charge, the hemisphere drive and Q_diff
-//   field:   per particle, the far field of all other tiles from the tile's
-//            coefficient vector, the near field of its own tile pair by pair,
+//   field:   per particle, the far field of all other halves from its half's
+//            coefficient vector, the near field of its own half pair by pair,
 //            the self-image correction and the ion background; then the
 //            leapfrog kick/drift, the wall rules and the next step's sort key
 //            and bucket slot (the key kernel keys only what the push did not)
@@ -320,9 +320,9 @@ __device__ inline void wave_lds_sync()
 // steps) they land in a few buckets, and their atomics on the few cache lines
 // of those counts queue up: then the wave counts in LDS first and adds each
 // bucket's count once, neighbouring counts from neighbouring lanes.  1e6
-// electrons and ions at dt 0.01: the field and push kernel 130 -> 40 us, the key kernel
-// 51 -> 20.  Spread wider than
-// kSlotWindow buckets, the atomics already fall on distinct lines.
+// electrons and ions at dt 0.01: the field and push kernel 130 -> 40 us, the
+// key kernel 51 -> 20.  Spread wider than kSlotWindow buckets, the atomics
+// already fall on distinct lines.
 constexpr uint32_t kSlotWindow = 256;
 
 __device__ inline uint32_t take_slot(int lane, bool on, uint32_t b, uint32_t *hist, uint32_t *cnt)
@@ -502,8 +502,10 @@ __device__ inline void member_live(const Map &mp, const uint32_t *off, const KPa
 // SCAN, for histograms of up to kScanLdsBuckets buckets: every block scans the
 // histogram for itself in LDS (the first one stores the offsets for the later
 // kernels), which saves the launch of the offsets kernel: a step of 10,000
-// particles at l_max 8 36.1 -> 35.2 us, with its read-back
-// (100 steps) 38.2 -> 35.8.  A later kernel clears the histogram.
+// particles at l_max 8 36.1 -> 35.2 us, with its share of the read-back
+// (100 steps) 38.2 -> 35.8.  A later kernel clears the histogram.  At 16384
+// buckets every block's scan of 64 KiB costs more than it saves (1e5 particles
+// at l_max 16 83.3 -> 86.8 us per step).
 constexpr int kScanLdsBuckets = 4096;
 
 template <bool SCAN>
@@ -689,7 +691,8 @@ __device__ inline double dpp_shr4_odd_banks(double v)
 // same unit).  Slicing m over the waves, not the particles, keeps the group's
 // scan over its tiles inside a wave, without barriers, and lets a small launch
 // spread one group over several blocks (21,347 particles at l_max 32: the
-// evaluation 344 -> 222 us).  1.6e7 particles, l_max 16: 1.94 -> 1.29 ms.
+// evaluation 344 -> 222 us).  1.6e7 particles, l_max 16: 1.94 -> 1.29 ms, and
+// 1.92 with the ranking (k_moments) that took 0.57 apart.
 template <bool FULL>
 __device__ inline void moment_sums(const double (&x)[kMomParts], const double (&y)[kMomParts],
                                    const double (&z)[kMomParts], const double (&q)[kMomParts],
@@ -1277,8 +1280,11 @@ __device__ inline ChannelWeights channel_weights(const Tables &tb, const Seg &sg
 // coefficients go back the same way.  One round trip of loads, where the
 // chunked kernels' three launches take several: 100,117 particles (392 groups)
 // at l_max 16 14.6 us for the three, 10.1 here (4.4 of either are the events
-// around them).  Up to kOneCarryGroups groups (a
-// run of eight).
+// around them).  Up to kOneCarryGroups groups, a
+// run of eight per lane.  Steps of 5,000 / 30,000 / 128,000 particles, chunked
+// and here, in us: l_max 16 43.7 / 53.8 / 90.3 and 38.0 / 48.1 / 88.5, l_max 32
+// 66.0 / 90.9 / 177.8 and 59.9 / 84.9 / 177.9; room for 960 groups gained 3% at
+// 200,000 particles and l_max 3, but cost the small ones 0.7 us.
 constexpr int kOneCarryGroups = kWave * kCarryBatch;
 constexpr int kOneChannels = kWavesPerBlock;   // channels per block
 constexpr int kOneRow = kOneCarryGroups + 1;
@@ -2050,6 +2056,13 @@ __device__ inline void near_field_full(int lane, int W, int L, const LG *lg, con
 {
     R ck = 0, bx = 0, by = 0, bz = 0;
     const LG c1 = lg[1];
+    // FP32: the constants of the first four degrees and of the last (L - 1) mod 4
+    // stay in scalar registers over the shifts.  Loaded in each shift, the last
+    // ones alone took two waits (4e6 particles, field kernel: l_max 4 233 -> 229
+    // us, 8 306 -> 297, 16 599 -> 588).
+    const int n_last = (L - 1) & 3;
+    const LG f0 = lg[1], f1 = lg[min(2, L)], f2 = lg[min(3, L)], f3 = lg[min(4, L)];
+    const LG e0 = lg[L - n_last], e1 = lg[min(L - n_last + 1, L)], e2 = lg[L - (n_last & 1)];
     const int hl = lane & (W - 1), hb = 2 * (lane & W);
     auto shift = [&](const int sft, R qk_s, bool last) {
         const int j = hb + hl + sft;   // partner, in the doubled block row
@@ -2083,9 +2096,9 @@ __device__ inline void near_field_full(int lane, int W, int L, const LG *lg, con
             S1 = rho * u;
             Sl = S1;
             SB = rho;
-            // two degrees per pass, the registers of degree l and l + 1
-            // trading roles: (Pa, Da, dPa) hold P_l, E_l, P'_l and dPb
-            // P'_{l-1}, which the first half overwrites with P'_{l+1}
+            // the registers of degree l and l + 1 trade roles: (Pa, Da, dPa)
+            // hold P_l, E_l, P'_l and dPb P'_{l-1}, which the first of two
+            // degrees overwrites with P'_{l+1}
             R Pa = u, Da = -w, dPa = 1, dPb = 0, rl = rho, Pb, Db;
             auto degree = [&](const LG c, R &P, R &D, R &dPm, R &Pn, R &Dn) {
                 Dn = fmaf(-(c.z * w), P, D);
@@ -2098,6 +2111,13 @@ __device__ inline void near_field_full(int lane, int W, int L, const LG *lg, con
                 SB = fmaf(rl, dPm, SB);
             };
             int l = 1;
+            if (L > 4) {
+                degree(f0, Pa, Da, dPb, Pb, Db);
+                degree(f1, Pb, Db, dPa, Pa, Da);
+                degree(f2, Pa, Da, dPb, Pb, Db);
+                degree(f3, Pb, Db, dPa, Pa, Da);
+                l = 5;
+            }
 #pragma unroll 1
             for (; l + 3 < L; l += 4) {   // four degrees: one wait for their constants
                 const LG ca = lg[l], cb = lg[l + 1], cc = lg[l + 2], cd = lg[l + 3];
@@ -2106,12 +2126,11 @@ __device__ inline void near_field_full(int lane, int W, int L, const LG *lg, con
                 degree(cc, Pa, Da, dPb, Pb, Db);
                 degree(cd, Pb, Db, dPa, Pa, Da);
             }
-            if (l + 1 < L) {
-                degree(lg[l], Pa, Da, dPb, Pb, Db);
-                degree(lg[l + 1], Pb, Db, dPa, Pa, Da);
-                l += 2;
+            if (n_last & 2) {
+                degree(e0, Pa, Da, dPb, Pb, Db);
+                degree(e1, Pb, Db, dPa, Pa, Da);
             }
-            if (l < L) degree(lg[l], Pa, Da, dPb, Pb, Db);
+            if (n_last & 1) degree(e2, Pa, Da, dPb, Pb, Db);
         } else {
             const R rmin = k_outer ? rj : r;   // r_<
             const R rho = rmin * irmx;
@@ -2497,8 +2516,13 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 && !SPLIT ? 6 :
         double sr = 0.0, sz = 0.0;   // radial and (e_z - c xh) parts of grad Phi_self
         double rl = inv_r2 * inv_r2 * inv_r;   // r^-(2l+3) at l = 1
         if (FULL) {
-            for (int l = L; l >= 1; --l) sr = fma(sr, inv_r2, tb.self_w1[l]);
-            sr *= rl;
+            for (int l = 1; l <= L; ++l) {
+                // (by Horner's rule one operation fewer, but 16 VGPRs spilled
+                // at six waves per SIMD: 4e6 particles at l_max 4, FP32, 233
+                // -> 268 us, l_max 8 306 -> 327, 16 599 -> 610)
+                sr = fma(tb.self_w1[l], rl, sr);
+                rl *= inv_r2;
+            }
             // grad Phi_self = -q sum f_l (l+1)/(4 pi nt) r^-(2l+3) xh; E = -grad
             const double e = qk * inv_nt * sr;
             Ex += e * xh;
