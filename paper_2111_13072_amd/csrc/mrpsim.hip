@@ -2204,15 +2204,19 @@ __device__ inline void near_field_full(int lane, int W, int L, const LG *lg, con
     }
 }
 
-// FP32 (half the LDS rows, fewer registers) runs at six waves per SIMD;
 // NEAR64: FP32 far field with the near field in FP64 (FP32 mode at high l_max).
+// Waves per SIMD as the registers allow without spills: six in FP32, five for
+// NEAR64 (four: 1e6 particles at l_max 32 670 us, five 640) and SPLIT (four:
+// 1e5 particles at l_max 16, FP64, 41.0 us, five 38.6), four for FP64 in
+// groups (five: ten registers spilled, 2e6 at l_max 4 157 -> 163 us).
 // A block is a group, one tile per wave, or, for launches too small to fill the
 // chip that way (SPLIT, split_max_tiles), one tile: each wave takes a slice of
 // the orders m and a part of the pair shifts for all 64 particles, and the
 // first wave adds the four and pushes.  Both forms add the same slices and
 // parts in the same order: a member's results do not depend on the form.
 template <bool FULL, bool FIELD_ONLY, bool FP32, bool NEAR64, bool SPLIT>
-__global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 && !SPLIT ? 6 : 4) void k_field_push(Map mp, State B, PRec *A, uint8_t *dead,
+__global__ __launch_bounds__(kBlock, !FULL ? 8 : SPLIT || NEAR64 ? 5 : FP32 ? 6 : 4)
+                                     void k_field_push(Map mp, State B, PRec *A, uint8_t *dead,
                                                        Grave G, const double *H,
                                                        const double *CR, const double *qpre,
                                                        Tables tb, KParams kp, double *Eout,
@@ -2225,13 +2229,12 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : FP32 && !NEAR64 && !SPLIT ? 6 :
     using RF = typename std::conditional<FP32, float, double>::type;
     using NFF = typename std::conditional<FP32, float4, double4>::type;
     // Per wave: the two halves' coefficients while the far field runs, then
-    // the near field's rows.  The size keeps the block's LDS within a CU's
-    // 160 KB at the kernel's occupancy (four blocks FP64, six FP32) and holds
-    // a window of 288 FP64 channels (all of l_max 16) or 384 FP32 ones; the
-    // second half's coefficients start kHalfPad bytes further, so that the two
+    // the near field's rows.  The size is that of the FP64 rows, keeps the
+    // block's LDS within a CU's 160 KB for up to six blocks and holds a window
+    // of 192 FP64 channels or 384 FP32 ones; the second half's coefficients start kHalfPad bytes further, so that the two
     // addresses of a read fall on different banks.
     constexpr int kHalfPad = 16;
-    constexpr int kLdsBytes = (FP32 && !NEAR64 ? 6144 : 9216) + kHalfPad;
+    constexpr int kLdsBytes = 6144 + kHalfPad;
     static_assert(sizeof(NearRows<R>) <= (size_t)kLdsBytes, "near-field rows exceed the wave's LDS");
     union WaveLds {
         NearRows<R> rows;
