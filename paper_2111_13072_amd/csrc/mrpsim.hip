@@ -3309,12 +3309,15 @@ unsigned slice_orders(const Layout &lo, int n_groups, uint8_t *m_slice)
 
 // Up to this many tiles the field kernel takes a block per tile: a chip's worth
 // of waves hides the latencies that one wave per SIMD cannot, until the
-// repeated setup of four waves per tile costs more.  Field kernel, one form
-// and the other, in us: l_max 16 FP64 10,000 particles 37.6 / 17.0, 131,000 59.8
-// / 42.2, 200,000 69.7 / 60.6, 400,000 113 / 118; l_max 3 30,000 15.7 / 12.7,
-// 65,000 17.8 / 16.8, 131,000 24.4 / 27.9; l_max 8 131,000 32.0 / 32.0; l_max 32
-// FP32 10,000 104 / 35, 400,000 326 / 319.
-int split_max_tiles(int L) { return 600 + 200 * L; }
+// repeated setup of four waves per tile costs more; later with a near field in
+// FP64, whose groups' blocks hold fewer waves per SIMD.  Field kernel, blocks of
+// groups and of tiles, in us.  FP64: l_max 3 85,000 particles 20.2 / 19.5,
+// 100,000 21.0 / 22.0; l_max 8 200,000 42.3 / 40.4, 240,000 42.9 / 44.4; l_max 16
+// 10,000 37.6 / 16.4, 300,000 96 / 86, 450,000 121 / 121; l_max 32 600,000 418 /
+// 383.  FP32 with the near field in FP64: l_max 24 400,000 158 / 151, 600,000 219 /
+// 224; l_max 32 700,000 476 / 452.  FP32: l_max 3 115,000 20.8 / 22.6; l_max 8
+// 200,000 33.5 / 36.0; l_max 16 300,000 68.3 / 70.0.
+int split_max_tiles(int L, bool near_fp32) { return near_fp32 ? 600 + 200 * L : 400 + 350 * L; }
 
 // The push prepares the next step's sort keys unless told otherwise.
 bool keys_in_push(const sim *h) { return h->lo.tu.keys >= 0; }
@@ -3401,7 +3404,7 @@ int launch_step(sim *h, hipStream_t s, bool field_only, bool with_keys, hipEvent
         k_chunk_apply<<<dim3(ex.n_chunks, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkC, h->T, h->tb,
                                                                kp, h->CR, h->qpre);
     mark(KN_FIELD_PUSH);
-    const bool split = lo.full && ex.n_tiles <= split_max_tiles(lo.L);
+    const bool split = lo.full && ex.n_tiles <= split_max_tiles(lo.L, lo.fp32 && !lo.near64);
     uint8_t cuts[kMaxMSlices + 1];
     cut_orders(lo.L, lo.L, kWavesPerBlock, cuts);
     kp.f_ends = 0;

@@ -134,7 +134,7 @@ def test_field_forms_agree_bitwise(L, precision, split):
 
     small = member(577, 21)
     out = []
-    for others in ([], [member(1_100_000 if L < 9 else 140_000, 22)]):
+    for others in ([], [member(1_100_000, 22)]):
         with S.Batch(common, [small] + others) as b:
             E = b.eval_field(0)
             b.step(3)
