@@ -270,9 +270,30 @@ __device__ inline T ld_const(const T *p, int i)
 
 
 // r^2 as (x*x + y*y) + z*z without contraction: the exact radial sort key.
+// (HIP's __dadd_rn and __dmul_rn are plain operators, which the compiler fuses
+// where it likes; the pragma keeps every operation rounded by itself.)
 __device__ inline double key_r2(double x, double y, double z)
 {
-    return __dadd_rn(__dadd_rn(__dmul_rn(x, x), __dmul_rn(y, y)), __dmul_rn(z, z));
+#pragma clang fp contract(off)
+    return (x * x + y * y) + z * z;
+}
+
+// a + b c and a - b c with the product rounded first (the push).
+__device__ inline double add_product(double a, double b, double c)
+{
+#pragma clang fp contract(off)
+    return a + b * c;
+}
+__device__ inline double sub_product(double a, double b, double c)
+{
+#pragma clang fp contract(off)
+    return a - b * c;
+}
+// a . b, every operation rounded by itself.
+__device__ inline double dot3(double ax, double ay, double az, double bx, double by, double bz)
+{
+#pragma clang fp contract(off)
+    return (ax * bx + ay * by) + az * bz;
 }
 
 // ---------------------------------------------------------------------------
@@ -280,10 +301,11 @@ __device__ inline double key_r2(double x, double y, double z)
 // ---------------------------------------------------------------------------
 
 // Bucket of a key: a monotone non-decreasing map of r^2 to the member's
-// buckets [b0, b0 + nb) by enclosed shell volume.  The sort and the rank
-// kernels both use this one expression, so they agree bit for bit.
+// buckets [b0, b0 + nb) by enclosed shell volume.  Every kernel that sorts or
+// ranks uses this one expression, without contraction, so they agree bit for bit.
 __device__ inline uint32_t bucket_of(double r2, double inv_vol, uint32_t b0, uint32_t nb)
 {
+#pragma clang fp contract(off)
     const double t = (r2 * sqrt(r2) - 1.0) * inv_vol * (double)nb;
     uint32_t lb;
     if (!(t > 0.0)) lb = 0;
@@ -2607,12 +2629,12 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : SPLIT || NEAR64 ? 5 : FP32 ? 6 
         vy = B.vy[p];
         vz = B.vz[p];
     }
-    vx = __dadd_rn(vx, __dmul_rn(qm * Ex, dt));
-    vy = __dadd_rn(vy, __dmul_rn(qm * Ey, dt));
-    vz = __dadd_rn(vz, __dmul_rn(qm * Ez, dt));
-    x = __dadd_rn(x, __dmul_rn(vx, dt));
-    y = __dadd_rn(y, __dmul_rn(vy, dt));
-    z = __dadd_rn(z, __dmul_rn(vz, dt));
+    vx = add_product(vx, qm * Ex, dt);
+    vy = add_product(vy, qm * Ey, dt);
+    vz = add_product(vz, qm * Ez, dt);
+    x = add_product(x, vx, dt);
+    y = add_product(y, vy, dt);
+    z = add_product(z, vz, dt);
 
     // ---- walls (tested on the new position) ----
     const double rn = sqrt(key_r2(x, y, z));
@@ -2631,8 +2653,7 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : SPLIT || NEAR64 ? 5 : FP32 ? 6 
             y = y * s;
             z = z * s;
             if (bc == SIM_BC_DIFFUSE) {
-                const double sp = sqrt(__dadd_rn(__dadd_rn(__dmul_rn(vx, vx), __dmul_rn(vy, vy)),
-                                                 __dmul_rn(vz, vz)));
+                const double sp = sqrt(dot3(vx, vy, vz, vx, vy, vz));
                 double inw[3] = {nrm[0], nrm[1], nrm[2]};
                 if (!probe) {
                     inw[0] = -inw[0];
@@ -2645,12 +2666,10 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : SPLIT || NEAR64 ? 5 : FP32 ? 6 
                 vy = sp * d[1];
                 vz = sp * d[2];
             } else {
-                const double vn = __dadd_rn(__dadd_rn(__dmul_rn(vx, nrm[0]), __dmul_rn(vy, nrm[1])),
-                                            __dmul_rn(vz, nrm[2]));
-                const double two_vn = 2.0 * vn;
-                vx = __dsub_rn(vx, __dmul_rn(two_vn, nrm[0]));
-                vy = __dsub_rn(vy, __dmul_rn(two_vn, nrm[1]));
-                vz = __dsub_rn(vz, __dmul_rn(two_vn, nrm[2]));
+                const double two_vn = 2.0 * dot3(vx, vy, vz, nrm[0], nrm[1], nrm[2]);
+                vx = sub_product(vx, two_vn, nrm[0]);
+                vy = sub_product(vy, two_vn, nrm[1]);
+                vz = sub_product(vz, two_vn, nrm[2]);
             }
         }
     }
