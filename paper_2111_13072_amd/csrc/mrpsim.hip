@@ -308,8 +308,8 @@ __device__ inline uint32_t bucket_of(double r2, double inv_vol, uint32_t b0, uin
 #pragma clang fp contract(off)
     const double t = (r2 * sqrt(r2) - 1.0) * inv_vol * (double)nb;
     uint32_t lb;
-    if (!(t > 0.0)) lb = 0;
-    else if (!(t < (double)(nb - 1))) lb = nb - 1;
+    if (!(t < (double)(nb - 1))) lb = nb - 1;   // NaN too: its key sorts above every number's
+    else if (!(t > 0.0)) lb = 0;
     else lb = (uint32_t)t;
     return b0 + lb;
 }

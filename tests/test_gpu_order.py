@@ -54,3 +54,23 @@ def test_order_of_nearly_equal_radii_matches_oracle(keys):
     assert _err(E, O.field(op2, ref.pos)[0]) <= 1e-12
     np.testing.assert_array_equal(out["pos"], ref.pos)
     np.testing.assert_array_equal(out["vel"], ref.vel)
+
+
+# A position that is not a number makes every field one, and none is left out:
+# its key sorts above every number's, so its bucket has to be the last one where
+# a tile selects its records by the key (600 particles in the first bucket's
+# shell, past the ranking's LDS window).
+def test_field_with_a_nan_position_is_written_everywhere():
+    import torch
+
+    n, first = 3000, 600
+    print(f"[gpu] NaN positions n={n}", file=sys.stderr, flush=True)
+    st = W.uniform_shell(n, 57, 5.0, 0.1)
+    pos = st.pos.copy()
+    r = np.linalg.norm(pos, axis=1)
+    pos[:first] *= ((1.0 + 1e-4 * (r - 1.0)) / r)[:first, None]
+    pos[100:300] = np.nan
+    dpos = torch.from_numpy(pos).cuda()
+    E = torch.full_like(dpos, 7.0)
+    S.eval_field_static(S.SimParams(ntilde=W.ntilde_for(n, 5.0), l_max=3), dpos, E)
+    assert bool(torch.isnan(E).all())
