@@ -955,32 +955,181 @@ struct __attribute__((aligned(16))) Parts {
     }
 };
 
-// The ranking inside the moments kernel: each wave of a
-// group's block places a tile, without barriers, its records' gathers issued
-// before the ranking.  Windows of whole buckets around a tile in LDS.
-constexpr int kPlaceWindow = 320;    // records
+// The ranking inside the moments kernel: each wave of a group's block places a
+// tile, its records' gathers issued before the ranking.  A tile's window, the
+// whole buckets around its positions, is ranked from LDS where it fits; where
+// one of the block's four does not (the radial density well over the mean: 8
+// records per bucket leave 80 in a window), every wave selects the records of its
+// tile's slots from its window by counting digits of the key.  A step of 1e6
+// particles at l_max 4, half of them at 10 / 30 / 100 / 1000 times the mean density:
+// 209 / 241 / 275 / 404 us; with the ranking in a kernel of its own (windows of up
+// to 1024 records per block in LDS, longer ones from memory) 247 / 324 / 762 / 3454, and
+// with a counting pass per bit of the key past 320 records 272 / 658 / 881 / 2849.
+// Windows of up to 144 or 420 records in LDS: 238 / 233 and 210 / 250 (290 at 20
+// times), 320 records left to the last ranking instead of 96: 584 at 20 times (229).
+constexpr int kPlaceWindow = 256;    // records of a window in LDS
 constexpr int kPlaceMaxBucket = 32;  // larger mean buckets would not fit the window
+constexpr int kPlaceRead = 4;        // keys a ranking reads at once (past its end, too)
+constexpr int kDigitBits = 8, kDigits = 1 << kDigitBits;
+constexpr int kPlaceSelect = 96;     // records left to a selecting wave for its last ranking
 
-struct PlaceLds {
-    uint64_t key[kPlaceWindow];
-    uint32_t uid[kPlaceWindow];
+union PlaceLds {
+    struct {
+        uint64_t key[kPlaceWindow + kPlaceRead];
+        uint32_t uid[kPlaceWindow];
+    } win;
+    uint32_t hist[2][kDigits];
+    OrdRec sel[kPlaceSelect];
 };
 
-// Places what the tile's positions of the bucket order hold (and what the
-// tile's slots take from outside the group): p_group is the group's first
-// position, count its particles, slot0 its first slot; q the tile; write: to the
-// sorted state too.
+// Calls f(on, record) for the n records from rec on, all lanes in step, the loads
+// of four records per lane issued ahead.
+template <typename F>
+__device__ inline void each_record(const OrdRec *__restrict__ rec, uint32_t n, int lane, F &&f)
+{
+    constexpr uint32_t kBatch = 4;
+    for (uint32_t j0 = 0; j0 < n; j0 += kBatch * kWave) {
+        OrdRec o[kBatch];
+#pragma unroll
+        for (uint32_t k = 0; k < kBatch; ++k) {
+            const uint32_t j = j0 + k * kWave + (uint32_t)lane;
+            o[k] = rec[min(j, n - 1)];
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kBatch; ++k) f(j0 + k * kWave + (uint32_t)lane < n, o[k]);
+    }
+}
+
+// One end of a tile's slots in its window's order: its class of records (those
+// whose key, less the window's smallest, agrees with it above some bit, and, once
+// keys are told apart, whose id does), and the records before and in the class.
+struct PlaceEnd {
+    uint64_t key = 0;
+    uint32_t uid = 0, below = 0, count = 0;
+};
+
+// The records of the window of n from rec on that rank first .. first + tc - 1 in
+// it, by store(rank - first, source slot); all lanes of the wave.  The classes of
+// the two end ranks are narrowed digit by digit, one counting pass each (in all
+// a pass for the smallest and largest key, one per digit and one that collects),
+// until at most kPlaceSelect records lie between; these are ranked in LDS.  1 to 2
+// digits where the density inside a bucket is smooth; the ids' digits count
+// only where that many keys are equal.
+template <typename Store>
+__device__ inline void select_tile(const OrdRec *__restrict__ rec, uint32_t n, uint32_t first,
+                                   uint32_t tc, int lane, PlaceLds &r, Store &&store)
+{
+    uint64_t least = ~0ull, most = 0ull;
+    each_record(rec, n, lane, [&](bool, const OrdRec &o) {
+        least = min(least, o.key);
+        most = max(most, o.key);
+    });
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        least = min(least, (uint64_t)__shfl_xor((unsigned long long)least, o));
+        most = max(most, (uint64_t)__shfl_xor((unsigned long long)most, o));
+    }
+    // the bits of (key - least), then of the id, not yet told apart
+    int kbits = most > least ? 64 - __builtin_clzll(most - least) : 0, ubits = 32;
+    PlaceEnd lo, hi;   // of ranks first and first + tc - 1
+    hi.count = n;
+    auto low_mask = [](int bits) { return bits > 0 ? ~0ull >> (64 - bits) : 0ull; };
+    while (hi.below + hi.count - lo.below > (uint32_t)kPlaceSelect && kbits + ubits > 0) {
+        const bool ids = kbits == 0;
+        int &bits = ids ? ubits : kbits;
+        const uint64_t rest = low_mask(kbits), urest = low_mask(ubits);
+        const int shift = max(bits - kDigitBits, 0);
+        const bool one = lo.key == hi.key && lo.uid == hi.uid;   // one class for both ends
+#pragma unroll
+        for (int k = 0; k < 2 * kDigits / kWave; ++k) r.hist[0][k * kWave + lane] = 0u;
+        wave_lds_sync();
+        each_record(rec, n, lane, [&](bool on, const OrdRec &o) {
+            const uint64_t key = o.key - least;
+            auto in = [&](const PlaceEnd &e) {
+                return (key & ~rest) == e.key && (!ids || (o.uid & ~(uint32_t)urest) == e.uid);
+            };
+            const uint32_t digit =
+                (uint32_t)((ids ? (uint64_t)o.uid : key) >> shift) & (uint32_t)(kDigits - 1);
+            if (on && in(lo)) atomicAdd(&r.hist[0][digit], 1u);
+            if (on && !one && in(hi)) atomicAdd(&r.hist[1][digit], 1u);
+        });
+        wave_lds_sync();
+        auto narrow = [&](PlaceEnd &e, const uint32_t *hist, uint32_t rank) {
+            constexpr int per = kDigits / kWave;
+            uint32_t c[per], sum = 0;
+#pragma unroll
+            for (int k = 0; k < per; ++k) {
+                c[k] = hist[per * lane + k];
+                sum += c[k];
+            }
+            uint32_t incl = sum;
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) {
+                const uint32_t t = __shfl_up(incl, o);
+                if (lane >= o) incl += t;
+            }
+            const uint32_t at = rank - e.below;   // in the class
+            uint32_t digit = (uint32_t)(per * lane), before = incl - sum, count = c[0];
+#pragma unroll
+            for (int k = 1; k < per; ++k)
+                if (before + count <= at) {
+                    before += count;
+                    count = c[k];
+                    ++digit;
+                }
+            // the lane whose digits hold the rank
+            const int src = (int)__builtin_ctzll(__ballot(at < incl) | 1ull << (kWave - 1));
+            const uint64_t d = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)digit, src);
+            e.below += (uint32_t)__builtin_amdgcn_readlane((int)before, src);
+            e.count = (uint32_t)__builtin_amdgcn_readlane((int)count, src);
+            if (ids) e.uid |= (uint32_t)(d << shift);
+            else e.key |= d << shift;
+        };
+        narrow(lo, r.hist[0], first);
+        narrow(hi, r.hist[one ? 0 : 1], first + tc - 1);
+        bits = shift;
+        wave_lds_sync();   // the counts are read
+    }
+    const uint64_t key1 = hi.key | low_mask(kbits);
+    const uint32_t uid1 = hi.uid | (uint32_t)low_mask(ubits);
+    uint32_t got = 0;
+    each_record(rec, n, lane, [&](bool on, const OrdRec &o) {
+        const uint64_t key = o.key - least;
+        const bool in = on && (key > lo.key || (key == lo.key && o.uid >= lo.uid)) &&
+                        (key < key1 || (key == key1 && o.uid <= uid1));
+        const uint64_t v = __ballot(in);
+        const uint32_t at = got + (uint32_t)__popcll(v & ((1ull << lane) - 1ull));
+        if (in && at < (uint32_t)kPlaceSelect) r.sel[at] = o;
+        got += (uint32_t)__popcll(v);
+    });
+    wave_lds_sync();
+    const uint32_t m = min(got, (uint32_t)kPlaceSelect);
+    for (uint32_t i0 = 0; i0 < m; i0 += kWave) {
+        const uint32_t i = i0 + (uint32_t)lane;
+        const OrdRec mine = r.sel[min(i, m - 1)];
+        uint32_t rank = lo.below - first;   // wraps for records before the tile's
+#pragma unroll 4
+        for (uint32_t j = 0; j < m; ++j) {
+            const OrdRec o = r.sel[j];
+            rank += (o.key < mine.key) || (o.key == mine.key && o.uid < mine.uid);
+        }
+        if (i < m && rank < tc) store(rank, mine.idx);
+    }
+    wave_lds_sync();
+}
+
+// Places the tile's particles of the group (and, where the windows are ranked from
+// LDS, what the tile's positions of the bucket order hold for the group's other
+// tiles): p_group is the group's first position, count its particles, slot0 its
+// first slot; q the tile; write: to the sorted state too.  All waves of the block.
 __device__ inline void place_tile(const Seg &sg, const OrdRec *__restrict__ orec,
                                   const uint32_t *__restrict__ off, const PRec *__restrict__ A,
                                   const State &B, bool write, uint32_t p_group, int count,
-                                  size_t slot0, int q, int lane, PlaceLds &r, Parts &out)
+                                  size_t slot0, int q, int lane, PlaceLds &r,
+                                  uint32_t (&dense)[kWavesPerBlock], Parts &out)
 {
     const int tc = min(max(count - q * kWave, 0), kWave);
     if (lane >= tc) out.put(q * kWave + lane, 0.0, 0.0, 2.0, 0.0f);
-    if (tc == 0) return;
-    auto bucket = [&](uint64_t key) {
-        return bucket_of(__longlong_as_double((long long)key), sg.inv_vol, sg.b0, sg.nb);
-    };
     auto store = [&](uint32_t slot, const PRec &a) {
         out.put((int)slot, a.x, a.y, a.z, (a.uid & kIonBit) ? 1.0f : (float)kQ);
         if (!write) return;
@@ -995,157 +1144,88 @@ __device__ inline void place_tile(const Seg &sg, const OrdRec *__restrict__ orec
     };
     const uint32_t pf = p_group + (uint32_t)(q * kWave), pl = pf + (uint32_t)tc - 1;
     const bool on = lane < tc;
-    const OrdRec me = orec[on ? pf + (uint32_t)lane : pl];
-    const PRec a = A[me.idx];
-    const uint32_t b = bucket(me.key);
-    const uint32_t lo = off[b], hi = off[b + 1];
-    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)lo, 0);
-    const uint32_t h0 = (uint32_t)__builtin_amdgcn_readlane((int)hi, 0);
-    const uint32_t l1 = (uint32_t)__builtin_amdgcn_readlane((int)lo, tc - 1);
-    const uint32_t w1 = (uint32_t)__builtin_amdgcn_readlane((int)hi, tc - 1);
-    const uint32_t nw = w1 - w0, before = pf - w0, extra = before + (w1 - 1 - pl);
-    if (nw <= (uint32_t)kPlaceWindow) {
-        // the window's records before and after the tile's positions
-        auto extra_at = [&](uint32_t e) { return e < before ? w0 + e : pl + 1 + (e - before); };
-        OrdRec ex{0ull, 0u, 0u};
-        if ((uint32_t)lane < extra) ex = orec[extra_at(lane)];
-        for (uint32_t e = (uint32_t)(lane + kWave); e < extra; e += kWave) {
-            const OrdRec o = orec[extra_at(e)];
-            r.key[extra_at(e) - w0] = o.key;
-            r.uid[extra_at(e) - w0] = o.uid;
-        }
-        if (on) {
-            r.key[before + lane] = me.key;
-            r.uid[before + lane] = me.uid;
-        }
-        if ((uint32_t)lane < extra) {
-            r.key[extra_at(lane) - w0] = ex.key;
-            r.uid[extra_at(lane) - w0] = ex.uid;
-        }
-        wave_lds_sync();
-        auto ranked = [&](uint64_t k, uint32_t u, uint32_t first, uint32_t end) {
-            uint32_t pos = first;
-            for (uint32_t i = first - w0; i < end - w0; ++i) {
-                const uint64_t ki = r.key[i];
-                pos += (ki < k) || (ki == k && r.uid[i] < u);
-            }
-            return pos - p_group;   // wraps for positions before the group
-        };
-        const uint32_t slot = ranked(me.key, me.uid, lo, hi);
-        if (on && slot < (uint32_t)count) store(slot, a);
-        // records of other groups' positions that rank into this one: in the
-        // buckets across the group's ends
-        for (uint32_t e = (uint32_t)lane; __ballot(e < extra); e += kWave) {
-            const uint32_t p = extra_at(e);
-            const bool out_of_group = e < extra && p - p_group >= (uint32_t)count;
-            if (!__ballot(out_of_group)) continue;
-            if (out_of_group) {
-                const OrdRec o = e < (uint32_t)kWave ? ex : orec[p];
-                const bool low = e < before;
-                const uint32_t es = ranked(o.key, o.uid, low ? w0 : l1, low ? h0 : w1);
-                if (es < (uint32_t)count) store(es, A[o.idx]);
-            }
-        }
-        wave_lds_sync();   // the window is read
+    OrdRec me{0ull, 0u, 0u};
+    PRec a;
+    uint32_t lo = 0, hi = 0, w0 = 0, h0 = 0, l1 = 0, w1 = 0;
+    if (tc > 0) {
+        me = orec[on ? pf + (uint32_t)lane : pl];
+        a = A[me.idx];
+        const uint32_t b =
+            bucket_of(__longlong_as_double((long long)me.key), sg.inv_vol, sg.b0, sg.nb);
+        lo = off[b];
+        hi = off[b + 1];
+        w0 = (uint32_t)__builtin_amdgcn_readlane((int)lo, 0);
+        h0 = (uint32_t)__builtin_amdgcn_readlane((int)hi, 0);
+        l1 = (uint32_t)__builtin_amdgcn_readlane((int)lo, tc - 1);
+        w1 = (uint32_t)__builtin_amdgcn_readlane((int)hi, tc - 1);
+    }
+    const uint32_t nw = w1 - w0;
+    if (lane == 0) dense[q] = nw > (uint32_t)kPlaceWindow ? 1u : 0u;
+    __syncthreads();
+    uint32_t any = 0;
+#pragma unroll
+    for (int k = 0; k < kWavesPerBlock; ++k) any |= dense[k];
+    if (tc == 0) return;
+    if (uniform_u32(any)) {
+        select_tile(orec + w0, nw, pf - w0, (uint32_t)tc, lane, r,
+                    [&](uint32_t i, uint32_t idx) { store((uint32_t)(q * kWave) + i, A[idx]); });
         return;
     }
-    // A window too large for LDS (a radial concentration far over the mean
-    // density): the tile's slots by selection.  The keys (r^2, id) of its first
-    // and last position by bisection over the bits in which the window's keys
-    // differ, one counting pass of the wave per bit (the ids' bits only where
-    // keys are equal), then the records between them, ranked in LDS.
-    uint64_t all = ~0ull, any = 0ull;
-    for (uint32_t j = (uint32_t)lane; j < nw; j += kWave) {
-        const uint64_t k = orec[w0 + j].key;
-        all &= k;
-        any |= k;
+    const uint32_t before = pf - w0, extra = before + (w1 - 1 - pl);
+    // the window's records before and after the tile's positions
+    auto extra_at = [&](uint32_t e) { return e < before ? w0 + e : pl + 1 + (e - before); };
+    OrdRec ex{0ull, 0u, 0u};
+    if ((uint32_t)lane < extra) ex = orec[extra_at(lane)];
+    for (uint32_t e = (uint32_t)(lane + kWave); e < extra; e += kWave) {
+        const OrdRec o = orec[extra_at(e)];
+        r.win.key[extra_at(e) - w0] = o.key;
+        r.win.uid[extra_at(e) - w0] = o.uid;
     }
+    if (on) {
+        r.win.key[before + lane] = me.key;
+        r.win.uid[before + lane] = me.uid;
+    }
+    if ((uint32_t)lane < extra) {
+        r.win.key[extra_at(lane) - w0] = ex.key;
+        r.win.uid[extra_at(lane) - w0] = ex.uid;
+    }
+    wave_lds_sync();
+    // slot in the group of a record whose bucket is [begin, end); the ids only
+    // where another key is equal
+    auto ranked = [&](uint64_t k, uint32_t u, uint32_t begin, uint32_t end) {
+        uint32_t pos = begin, same = 0;
+        for (uint32_t i = begin - w0; i < end - w0; i += kPlaceRead) {
+            uint64_t key[kPlaceRead];
 #pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        all &= (uint64_t)__shfl_xor((unsigned long long)all, o);
-        any |= (uint64_t)__shfl_xor((unsigned long long)any, o);
-    }
-    const uint64_t differ = all ^ any;
-    const int top = differ ? 63 - __builtin_clzll(differ) : -1;   // highest differing bit
-    uint64_t key0 = top < 63 ? all >> (top + 1) << (top + 1) : 0ull, key1 = key0;
-    uint32_t uid0 = 0, uid1 = 0;
-    const uint32_t r0 = pf - w0, r1 = pl - w0;
-    auto count2 = [&](auto f0, auto f1, uint32_t *c0, uint32_t *c1) {
-        *c0 = *c1 = 0;
-        for (uint32_t j = 0; j < nw; j += kWave) {
-            bool s0 = false, s1 = false;
-            if (j + (uint32_t)lane < nw) {
-                const OrdRec o = orec[w0 + j + lane];
-                s0 = f0(o);
-                s1 = f1(o);
+            for (uint32_t t = 0; t < (uint32_t)kPlaceRead; ++t) key[t] = r.win.key[i + t];
+#pragma unroll
+            for (uint32_t t = 0; t < (uint32_t)kPlaceRead; ++t) {
+                const bool has = i + t < end - w0;
+                pos += has && key[t] < k;
+                same += has && key[t] == k;
             }
-            *c0 += (uint32_t)__popcll(__ballot(s0));
-            *c1 += (uint32_t)__popcll(__ballot(s1));
         }
+        if (same > 1)
+            for (uint32_t i = begin - w0; i < end - w0; ++i)
+                pos += r.win.key[i] == k && r.win.uid[i] < u;
+        return pos - p_group;   // wraps for positions before the group
     };
-    uint32_t c0, c1;
-    for (int bit = top; bit >= 0; --bit) {
-        const uint64_t t0 = key0 | 1ull << bit, t1 = key1 | 1ull << bit;
-        count2([&](const OrdRec &o) { return o.key < t0; },
-               [&](const OrdRec &o) { return o.key < t1; }, &c0, &c1);
-        if (c0 <= r0) key0 = t0;
-        if (c1 <= r1) key1 = t1;
-    }
-    count2([&](const OrdRec &o) { return o.key == key0; },
-           [&](const OrdRec &o) { return o.key == key1; }, &c0, &c1);
-    if (c0 <= 1 && c1 <= 1) {
-        uid1 = ~0u;
-    } else {
-        for (int bit = 31; bit >= 0; --bit) {
-            const uint32_t v0 = uid0 | 1u << bit, v1 = uid1 | 1u << bit;
-            count2([&](const OrdRec &o) { return o.key < key0 || (o.key == key0 && o.uid < v0); },
-                   [&](const OrdRec &o) { return o.key < key1 || (o.key == key1 && o.uid < v1); },
-                   &c0, &c1);
-            if (c0 <= r0) uid0 = v0;
-            if (c1 <= r1) uid1 = v1;
+    const uint32_t slot = ranked(me.key, me.uid, lo, hi);
+    if (on && slot < (uint32_t)count) store(slot, a);
+    // records of other groups' positions that rank into this one: in the
+    // buckets across the group's ends
+    for (uint32_t e = (uint32_t)lane; __ballot(e < extra); e += kWave) {
+        const uint32_t p = extra_at(e);
+        const bool out_of_group = e < extra && p - p_group >= (uint32_t)count;
+        if (!__ballot(out_of_group)) continue;
+        if (out_of_group) {
+            const OrdRec o = e < (uint32_t)kWave ? ex : orec[p];
+            const bool low = e < before;
+            const uint32_t es = ranked(o.key, o.uid, low ? w0 : l1, low ? h0 : w1);
+            if (es < (uint32_t)count) store(es, A[o.idx]);
         }
     }
-    uint32_t got = 0;
-    OrdRec mine{0ull, 0u, 0u};
-    for (uint32_t j = 0; j < nw; j += kWave) {
-        bool in = false;
-        OrdRec o{0ull, 0u, 0u};
-        if (j + (uint32_t)lane < nw) {
-            o = orec[w0 + j + lane];
-            in = (o.key > key0 || (o.key == key0 && o.uid >= uid0)) &&
-                 (o.key < key1 || (o.key == key1 && o.uid <= uid1));
-        }
-        const uint64_t v = __ballot(in);
-        const uint32_t at = got + (uint32_t)__popcll(v & ((1ull << lane) - 1ull));
-        if (in && at < (uint32_t)kWave) {   // ids are distinct: exactly tc records
-            r.key[at] = o.key;
-            r.uid[at] = o.uid;
-            reinterpret_cast<uint32_t *>(r.key + kWave)[at] = o.idx;
-        }
-        got += (uint32_t)__popcll(v);
-    }
-    wave_lds_sync();
-    if (on && (uint32_t)lane < got) {
-        mine.key = r.key[lane];
-        mine.uid = r.uid[lane];
-        mine.idx = reinterpret_cast<uint32_t *>(r.key + kWave)[lane];
-        uint32_t rank = 0;
-        for (int i = 0; i < tc; ++i)
-            rank += (r.key[i] < mine.key) || (r.key[i] == mine.key && r.uid[i] < mine.uid);
-        store((uint32_t)(q * kWave) + rank, A[mine.idx]);
-    }
-    // and the small buckets' records at this tile's positions whose slots are
-    // in another tile of the group (that tile may not be selecting)
-    if (on && hi - lo <= (uint32_t)kPlaceWindow) {
-        uint32_t pos = lo;
-        for (uint32_t i = lo; i < hi; ++i) {
-            const OrdRec o = orec[i];
-            pos += (o.key < me.key) || (o.key == me.key && o.uid < me.uid);
-        }
-        const uint32_t slot = pos - p_group;
-        if (slot < (uint32_t)count && slot / kWave != (uint32_t)q) store(slot, a);
-    }
-    wave_lds_sync();
+    wave_lds_sync();   // the window is read
 }
 
 // RANK: the block first puts its group in radial order (place_tile) and goes
@@ -1165,6 +1245,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, const OrdRec *ore
         double buf[kWavesPerBlock][2 * kMomSlots * kMomRow];
     } lds;
     __shared__ __attribute__((aligned(16))) typename std::conditional<RANK, Parts, double>::type part;
+    __shared__ uint32_t dense[kWavesPerBlock];   // whose windows do not fit
     const int lane = threadIdx.x & 63;
     const int w = (int)uniform_u32(threadIdx.x >> 6);
     // (neighbouring groups share gathered lines)
@@ -1188,7 +1269,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, const OrdRec *ore
         const uint32_t live = uniform_u32(off[sg.b0 + sg.nb]) - o0;
         count = live > first ? (int)min(live - first, (uint32_t)kGroupSlots) : 0;
         place_tile(sg, orec, off, A, B, blockIdx.y == 0, o0 + first, count,
-                   (size_t)group * kGroupSlots, w, lane, lds.place[w], part);
+                   (size_t)group * kGroupSlots, w, lane, lds.place[w], dense, part);
         __syncthreads();   // and the ranking's LDS is free for the sums from here on
         part.load(lane, x, y, z, q, ions);
     } else {

@@ -74,3 +74,71 @@ def test_field_with_a_nan_position_is_written_everywhere():
     E = torch.full_like(dpos, 7.0)
     S.eval_field_static(S.SimParams(ntilde=W.ntilde_for(n, 5.0), l_max=3), dpos, E)
     assert bool(torch.isnan(E).all())
+
+
+def _dense_shell(n, times, seed, r_out=5.0):
+    """A uniform shell, every other particle at `times` the mean density from r = 2 outward."""
+    st = W.uniform_shell(n, seed, r_out, 0.02)
+    pos = st.pos.copy()
+    r = np.linalg.norm(pos, axis=1)
+    half = np.arange(n) % 2 == 0
+    u = np.random.default_rng(seed).random(half.sum())
+    rn = (8.0 + u * 0.5 * (r_out ** 3 - 1.0) / times) ** (1.0 / 3.0)
+    pos[half] *= (rn / r[half])[:, None]
+    return pos, st.vel
+
+
+# Tiles whose window of whole buckets is around the ranking's LDS window (8
+# particles per bucket and 12 times the density: buckets of ~100 beside tiles of
+# 64), well past it, whole members in a few buckets, and more equal keys than a
+# selecting wave ranks (their ids decide, by their low digits and their high
+# ones), with tiles and groups partly filled: bit for bit the order of the
+# kernel for large buckets (sort_bucket 64), which the oracle tests pin.
+@pytest.mark.parametrize("n,times,tied,id_shift", [
+    (5000, 12, 0, 0), (5000, 25, 0, 16), (4097, 60, 0, 0), (3001, 1000, 0, 0), (2500, 1, 700, 0),
+    (2500, 1, 700, 15), (130, 1, 129, 23), (257, 1, 257, 0), (66, 1, 66, 8)])
+def test_dense_windows_rank_exactly(n, times, tied, id_shift):
+    print(f"[gpu] dense windows n={n} times={times} tied={tied}", file=sys.stderr, flush=True)
+    pos, vel = _dense_shell(n, times, 90 + n)
+    if tied:
+        signs = np.array([[sx, sy, sz] for sx in (1, -1) for sy in (1, -1) for sz in (1, -1)])
+        pos[:tied] = np.array([1.1, 0.7, 1.5]) * signs[np.arange(tied) % 8]
+    ids = np.random.default_rng(n).permutation(n).astype(np.uint32)
+    ids <<= np.uint32(id_shift)
+    assert ids.max() < 1 << 31
+    out = []
+    for bucket in (8, 64):
+        with S.Sim(S.SimParams(ntilde=W.ntilde_for(n, 5.0), l_max=2, sort_bucket=bucket), pos, vel,
+                   np.array([0.2, 0.1, 0.0]), ids=ids) as sim:
+            E = sim.eval_field()
+            sim.step(3)
+            s = sim.read_state()
+            out.append((E, sim.read_response(0, 3), s["pos"], s["vel"], s["alive"]))
+    assert all(np.isfinite(a).all() for a in out[0])
+    for a, c in zip(*out):
+        np.testing.assert_array_equal(a, c)
+
+
+def test_dense_shell_steps_at_about_the_uniform_speed():
+    """Half of the particles at 30 times the mean density (buckets of ~240) may not
+    step at twice the uniform shell's cost: the ranking in a kernel of its own took
+    1.7 times it, a pass over a tile's window per bit of the key 3.8 times."""
+    import time
+
+    n = 1_000_000
+    best = []
+    for times in (1, 30):
+        print(f"[gpu] dense shell n={n} times={times}", file=sys.stderr, flush=True)
+        pos, vel = _dense_shell(n, times, 7)
+        runs = []
+        with S.Sim(S.SimParams(ntilde=1e9, ion_density=0.0, l_max=4, dt=0.02), pos, vel,
+                   np.zeros(40)) as sim:
+            sim.step(2)
+            sim.sync()
+            for _ in range(8):
+                t = time.perf_counter()
+                sim.step(4)
+                sim.sync()
+                runs.append(time.perf_counter() - t)
+        best.append(min(runs))
+    assert best[1] <= 2.0 * best[0]
