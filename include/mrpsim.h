@@ -246,7 +246,9 @@ int64_t sim_eval_field_static_bytes(const sim_params *p, int64_t n);
 
 /*
  * Run k steps with a HIP event around every kernel and return the average
- * duration in milliseconds of each kernel kind (indices as sim_kernel_name).
+ * duration in milliseconds of each kernel kind (indices as sim_kernel_name; 0
+ * for a step that does not launch the kind, as its size or state decides, and
+ * always for "step_finish", whose work other kernels have taken over).
  * kernel_ms has n_kernels entries; entries beyond sim_num_kernels() are left
  * untouched.  Advances the simulation by k steps.
  */

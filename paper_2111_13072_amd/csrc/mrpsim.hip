@@ -3279,9 +3279,16 @@ void launch_keys(sim *h, hipStream_t s, const KParams &kp)
                                                             kp);
 }
 
+// An event before each kernel kind and after the last, and which kinds a step
+// launched (between the events of one that it did not, only their own time passes).
+struct Marks {
+    hipEvent_t ev[KN_COUNT + 1];
+    bool ran[KN_COUNT];
+};
+
 // One step (or field evaluation).  with_keys: the key kernel comes first; not
 // needed where every running member's last push prepared its keys.
-int launch_step(sim *h, hipStream_t s, bool field_only, bool with_keys, hipEvent_t *ev)
+int launch_step(sim *h, hipStream_t s, bool field_only, bool with_keys, Marks *marks)
 {
     const Layout &lo = h->lo;
     const Extent &ex = h->ext;
@@ -3292,25 +3299,26 @@ int launch_step(sim *h, hipStream_t s, bool field_only, bool with_keys, hipEvent
     const unsigned gT = (unsigned)(ex.n_tiles / kTilesPerGroup);   // one block per group
     const unsigned gC = (unsigned)((lo.C2 + 1 + kBlock - 1) / kBlock);   // group-sum columns
     int e = 0;
-    auto mark = [&](int k) {
-        if (ev) (void)hipEventRecord(ev[k], s);
+    auto mark = [&](int k, bool launched) {
+        if (marks) (void)hipEventRecord(marks->ev[k], s);
+        if (marks) marks->ran[k] = launched;
+        return launched;
     };
-    mark(KN_SORT_KEY);
-    if (with_keys) launch_keys(h, s, kp);
+    if (mark(KN_SORT_KEY, with_keys)) launch_keys(h, s, kp);
     const bool fused = lo.tu.bucket <= kPlaceMaxBucket;
     const bool lds_scan = fused && ex.nb <= kScanLdsBuckets;
-    mark(KN_SCAN_A);
-    if (!lds_scan) k_scan_a<<<ex.nb_blocks, kBlock, 0, s>>>(mp, kp, h->hist, h->bsum, ex.nb);
-    mark(KN_SCAN_C);
-    if (!lds_scan) k_scan_c<<<ex.nb_blocks, kBlock, 0, s>>>(h->hist, h->bsum, h->off, ex.nb);
-    mark(KN_SORT_SCATTER);
+    if (mark(KN_SCAN_A, !lds_scan))
+        k_scan_a<<<ex.nb_blocks, kBlock, 0, s>>>(mp, kp, h->hist, h->bsum, ex.nb);
+    if (mark(KN_SCAN_C, !lds_scan))
+        k_scan_c<<<ex.nb_blocks, kBlock, 0, s>>>(h->hist, h->bsum, h->off, ex.nb);
+    mark(KN_SORT_SCATTER, true);
     if (lds_scan)
         k_sort_scatter<true><<<gN, kBlock, 0, s>>>(mp, h->krec, h->hist, h->off, h->orec, kp);
     else
         k_sort_scatter<false><<<gN, kBlock, 0, s>>>(mp, h->krec, h->hist, h->off, h->orec, kp);
-    mark(KN_SORT_RANK);
-    if (!fused) k_sort_rank_move<<<gN, kBlock, 0, s>>>(mp, h->orec, h->off, h->A, h->B, kp);
-    mark(KN_MOMENTS);
+    if (mark(KN_SORT_RANK, !fused))
+        k_sort_rank_move<<<gN, kBlock, 0, s>>>(mp, h->orec, h->off, h->A, h->B, kp);
+    mark(KN_MOMENTS, true);
     const unsigned gS = slice_orders(lo, (int)gT, kp.m_slice);
 #define MRP_MOMENTS(FULLV, RANKV)                                                       \
     k_moments<FULLV, RANKV><<<dim3(gT, gS), kBlock, 0, s>>>(mp, h->orec, h->off, h->A, h->B, \
@@ -3324,20 +3332,17 @@ int launch_step(sim *h, hipStream_t s, bool field_only, bool with_keys, hipEvent
         else MRP_MOMENTS(false, false);
     }
 #undef MRP_MOMENTS
-    mark(KN_CHUNK_SUMS);
-    if (ex.chunked)
+    if (mark(KN_CHUNK_SUMS, ex.chunked))
         k_chunk_sums<<<dim3(ex.n_chunks, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkS, kp);
-    mark(KN_CHUNK_SCAN);
     const unsigned n_cols = ex.chunked ? (lo.C2 + 1 + kWavesPerBlock - 1) / kWavesPerBlock : 0;
     const unsigned n_one = ex.one_carry ? one_carry_blocks(lo.C) : 0;
-    if (n_cols + n_one > 0)   // none in a handle without members
+    if (mark(KN_CHUNK_SCAN, n_cols + n_one > 0))   // none in a handle without members
         k_chunk_scan<<<dim3(n_cols + n_one, ex.n_members), kBlock, 0, s>>>(
             mp, h->chunkS, h->chunkC, h->T, h->tb, kp, (int)n_cols, h->GS, h->CR, h->qpre);
-    mark(KN_CHUNK_APPLY);
-    if (ex.chunked)
+    if (mark(KN_CHUNK_APPLY, ex.chunked))
         k_chunk_apply<<<dim3(ex.n_chunks, gC), kBlock, 0, s>>>(mp, h->GS, h->chunkC, h->T, h->tb,
                                                                kp, h->CR, h->qpre);
-    mark(KN_FIELD_PUSH);
+    mark(KN_FIELD_PUSH, true);
     const bool split = lo.full && ex.n_tiles <= split_max_tiles(lo.L, lo.fp32 && !lo.near64);
     uint8_t cuts[kMaxMSlices + 1];
     cut_orders(lo.L, lo.L, kWavesPerBlock, cuts);
@@ -3370,8 +3375,8 @@ int launch_step(sim *h, hipStream_t s, bool field_only, bool with_keys, hipEvent
     };
     if (field_only) by_form(yes);
     else by_form(no);
-    mark(KN_STEP_FINISH);   // part of the sort and the moments
-    if (ev) (void)hipEventRecord(ev[KN_COUNT], s);
+    mark(KN_STEP_FINISH, false);   // part of the sort and the moments
+    if (marks) (void)hipEventRecord(marks->ev[KN_COUNT], s);
     hipError_t le = hipGetLastError();
     if (le != hipSuccess) e = fail(SIM_EDEVICE, std::string("kernel launch: ") + hipGetErrorString(le));
     return e;
@@ -4465,18 +4470,19 @@ int sim_profile(sim_t *h, int64_t k, double *kernel_ms, int32_t n_kernels)
     if (k <= 0 || !kernel_ms) return fail(SIM_EINVAL, "k must be > 0 and kernel_ms non-NULL");
     for (const Member &m : h->members)
         if (m.used && m.step_host + k > m.seg.n_steps) return fail(SIM_ERANGE, "steps beyond n_steps");
-    hipEvent_t ev[KN_COUNT + 1];
+    Marks marks;
+    hipEvent_t *ev = marks.ev;
     for (int i = 0; i <= KN_COUNT; ++i)
         if (hipEventCreate(&ev[i]) != hipSuccess) return fail(SIM_EDEVICE, "hipEventCreate failed");
     std::vector<double> acc(KN_COUNT, 0.0);
     for (int64_t s = 0; s < k && rc == SIM_OK; ++s) {
-        rc = launch_step(h, h->stream, false, !keys_in_push(h) || h->keys_needed, ev);
+        rc = launch_step(h, h->stream, false, !keys_in_push(h) || h->keys_needed, &marks);
         h->keys_needed = false;
         if (rc == SIM_OK && hipEventSynchronize(ev[KN_COUNT]) != hipSuccess)
             rc = fail(SIM_EDEVICE, "event sync failed");
         for (int i = 0; i < KN_COUNT && rc == SIM_OK; ++i) {
             float ms = 0.f;
-            if (hipEventElapsedTime(&ms, ev[i], ev[i + 1]) == hipSuccess) acc[i] += ms;
+            if (marks.ran[i] && hipEventElapsedTime(&ms, ev[i], ev[i + 1]) == hipSuccess) acc[i] += ms;
         }
         if (rc == SIM_OK)
             for (Member &m : h->members)
