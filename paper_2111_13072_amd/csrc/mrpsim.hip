@@ -3157,8 +3157,9 @@ void plan_alloc(sim *h, Alloc &al, size_t pool_bytes)
     const Layout &lo = h->lo;
     const size_t n = (size_t)lo.n_tiles * kWave;
     al.add(&h->A, n);
-    al.add(&h->B.x, n); al.add(&h->B.y, n); al.add(&h->B.z, n);
-    al.add(&h->B.vx, n); al.add(&h->B.vy, n); al.add(&h->B.vz, n);
+    // (three columns in one array each: a state read uses them as one [3n]; see carve)
+    al.add(&h->B.x, 3 * n);
+    al.add(&h->B.vx, 3 * n);
     al.add(&h->B.uid, n);
     al.add(&h->G.x, n); al.add(&h->G.y, n); al.add(&h->G.z, n);
     al.add(&h->G.vx, n); al.add(&h->G.vy, n); al.add(&h->G.vz, n);
@@ -3489,13 +3490,18 @@ void bind_device_tables(sim *h)
 
 // Carve the arrays of plan_alloc out of one block at base, in order, each
 // 256-byte aligned.
-void carve(Alloc &al, void *base)
+void carve(sim *h, Alloc &al, void *base)
 {
     char *at = static_cast<char *>(base);
     for (auto &it : al.items) {
         *it.first = at;
         at += align_unit(it.second);
     }
+    const size_t n = (size_t)h->lo.n_tiles * kWave;
+    h->B.y = h->B.x + n;
+    h->B.z = h->B.y + n;
+    h->B.vy = h->B.vx + n;
+    h->B.vz = h->B.vy + n;
 }
 
 // Allocate the arena (the shared arrays and the members' data pool, in one
@@ -3535,7 +3541,7 @@ int engine_init(sim *h, const sim_params *p, const Layout &lo, void *hip_stream,
             return fail(SIM_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
         }
     }
-    carve(al, h->arena);
+    carve(h, al, h->arena);
     h->mdata_units.reset((uint32_t)(std::max<size_t>(pool_bytes, kPoolUnit) / kPoolUnit));
     if (hip_stream) {
         h->stream = (hipStream_t)hip_stream;
@@ -4254,7 +4260,8 @@ int sim_member_read_state(sim_t *h, int32_t index, double *pos, double *vel, uin
         // Put in order on the device and copied once (a search per particle on
         // the host took 10 of the 11 ms that 100,117 particles needed: now 0.41
         // ms).  The sorted copy of the state, rewritten by the next step, is the
-        // room: three arrays of all slots hold the member's [3n] at 3 p0.
+        // room: its three columns of all slots, one array, hold the member's [3n]
+        // at 3 p0.
         const unsigned count = (unsigned)std::max(na, ng);
         double *dp = h->B.x + 3 * p0, *dv = h->B.vx + 3 * p0;
         uint8_t *da = reinterpret_cast<uint8_t *>(h->Eid + p0);
@@ -4406,7 +4413,7 @@ int sim_eval_field_static(const sim_params *p, int64_t n, const double *pos, dou
                                     std::to_string(kScratchBytes) + " B");
     void *base = nullptr;
     if (int rc = scratch_address(&base)) return rc;
-    carve(al, base);
+    carve(&h, al, base);
     bind_device_tables(&h);
     h.ext.n_tiles = (int)sh.nt;
     h.ext.n_chunks = (int)sh.nc;
