@@ -138,8 +138,8 @@ struct Seg {
 
 constexpr uint32_t kNone = 0xffffffffu;
 
-// Per-l and per-(l, m) constant tables (host-computed, read-only).  The
-// super-particle density 1 / ntilde is a per-member factor applied at use.
+// Per-l and per-(l, m) constant tables (filled by fill_tables, read-only after it).
+// The super-particle density 1 / ntilde is a per-member factor applied at use.
 struct Tables {
     const double *ftil;     // image coefficient f_l, with f_0 = 0 (floating probe)
     const double *wl;       // 1 / (2l+1)
@@ -166,8 +166,8 @@ struct Tables {
     const double *chn;
     // FP32 copies of the field kernel's tables for the FP32-compensated mode
     const float4 *fq4_32;
-    // FP32 near field's Legendre recurrence on D_l = P_l - P_{l-1}, per l:
-    // {l / (l+1), -(2l+1) / (l+1), 2l+1, l+1}
+    // FP32 near field's Legendre recurrence on E_l = l (P_l - P_{l-1}), per l:
+    // {1 / (l+1), 0, 2l+1, l+1}
     const float4 *lw4_32;
 };
 
@@ -190,7 +190,6 @@ struct KParams {
     int n_chunks;   // chunk capacity
     int nb;         // bucket capacity
     int n_members;  // member table size
-    int fp32;       // SIM_FP32_COMP
     int field_only; // evaluation without a step: every used member runs
     int fuse_keys;  // the push prepares the next step's sort records
     // moments kernel: slice s of m is [m_slice[s], m_slice[s + 1])
@@ -1230,10 +1229,11 @@ __device__ inline void place_tile(const Seg &sg, const OrdRec *__restrict__ orec
 
 // RANK: the block first puts its group in radial order (place_tile) and goes
 // on with the particles it has in LDS.  Against a ranking kernel of its own
-// this saves a launch and the reads of the sorted state: evaluation of 120,011
-// particles at l_max 16 171 -> 156 us, 1e6 at l_max 1 112 -> 108 us per step, 4e6
-// at l_max 8 0.759 -> 0.742 ms, 1.6e7 at l_max 16 4.955 -> 4.935 ms.  Only mean
-// buckets over kPlaceMaxBucket rank apart.
+// this saves a launch and the reads of the sorted state.  Ranking and moments in
+// kernels of their own and here, in us: 1.6e7 particles at l_max 1 711 / 710, 3 777 /
+// 760, 4 836 / 789, 10 (6e6) 558 / 418 (the older moments kernel beside the ranking);
+// evaluation of 120,011 particles at l_max 16 171 / 156.  Only mean buckets over
+// kPlaceMaxBucket rank apart.
 template <bool FULL, bool RANK>
 __global__ __launch_bounds__(kBlock, 4) void k_moments(Map mp, const OrdRec *orec,
                                                        const uint32_t *off, const PRec *A, State B,
@@ -1817,7 +1817,9 @@ __device__ inline double gauss_field_uniform(double charge, double ntilde, doubl
 //   grad Phi = rhat (1/r) sum [(l - m) Qh U - (2l+1) s_l Qh V]
 //              + (e_z - cos th rhat) sum U D_z Qh + (sum Qh dU/dx, sum Qh dU/dy, 0).
 // (Assembling the radial part from the two partial derivatives of Q instead
-// loses a factor ~l to cancellation.)
+// loses a factor ~l to cancellation.)  The radial bracket is summed as
+// (l + 1/2) Qh W - (m + 1/2) Qh U with W_lm as U_lm but beta - s_l alpha: see
+// far_order_zero.
 // Where the far field reads the coefficients of channel k: interior and
 // exterior side by side at p[2 (k - base)] and p[2 (k - base) + 1] (the
 // channels of a few consecutive degrees lie within one LDS instruction's
@@ -2448,8 +2450,11 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : SPLIT || NEAR64 ? 5 : FP32 ? 6 
             // them, so they go to LDS (the far field reads them as broadcasts, one
             // address per half), in windows of kWin channels (interior and
             // exterior of both halves) that hold whole m blocks; a window moves on
-            // when the next block does not fit (never at l_max <= 16).  An m block
-            // has at most 2 l_max <= 128 channels.
+            // when the next block does not fit (never up to l_max 12 in FP64 and 18
+            // in FP32, or where the waves share the orders, in a wave's slice of
+            // that size; FP64 with room for l_max 16, 9216 B: 2e6 particles 555 / 564
+            // us here, 560 / 552 with it).  An m block has at most 2 l_max <= 128
+            // channels.
             constexpr int kWin = (kLdsBytes - kHalfPad) / (int)sizeof(RF) / 4;
             constexpr int kH1 = 2 * kWin + kHalfPad / (int)sizeof(RF);   // half 1's offset
             static_assert(kWin >= 2 * kMaxL, "an m block must fit a window");
@@ -2474,8 +2479,8 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : SPLIT || NEAR64 ? 5 : FP32 ? 6 
             // time with all their loads issued before the first use.  The first
             // window is filled before the far field starts (no other work of the
             // wave could hide its loads then, and few registers are live: U = 2);
-            // a window moved inside the far field fills two channels at a time at
-            // four waves per SIMD, one at six.
+            // a window moved inside the far field fills two channels at a time, one
+            // in FP32 with the near field in FP32 (six waves per SIMD).
             auto fill = [&](int k0, int len, auto u_tag) {
                 constexpr int U = decltype(u_tag)::value;
                 const int n_iter = (len + kWave - 1) / kWave;
@@ -2769,7 +2774,8 @@ __global__ __launch_bounds__(kBlock, !FULL ? 8 : SPLIT || NEAR64 ? 5 : FP32 ? 6 
     }
     // the next step's sort record of this slot, when the member runs then
     // (the same key, bucket and atomic slot as the key kernel would take;
-    // the histogram was cleared by this step's offsets kernel)
+    // the histogram was cleared by this step's offsets kernel, or by its moments
+    // kernel where the scatter scanned it)
     if (kp.fuse_keys && step + 1 < sg.n_steps) {
         const bool live = valid && !absorbed;
         const double k2 = key_r2(x, y, z);
@@ -2854,7 +2860,7 @@ const char *kKernelNames[KN_COUNT] = {
 struct Tuning {
     int bucket = kBucketOccupancy;   // mean particles per sort bucket
     int chunk = 0;                   // groups per carry chunk, 0: by member size
-    int keys = 0;                    // sort keys: 1 push, -1 own pass, 0 by extent
+    int keys = 0;                    // sort keys: 0 or 1 push, -1 own pass
     int split = 0;                   // near field: 1 half tiles, -1 whole tiles, 0 by member
 };
 
@@ -3249,8 +3255,9 @@ unsigned slice_orders(const Layout &lo, int n_groups, uint8_t *m_slice)
 // groups and of tiles, in us.  FP64: l_max 3 85,000 particles 20.2 / 19.5,
 // 100,000 21.0 / 22.0; l_max 8 200,000 42.3 / 40.4, 240,000 42.9 / 44.4; l_max 16
 // 10,000 37.6 / 16.4, 300,000 96 / 86, 450,000 121 / 121; l_max 32 600,000 418 /
-// 383.  FP32 with the near field in FP64: l_max 24 400,000 158 / 151, 600,000 219 /
-// 224; l_max 32 700,000 476 / 452.  FP32: l_max 3 115,000 20.8 / 22.6; l_max 8
+// 383, l_max 48 1,000,000 1444 / 1309; l_max 64 1,300,000 2939 / 2682.  FP32 with the near
+// field in FP64: l_max 24 400,000 158 / 151, 600,000 219 / 224; l_max 32 700,000 476 / 452;
+// l_max 48 1,000,000 1260 / 1232; l_max 64 1,300,000 2374 / 2420.  FP32: l_max 3 115,000 20.8 / 22.6; l_max 8
 // 200,000 33.5 / 36.0; l_max 16 300,000 68.3 / 70.0.
 int split_max_tiles(int L, bool near_fp32) { return near_fp32 ? 600 + 200 * L : 400 + 350 * L; }
 
@@ -3479,7 +3486,6 @@ void bind_device_tables(sim *h)
     kp.n_chunks = lo.n_chunks;
     kp.nb = lo.nb;
     kp.n_members = lo.n_members;
-    kp.fp32 = lo.fp32 ? 1 : 0;
     kp.field_only = 0;
     kp.fuse_keys = 0;
     h->map.seg = h->seg;

@@ -13,10 +13,12 @@ namespace {
 
 constexpr double kPi = 3.14159265358979323846;
 
-// Layout of the FP64 table block: room for nine per-l arrays (ftil, wl,
-// drive_w, self_w, self_w1 in use) and two (l, m) triangles, then at 32-byte aligned
-// offsets the near-field constants (nf4, lg4) and the rescaled recurrence
-// (fq4) with its zero entry.
+// Layout of the FP64 table block: five per-l arrays (ftil, wl, drive_w, self_w,
+// self_w1), then at 32-byte aligned offsets the near-field constants (nf4, lg4)
+// and the rescaled recurrence (fq4) with its zero entry.  The first offset is that
+// of nine arrays and two (l, m) triangles, and the FP32 block starts two float4 per
+// l in: the sizes are part of what sim_footprint_bytes reports and of which
+// evaluations the static buffer takes, and stay what they were.
 __host__ __device__ inline size_t nf4_offset(int L)
 {
     const size_t base = (size_t)9 * (L + 1) + 2 * (size_t)((L + 1) * (L + 2) / 2);
@@ -28,8 +30,7 @@ __host__ __device__ inline size_t fq4_offset(int L) { return lg4_offset(L) + 4 *
 inline size_t tables_len(int L) { return fq4_offset(L) + 4 * (size_t)((L + 1) * (L + 2) / 2 + 1); }
 
 // FP32 tables of the field kernel, each at a 16-byte aligned offset: the
-// far-field recurrence and the full near field's Legendre constants, after
-// room for two more per-l tables.
+// far-field recurrence and the full near field's Legendre constants.
 __host__ __device__ inline size_t fq4_32_offset(int L) { return 8 * (size_t)(L + 1); }
 __host__ __device__ inline size_t lw4_32_offset(int L)
 {
