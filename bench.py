@@ -50,8 +50,9 @@ def _code_hash(text: str) -> str:
 
 
 def _kernel_source_hash() -> str:
-    p = os.path.join(ROOT, "paper_2111_13072_amd", "csrc", "mrpsim.hip")
-    return _code_hash(open(p).read())
+    csrc = os.path.join(ROOT, "paper_2111_13072_amd", "csrc")
+    return _code_hash("".join(open(os.path.join(csrc, f)).read()
+                              for f in ("mrpsim.hip", "tables.h")))
 
 
 def _traffic_from_profiles(kernel: str, workload: str):

@@ -713,7 +713,7 @@ __device__ inline double dpp_shr4_odd_banks(double v)
 // scan over its tiles inside a wave, without barriers, and lets a small launch
 // spread one group over several blocks (21,347 particles at l_max 32: the
 // evaluation 344 -> 222 us).  1.6e7 particles, l_max 16: 1.94 -> 1.29 ms, and
-// 1.92 with the ranking (k_moments) that took 0.57 apart.
+// 1.84 with the ranking (k_moments) that took 0.57 apart.
 template <bool FULL>
 __device__ inline void moment_sums(const double (&x)[kMomParts], const double (&y)[kMomParts],
                                    const double (&z)[kMomParts], const double (&q)[kMomParts],
